@@ -226,6 +226,7 @@ extern "C" lloid_status lloid_ctx_destroy(lloid_ctx *ctx) {
   if (ctx->pinned) (void)hipHostFree(ctx->pinned);
   if (ctx->d_halfband) (void)hipFree(ctx->d_halfband);
   if (ctx->d_hfrag[0][0]) (void)hipFree(ctx->d_hfrag[0][0]);
+  if (ctx->d_fft_tw) (void)hipFree(ctx->d_fft_tw);
   if (ctx->own_stream && ctx->stream) (void)hipStreamDestroy(ctx->stream);
   delete ctx;
   return LLOID_OK;
@@ -1076,16 +1077,17 @@ extern "C" lloid_status lloid_condition(lloid_ctx *ctx, int32_t full_rate_hz, co
   size_t bytes = 0;
   auto add = [&](size_t cnt, size_t sz) { bytes = (size_t)round_up((int64_t)bytes, 256) + cnt * sz; };
   if (host_strain) add((size_t)n, dtype_size(dtype));
-  add((size_t)n, 4);                       // float strain
   add((size_t)(nseg_p * nf), 4);           // periodograms
-  add((size_t)nf, 4);                      // PSD (FP32 on the device)
   add((size_t)nf, 4);                      // gain
   add((size_t)(nseg_w * L), 4);            // whitened segments
-  if (gating) add((size_t)n, 4), add((size_t)n, 1);
+  if (gating) add((size_t)ceil_div(n, 64), 8);
   if (host_out) add((size_t)n, 4);
-  add(1, 8);
-  add(1, sizeof(int));
+  // results in one block: the gated count, the data flag, the PSD (FP32 on the device)
+  const size_t res_bytes = 16 + (size_t)nf * 4;
+  add(res_bytes, 1);
   lloid_status rs = ensure_ws(ctx, ctx->ws, bytes);
+  if (rs != LLOID_OK) return rs;
+  rs = ensure_pinned(ctx, ctx->pinned, ctx->pinned_bytes, res_bytes);
   if (rs != LLOID_OK) return rs;
   Carve cv{(char *)ctx->ws.base};
   const void *d_strain = strain;
@@ -1094,36 +1096,49 @@ extern "C" lloid_status lloid_condition(lloid_ctx *ctx, int32_t full_rate_hz, co
     HIP_TRY(hipMemcpyAsync(p, strain, (size_t)n * dtype_size(dtype), hipMemcpyHostToDevice, st));
     d_strain = p;
   }
-  float *x = cv.take<float>((size_t)n);
-  float *parts = cv.take<float>((size_t)(nseg_p * nf));
-  float *psd = cv.take<float>((size_t)nf);
-  float *gain = cv.take<float>((size_t)nf);
-  float *y = cv.take<float>((size_t)(nseg_w * L));
-  float *xw = gating ? cv.take<float>((size_t)n) : nullptr;
-  uint8_t *mask = gating ? cv.take<uint8_t>((size_t)n) : nullptr;
-  float *dout = host_out ? cv.take<float>((size_t)n) : out;
-  unsigned long long *count = cv.take<unsigned long long>(1);
-  int *bad = cv.take<int>(1);
-  HIP_TRY(launch_fill_u8(bad, sizeof(int), st));
-  HIP_TRY(launch_fill_u8(count, 8, st));
-  if (gating) HIP_TRY(launch_fill_u8(mask, (size_t)n, st));
-  std::vector<float> psd_h((size_t)nf);
-  if (!estimate) {
-    for (int f = 0; f < nf; ++f) psd_h[f] = (float)opts->psd[f];
-    HIP_TRY(hipMemcpyAsync(psd, psd_h.data(), (size_t)nf * 4, hipMemcpyHostToDevice, st));
+  if (!ctx->d_fft_tw) {   // the first conditioning call of the context makes its transform tables
+    if (hipMalloc(&ctx->d_fft_tw, kCondMaxLen * (sizeof(float2) + sizeof(float))) != hipSuccess) {
+      (void)hipGetLastError();
+      ctx->d_fft_tw = nullptr;
+      return fail(LLOID_ENOMEM, "cannot allocate the transform tables");
+    }
+    ctx->d_fft_win = (float *)(ctx->d_fft_tw + kCondMaxLen);
+    HIP_TRY(launch_fft_tables(ctx->d_fft_tw, ctx->d_fft_win, st));
   }
-  HIP_TRY(launch_convert(d_strain, dtype, n, x, 0, n, 1.f, bad, st));
-  HIP_TRY(launch_condition(x, n, L, estimate, (float)full_rate_hz, parts, psd, gain, y, xw, opts->gate_threshold,
-                           opts->gate_half_width, mask, dout, count, st));
-  int h_bad = 0;
-  unsigned long long h_count = 0;
-  HIP_TRY(hipMemcpyAsync(&h_bad, bad, sizeof h_bad, hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipMemcpyAsync(&h_count, count, sizeof h_count, hipMemcpyDeviceToHost, st));
-  if (psd_out) HIP_TRY(hipMemcpyAsync(psd_h.data(), psd, (size_t)nf * 4, hipMemcpyDeviceToHost, st));
-  if (host_out) HIP_TRY(hipMemcpyAsync(out, dout, (size_t)n * 4, hipMemcpyDeviceToHost, st));
+  CondArgs c;
+  c.T = n;
+  c.estimate = estimate;
+  c.f0 = (float)full_rate_hz;
+  c.gate_thr = opts->gate_threshold;
+  c.gate_half = opts->gate_half_width;
+  c.tw = ctx->d_fft_tw;
+  c.win = ctx->d_fft_win;
+  c.parts = cv.take<float>((size_t)(nseg_p * nf));
+  c.gain = cv.take<float>((size_t)nf);
+  c.y = cv.take<float>((size_t)(nseg_w * L));
+  if (gating) c.loud = cv.take<uint64_t>((size_t)ceil_div(n, 64));
+  c.out = host_out ? cv.take<float>((size_t)n) : out;
+  char *res = cv.take<char>(res_bytes);
+  c.count = (unsigned long long *)res;
+  c.bad = (int *)(res + 8);
+  c.psd = (float *)(res + 16);
+  char *hres = (char *)ctx->pinned;
+  float *hpsd = (float *)(hres + 16);
+  if (estimate) {
+    HIP_TRY(launch_fill_u8(res, 16, st));
+  } else {
+    std::memset(hres, 0, 16);
+    for (int f = 0; f < nf; ++f) hpsd[f] = (float)opts->psd[f];
+    HIP_TRY(hipMemcpyAsync(res, hres, res_bytes, hipMemcpyHostToDevice, st));
+  }
+  HIP_TRY(launch_condition(d_strain, dtype, L, c, st));
+  HIP_TRY(hipMemcpyAsync(hres, res, psd_out ? res_bytes : 16, hipMemcpyDeviceToHost, st));
+  if (host_out) HIP_TRY(hipMemcpyAsync(out, c.out, (size_t)n * 4, hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
+  const int h_bad = *(const int *)(hres + 8);
+  const unsigned long long h_count = *(const unsigned long long *)hres;
   if (psd_out)
-    for (int f = 0; f < nf; ++f) psd_out[f] = (double)psd_h[f];
+    for (int f = 0; f < nf; ++f) psd_out[f] = (double)hpsd[f];
   if (h_bad) return fail(LLOID_EDATA, "strain holds a non-finite sample");
   if (n_gated) *n_gated = (int64_t)h_count;
   return LLOID_OK;

@@ -137,6 +137,8 @@ struct lloid_ctx {
   hipStream_t stream = nullptr;
   bool own_stream = false;
   float *d_halfband = nullptr;  // device copy of g[n] (kHalfTaps floats)
+  float2 *d_fft_tw = nullptr;   // conditioning: transform twiddles and window, one
+  float *d_fft_win = nullptr;   // allocation, made by the first conditioning call
   void *d_hfrag[3][2] = {};     // composite interpolation filters as MFMA fragments,
                                 // [F32, F16, BF16 hi/lo split][R = 2, 4], in one
                                 // allocation at d_hfrag[0][0]
@@ -210,14 +212,30 @@ hipError_t launch_xi2(lloid_dtype t, const MixJob *jobs, int n_jobs, int64_t n_w
 // counts holds trig_blocks(n_elems) slots.
 hipError_t launch_trigger_jobs(const TrigJob *jobs, int n_jobs, int64_t n_elems, float thr, int64_t *counts,
                                int64_t *total, int64_t cap, lloid_trigger *out, hipStream_t s);
-// Conditioning of one block (float strain x[T]): PSD estimate into psd (when
-// estimate; else psd holds the caller's), gain, whitened segments y, overlap-
-// add into xw (or straight into out without gating), gating into out with
-// the gated-sample count added to *count (mask zeroed by the caller).
+// Conditioning of one block of T samples (F64 or F32, on the device): PSD
+// estimate into psd (when estimate; else psd holds the caller's), gain,
+// whitened segments y, overlap-add into out, and, with a gate threshold, the
+// loud samples' bits and the gating of out, whose zeroed samples are added to
+// *count.  *bad is set when a sample is not finite in FP32.
 constexpr int kCondMinLen = 64, kCondMaxLen = 4096;
-hipError_t launch_condition(const float *x, int64_t T, int L, bool estimate, float f0, float *parts,
-                            float *psd, float *gain, float *y, float *xw, float gate_thr, int gate_half,
-                            uint8_t *mask, float *out, unsigned long long *count, hipStream_t s);
+struct CondArgs {
+  int64_t T = 0;
+  bool estimate = false;
+  float f0 = 0.f, gate_thr = 0.f;
+  int64_t gate_half = 0;
+  const float2 *tw = nullptr;      // tables of launch_fft_tables
+  const float *win = nullptr;
+  float *parts = nullptr;          // [segments inside the block][L/2 + 1]
+  float *psd = nullptr, *gain = nullptr;   // [L/2 + 1]
+  float *y = nullptr;              // [segments touching the block][L]
+  uint64_t *loud = nullptr;        // ceil(T / 64) words, gating only
+  float *out = nullptr;
+  unsigned long long *count = nullptr;
+  int *bad = nullptr;
+};
+hipError_t launch_condition(const void *x, lloid_dtype dt, int L, const CondArgs &c, hipStream_t s);
+// Transform tables: kCondMaxLen twiddles, kCondMaxLen window values.
+hipError_t launch_fft_tables(float2 *tw, float *win, hipStream_t s);
 // Coincidences of two sorted trigger lists: per-trigger counts (na slots),
 // their scan, pairs at the scanned offsets; *bad set when a list is out of order.
 hipError_t launch_coincide(const lloid_trigger *a, int64_t na, const lloid_trigger *b, int64_t nb, int64_t max_dt,

@@ -1750,126 +1750,312 @@ __global__ __launch_bounds__(kTrigThreads) void k_trigger_write(const TrigJob *_
 }
 
 // ---------------------------------------------------------- conditioning
-// PSD, whitening and gating before the filter (Sec. II.A).  Each segment of L
-// samples (hop L/2, periodic Hann window) is one workgroup: it loads the
-// windowed samples into LDS and runs a radix-2 Stockham FFT there (two LDS
-// buffers, one barrier per stage, output in natural order).  The PSD launch
-// writes each segment's |X[f]|^2; their mean is taken per bin in FP64.  The
-// whitening launch scales the spectrum by the gain, transforms back and
-// writes the segment; the overlap-add sums the two segments over each sample.
+// PSD, whitening and gating before the filter (Sec. II.A).  A segment of L
+// samples (hop L/2, periodic Hann window) is transformed by L/8 threads with
+// eight points each in registers: radix-2 Stockham stages taken three at a
+// time, one LDS exchange per three stages (three exchanges per 4096-point
+// transform; a barrier and a round trip per radix-2 stage, with the
+// twiddles computed in place, took 59 us for the periodograms and 131 us for
+// the whitening of 2^21 samples).  Twiddles and the window come from tables
+// of the context.  The last stages leave point j + b L/8 in register b of
+// thread j, the layout the input has, so whitening goes from the forward to
+// the inverse transform without an exchange.  Every butterfly is the radix-2
+// one (one product rounded, then a fused multiply-add), whatever the fusing.
 
-// X = DFT(a) over n = 2^lg points with exponent sign * 2 pi i / n; a and b
-// are LDS buffers of n values; returns the one that holds the result.
-__device__ float2 *fft_lds(float2 *a, float2 *b, int n, int lg, float sign) {
-  const int half = n >> 1;
-  for (int st = 0; st < lg; ++st) {
-    const int ns = 1 << st;
-    for (int j = threadIdx.x; j < half; j += blockDim.x) {
-      const int k = j & (ns - 1);
-      const float2 a0 = a[j], a1 = a[j + half];
-      float sn, cs;
-      sincospif(sign * (float)k / (float)ns, &sn, &cs);   // angle sign * 2 pi k / (2 ns)
-      const float tx = a1.x * cs - a1.y * sn, ty = a1.x * sn + a1.y * cs;
-      const int idx = ((j >> st) << (st + 1)) + k;
-      b[idx] = make_float2(a0.x + tx, a0.y + ty);
-      b[idx + ns] = make_float2(a0.x - tx, a0.y - ty);
+// tw[ns + k] = (cos, sin)(pi k / ns), k < ns, for the radix-2 stage that
+// combines transforms of ns points (ns = 1, 2, .. 2048): a stage's twiddles are
+// contiguous in k, so a wave's read is a few lines (one half-turn table read
+// with a stride per stage touched a line per lane).  win[n] = sin(pi n / 4096),
+// n < 4096: shorter segments take every (4096 / L)-th entry.
+constexpr int kFftMax = kCondMaxLen;
+
+__global__ void k_fft_tables(float2 *__restrict__ tw, float *__restrict__ win) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i > 0 && i < kFftMax) {
+    const int ns = 1 << (31 - __clz(i));
+    float sn, cs;
+    sincospif((float)(i - ns) / (float)ns, &sn, &cs);
+    tw[i] = make_float2(cs, sn);
+  }
+  if (i < kFftMax) win[i] = sinpif((float)i / (float)kFftMax);
+}
+
+// (a, b) -> (a + w b, a - w b), w = cos + i SIGN sin of table entry t
+template <int SIGN> __device__ __forceinline__ void fft_bfly(float2 &a, float2 &b, float2 t) {
+  // the window or gain product that made a point is rounded before it is
+  // added here: only the fused multiply-adds written out
+#pragma clang fp contract(off)
+  const float cs = t.x, sn = SIGN < 0 ? -t.y : t.y;
+  const float tx = __builtin_fmaf(b.x, cs, -(b.y * sn)), ty = __builtin_fmaf(b.y, cs, b.x * sn);
+  const float2 a0 = a;
+  a = make_float2(a0.x + tx, a0.y + ty);
+  b = make_float2(a0.x - tx, a0.y - ty);
+}
+
+// LDS place of point i: a pad every 8 points keeps the strided exchange
+// writes off each other's banks
+__device__ __forceinline__ int fft_place(int i) { return i + (i >> 3); }
+
+// In-register transform of the segment's points v[c] = x[j + c L/8]; `buf` is
+// the segment's exchange buffer of L 9/8 values.  Every thread of the
+// workgroup calls it.
+template <int LG, int SIGN>
+__device__ __forceinline__ void fft_regs(float2 (&v)[8], float2 *buf, const float2 *__restrict__ tw, int j) {
+  constexpr int NT = (1 << LG) / 8;
+  constexpr int FULL = LG / 3, REM = LG % 3;
+#pragma unroll
+  for (int p = 0; p < FULL; ++p) {
+    const int st = 3 * p, ns = 1 << st;
+    const int k = j & (ns - 1), m = j >> st;
+    // stage st pairs points c and c + 4, st + 1 points c and c + 2 of those, st + 2 neighbours;
+    // v[c] then holds output (c bit 2, bit 1, bit 0) -> bits 0, 1, 2 of the output number
+    const float2 t0 = tw[ns + k];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) fft_bfly<SIGN>(v[c], v[c + 4], t0);
+#pragma unroll
+    for (int b0 = 0; b0 < 2; ++b0) {
+      const float2 t1 = tw[2 * ns + b0 * ns + k];
+      fft_bfly<SIGN>(v[4 * b0], v[4 * b0 + 2], t1);
+      fft_bfly<SIGN>(v[4 * b0 + 1], v[4 * b0 + 3], t1);
     }
-    __syncthreads();
-    float2 *t = a;
-    a = b;
-    b = t;
+#pragma unroll
+    for (int b0 = 0; b0 < 2; ++b0)
+#pragma unroll
+      for (int b1 = 0; b1 < 2; ++b1)
+        fft_bfly<SIGN>(v[4 * b0 + 2 * b1], v[4 * b0 + 2 * b1 + 1], tw[4 * ns + (b0 + 2 * b1) * ns + k]);
+    float2 o[8];
+#pragma unroll
+    for (int b = 0; b < 8; ++b) o[b] = v[4 * (b & 1) + 2 * ((b >> 1) & 1) + (b >> 2)];
+    if (p == FULL - 1 && REM == 0) {
+#pragma unroll
+      for (int b = 0; b < 8; ++b) v[b] = o[b];   // m = 0: output b sits at j + b L/8
+    } else {
+      if (p > 0) __syncthreads();                // the previous exchange has been read
+#pragma unroll
+      for (int b = 0; b < 8; ++b) buf[fft_place((m << (st + 3)) + (b << st) + k)] = o[b];
+      __syncthreads();
+#pragma unroll
+      for (int c = 0; c < 8; ++c) v[c] = buf[fft_place(j + c * NT)];
+    }
   }
-  return a;
+  if constexpr (REM == 1) {
+    // last stage: points j + c L/8 and the ones half a segment on, outputs in place
+#pragma unroll
+    for (int c = 0; c < 4; ++c) fft_bfly<SIGN>(v[c], v[c + 4], tw[4 * NT + j + c * NT]);
+  }
+  if constexpr (REM == 2) {
+    // last two stages (ns = L/4, L/2): point c = 4 c2 + 2 m + c0 of thread j
+    float2 o[8];
+#pragma unroll
+    for (int c0 = 0; c0 < 2; ++c0) {
+      const float2 t = tw[2 * NT + j + c0 * NT];
+      fft_bfly<SIGN>(v[c0], v[c0 + 4], t);           // m = 0: outputs b0 = 0, 1
+      fft_bfly<SIGN>(v[c0 + 2], v[c0 + 6], t);       // m = 1
+#pragma unroll
+      for (int b0 = 0; b0 < 2; ++b0) {
+        float2 x = v[c0 + 4 * b0], y = v[c0 + 2 + 4 * b0];
+        fft_bfly<SIGN>(x, y, tw[4 * NT + j + (2 * b0 + c0) * NT]);
+        o[2 * b0 + c0] = x;
+        o[4 + 2 * b0 + c0] = y;
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < 8; ++c) v[c] = o[c];
+  }
 }
 
-// One segment per workgroup: segment m = seg0 + blockIdx.x covers samples
-// [m L/2, m L/2 + L) of x (zero outside [0, T)).  WHITEN = false: |X[f]|^2
-// for f <= L/2 into parts; true: X scaled by gain[min(f, L - f)], inverse
-// transform, real part / L into y.
-template <bool WHITEN>
-__global__ __launch_bounds__(256) void k_cond_segment(const float *__restrict__ x, int64_t T, int L, int lg,
-                                                      int64_t seg0, const float *__restrict__ gain,
-                                                      float *__restrict__ parts, float *__restrict__ y) {
-  extern __shared__ float2 cbuf[];   // 2 L values
-  float2 *a = cbuf, *b = cbuf + L;
-  const int64_t lo = (seg0 + (int64_t)blockIdx.x) * (L / 2);
-  for (int n = threadIdx.x; n < L; n += blockDim.x) {
+// Segments m = seg0 + 0 .. nseg - 1 cover samples [m L/2, m L/2 + L) of the
+// strain (zero outside [0, T); converted to FP32 here, a sample that is not
+// finite in FP32 counts as zero and is flagged by the whitening pass, whose
+// segments cover every sample).  WHITEN = false: |X[f]|^2 for f <= L/2 into
+// parts; true: X scaled by gain[min(f, L - f)], inverse transform, real part
+// / L into y.  Workgroups of max(256, L/8) threads: 4096-point segments one
+// each (36 KB of LDS, four workgroups per CU: every segment of 2^21 samples
+// in flight at once), shorter ones several.
+template <int LG> struct CondShape {
+  static constexpr int L = 1 << LG, NT = L / 8;
+  static constexpr int THREADS = NT > 256 ? NT : 256, SEGS = THREADS / NT;
+};
+
+template <int LG, bool WHITEN, typename TI>
+__global__ __launch_bounds__(CondShape<LG>::THREADS) void k_cond_segment(
+    const TI *__restrict__ x, int64_t T, int64_t seg0, int64_t nseg, const float2 *__restrict__ tw,
+    const float *__restrict__ win, const float *__restrict__ gain, float *__restrict__ parts, float *__restrict__ y,
+    int *__restrict__ bad) {
+  typedef CondShape<LG> S;
+  constexpr int L = S::L, NT = S::NT;
+  __shared__ float2 buf[S::SEGS * (L + L / 8)];
+  const int sg = threadIdx.x / NT, j = threadIdx.x % NT;
+  const int64_t s = (int64_t)blockIdx.x * S::SEGS + sg;
+  const bool live = s < nseg;
+  const int64_t lo = (seg0 + s) * (L / 2);
+  float2 v[8];
+  bool finite = true;
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    const int n = j + c * NT;
     const int64_t t = lo + n;
-    const float v = (t >= 0 && t < T) ? x[t] : 0.f;
-    const float s = sinpif((float)n / (float)L);
-    a[n] = make_float2(v * s * s, 0.f);
+    float u = (live && t >= 0 && t < T) ? (float)x[t] : 0.f;
+    if (!isfinite(u)) {
+      finite = false;
+      u = 0.f;
+    }
+    const float h = win[n * (kFftMax / L)];
+    v[c] = make_float2(u * h * h, 0.f);
   }
-  __syncthreads();
-  float2 *X = fft_lds(a, b, L, lg, -1.f);
-  if (!WHITEN) {
-    const int nf = L / 2 + 1;
-    for (int f = threadIdx.x; f < nf; f += blockDim.x)
-      parts[(int64_t)blockIdx.x * nf + f] = X[f].x * X[f].x + X[f].y * X[f].y;
-    return;
+  if (WHITEN && !finite) atomicOr(bad, 1);
+  float2 *seg = buf + sg * (L + L / 8);
+  fft_regs<LG, -1>(v, seg, tw, j);
+  if constexpr (!WHITEN) {
+    if (!live) return;
+    float *out = parts + s * (L / 2 + 1);
+#pragma unroll
+    for (int b = 0; b < 4; ++b) out[j + b * NT] = __builtin_fmaf(v[b].x, v[b].x, v[b].y * v[b].y);
+    if (j == 0) out[L / 2] = __builtin_fmaf(v[4].x, v[4].x, v[4].y * v[4].y);
+  } else {
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+      const int f = j + b * NT;
+      const float g = gain[f <= L / 2 ? f : L - f];
+      v[b] = make_float2(v[b].x * g, v[b].y * g);
+    }
+    __syncthreads();   // the forward transform's last exchange has been read
+    fft_regs<LG, 1>(v, seg, tw, j);
+    if (!live) return;
+    const float inv = 1.f / (float)L;
+#pragma unroll
+    for (int b = 0; b < 8; ++b) y[s * L + j + b * NT] = v[b].x * inv;
   }
-  for (int f = threadIdx.x; f < L; f += blockDim.x) {
-    const float g = gain[f <= L / 2 ? f : L - f];
-    X[f] = make_float2(X[f].x * g, X[f].y * g);
-  }
-  __syncthreads();
-  float2 *Y = fft_lds(X, X == a ? b : a, L, lg, 1.f);
-  const float inv = 1.f / (float)L;
-  for (int n = threadIdx.x; n < L; n += blockDim.x) y[(int64_t)blockIdx.x * L + n] = Y[n].x * inv;
 }
+
+__device__ __forceinline__ float psd_gain(float s, float f0) { return s > 0.f ? 1.f / sqrtf(s * f0 * 0.5f) : 0.f; }
 
 // Per bin f <= L/2: the mean periodogram, c_f / (nseg f0 sum w^2) times the
-// sum over segments (sum w^2 = 3 L / 8 for the periodic Hann window).  The
-// sum over segments is compensated (Kahan): in FP32 its error stays at a few
-// units of rounding whatever the number of segments.
-__global__ void k_psd_mean(const float *__restrict__ parts, int64_t nseg, int L, float f0, float *__restrict__ psd) {
+// sum over segments (sum w^2 = 3 L / 8 for the periodic Hann window), and the
+// whitening gain.  The sum over segments is compensated (Kahan): in FP32 its
+// error stays at a few units of rounding whatever the number of segments.
+// The sum is one dependent chain of four additions per segment, 64 bins to a
+// wave, so the reads have to run ahead of it: four waves read the next
+// 4 kPsdU segments into registers while the first adds the current ones from
+// LDS.  1023 segments of 2049 bins: 255 us with a read per addition waited for
+// in turn, 25 us with one wave reading 32 segments ahead, 19 us like this.
+constexpr int kPsdU = 32;
+
+__global__ __launch_bounds__(256) void k_psd_mean(const float *__restrict__ parts, int64_t nseg, int L, float f0,
+                                                  float *__restrict__ psd, float *__restrict__ gain) {
+  constexpr int U = kPsdU, TILE = 4 * U;
+  __shared__ float tile[2][TILE][64];
   const int nf = L / 2 + 1;
-  const int f = blockIdx.x * blockDim.x + threadIdx.x;
-  if (f >= nf) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int f = blockIdx.x * 64 + lane;
+  const int fl = f < nf ? f : nf - 1;
+  float r[U];
+  // this wave's U segments of tile t (past the last segment: the last again, not added)
+  auto read = [&](int64_t t) __attribute__((always_inline)) {
+    const int64_t m0 = t * TILE + wave * U;
+    const float *row = parts + min<int64_t>(m0, nseg - 1) * nf;
+    const int more = (int)min<int64_t>(U, nseg - 1 - m0);   // steps that stay inside
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      r[u] = row[fl];
+      row += u < more ? nf : 0;
+    }
+  };
   float acc = 0.f, comp = 0.f;
-  for (int64_t m = 0; m < nseg; ++m) {
-    const float y = parts[m * nf + f] - comp;
-    const float t = acc + y;
-    comp = (t - acc) - y;
-    acc = t;
+  const int64_t nt = (nseg + TILE - 1) / TILE;
+  read(0);
+  for (int64_t t = 0; t < nt; ++t) {
+    float(*tl)[64] = tile[t & 1];
+#pragma unroll
+    for (int u = 0; u < U; ++u) tl[wave * U + u][lane] = r[u];
+    __syncthreads();   // tile t is whole; tile t - 1 has been added (its buffer is next)
+    if (t + 1 < nt) read(t + 1);
+    if (wave == 0) {
+      const int n = (int)min<int64_t>(TILE, nseg - t * TILE);
+#pragma unroll 16
+      for (int u = 0; u < n; ++u) {
+        const float y = tl[u][lane] - comp;
+        const float s = acc + y;
+        comp = (s - acc) - y;
+        acc = s;
+      }
+    }
   }
+  if (wave != 0 || f >= nf) return;
   const float c = (f == 0 || f == L / 2) ? 1.f : 2.f;
-  psd[f] = c * acc / ((float)nseg * f0 * (0.375f * (float)L));
+  const float s = c * acc / ((float)nseg * f0 * (0.375f * (float)L));
+  psd[f] = s;
+  gain[f] = psd_gain(s, f0);
 }
 
 __global__ void k_psd_gain(const float *__restrict__ psd, int nf, float f0, float *__restrict__ gain) {
   const int f = blockIdx.x * blockDim.x + threadIdx.x;
-  if (f >= nf) return;
-  const float s = psd[f];
-  gain[f] = s > 0.f ? 1.f / sqrtf(s * f0 * 0.5f) : 0.f;
+  if (f < nf) gain[f] = psd_gain(psd[f], f0);
 }
 
-// xw[n] = the two segments' outputs over sample n (segment m starts at m L/2;
-// y holds segments seg0, seg0 + 1, ...)
-__global__ void k_overlap_add(const float *__restrict__ y, int64_t T, int L, int64_t seg0, float *__restrict__ xw) {
-  const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= T) return;
-  const int64_t h = L / 2;
-  const int64_t mb = n / h, ma = mb - 1;
-  xw[n] = y[(ma - seg0) * L + (n - ma * h)] + y[(mb - seg0) * L + (n - mb * h)];
+// out[n] = the two segments' outputs over sample n (segment m starts at m h,
+// h = L/2 = 2^lgh; y holds segments seg0, seg0 + 1, ...).  loud: NULL, or one
+// bit per sample, set where |out[n]| > thr.
+constexpr int kOverlapPer = 4;   // samples per thread, 256 apart
+
+__global__ __launch_bounds__(256) void k_overlap_add(const float *__restrict__ y, int64_t T, int lgh, int64_t seg0,
+                                                     float thr, float *__restrict__ out,
+                                                     uint64_t *__restrict__ loud) {
+  const int64_t b0 = (int64_t)blockIdx.x * (256 * kOverlapPer) + threadIdx.x;
+#pragma unroll
+  for (int q = 0; q < kOverlapPer; ++q) {
+    const int64_t n = b0 + 256 * q;
+    bool l = false;
+    if (n < T) {
+      const int64_t mb = n >> lgh, ma = mb - 1;
+      const float v = y[((ma - seg0) << (lgh + 1)) + (n - (ma << lgh))] +
+                      y[((mb - seg0) << (lgh + 1)) + (n - (mb << lgh))];
+      out[n] = v;
+      l = fabsf(v) > thr;
+    }
+    if (loud) {
+      const uint64_t m = __ballot(l);
+      if ((threadIdx.x & 63) == 0 && n < T) loud[n >> 6] = m;
+    }
+  }
 }
 
-// mask[k] = 1 for every k within half_width of a sample with |xw| > thr
-__global__ void k_gate_mark(const float *__restrict__ xw, int64_t T, float thr, int half_width,
-                            uint8_t *__restrict__ mask) {
-  const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= T || !(fabsf(xw[n]) > thr)) return;
-  const int64_t a = n - half_width < 0 ? 0 : n - half_width;
-  const int64_t e = n + half_width + 1 > T ? T : n + half_width + 1;
-  for (int64_t k = a; k < e; ++k) mask[k] = 1;
-}
+// Zeroes every sample within half_width of a loud one and counts them.  A
+// workgroup first looks for any loud sample in its reach (its own samples and
+// half_width on each side): transients are rare, so nearly all leave there.
+constexpr int kGateSpan = 512;    // samples per workgroup
+constexpr int kGateWords = 1024;  // words of its reach kept in LDS (half widths up to 32 thousand samples)
 
-__global__ void k_gate_apply(const float *__restrict__ xw, const uint8_t *__restrict__ mask, int64_t T,
-                             float *__restrict__ out, unsigned long long *__restrict__ count) {
-  const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const bool g = n < T && mask[n];
-  if (n < T) out[n] = g ? 0.f : xw[n];
-  const uint64_t m = __ballot(g);
-  if ((threadIdx.x & 63) == 0 && m) atomicAdd(count, (unsigned long long)__popcll(m));
+__global__ __launch_bounds__(256) void k_gate(const uint64_t *__restrict__ loud, int64_t T, int64_t half_width,
+                                              float *__restrict__ out, unsigned long long *__restrict__ count) {
+  __shared__ uint64_t lw[kGateWords];
+  const int64_t n0 = (int64_t)blockIdx.x * kGateSpan;
+  const int64_t w0 = max<int64_t>(0, n0 - half_width) >> 6;
+  const int64_t w1 = min<int64_t>(T - 1, n0 + kGateSpan - 1 + half_width) >> 6;
+  int any = 0;
+  for (int64_t w = w0 + threadIdx.x; w <= w1; w += 256) {
+    const uint64_t m = loud[w];
+    any |= m != 0;
+    if (w - w0 < kGateWords) lw[w - w0] = m;
+  }
+  if (!__syncthreads_or(any)) return;
+  const uint64_t *words = w1 - w0 < kGateWords ? lw : loud + w0;
+  for (int q = 0; q < kGateSpan / 256; ++q) {
+    const int64_t n = n0 + q * 256 + threadIdx.x;
+    bool g = false;
+    if (n < T) {
+      const int64_t a = max<int64_t>(0, n - half_width), e = min<int64_t>(T - 1, n + half_width);
+      for (int64_t w = a >> 6; w <= (e >> 6) && !g; ++w) {
+        uint64_t m = words[w - w0];
+        if (w == (a >> 6)) m &= ~0ull << (a & 63);
+        if (w == (e >> 6)) m &= ~0ull >> (63 - (e & 63));
+        g = m != 0;
+      }
+      if (g) out[n] = 0.f;
+    }
+    const uint64_t m = __ballot(g);
+    if ((threadIdx.x & 63) == 0 && m) atomicAdd(count, (unsigned long long)__popcll(m));
+  }
 }
 
 // ---------------------------------------------------------- coincidence
@@ -2163,25 +2349,47 @@ hipError_t launch_xi2(lloid_dtype t, const MixJob *jobs, int n_jobs, int64_t n_w
   return hipGetLastError();
 }
 
-hipError_t launch_condition(const float *x, int64_t T, int L, bool estimate, float f0, float *parts,
-                            float *psd, float *gain, float *y, float *xw, float gate_thr, int gate_half,
-                            uint8_t *mask, float *out, unsigned long long *count, hipStream_t s) {
-  int lg = 0;
-  while ((1 << lg) < L) ++lg;
-  const size_t lds = (size_t)2 * L * sizeof(float2);
-  const int nf = L / 2 + 1;
-  if (estimate) {
-    const int64_t nseg = (T - L) / (L / 2) + 1;
-    k_cond_segment<false><<<(unsigned)nseg, 256, lds, s>>>(x, T, L, lg, 0, nullptr, parts, nullptr);
-    k_psd_mean<<<blocks_for(nf, 256), 256, 0, s>>>(parts, nseg, L, f0, psd);
+hipError_t launch_fft_tables(float2 *tw, float *win, hipStream_t s) {
+  k_fft_tables<<<kFftMax / 256, 256, 0, s>>>(tw, win);
+  return hipGetLastError();
+}
+
+template <int LG, typename TI>
+static void cond_passes(const TI *x, const CondArgs &c, hipStream_t s) {
+  typedef CondShape<LG> S;
+  constexpr int L = S::L, nf = L / 2 + 1;
+  if (c.estimate) {
+    const int64_t nseg = (c.T - L) / (L / 2) + 1;
+    k_cond_segment<LG, false, TI><<<blocks_for(nseg, S::SEGS), S::THREADS, 0, s>>>(x, c.T, 0, nseg, c.tw, c.win, nullptr,
+                                                                                    c.parts, nullptr, nullptr);
+    k_psd_mean<<<blocks_for(nf, 64), 256, 0, s>>>(c.parts, nseg, L, c.f0, c.psd, c.gain);
+  } else {
+    k_psd_gain<<<blocks_for(nf, 256), 256, 0, s>>>(c.psd, nf, c.f0, c.gain);
   }
-  k_psd_gain<<<blocks_for(nf, 256), 256, 0, s>>>(psd, nf, f0, gain);
-  const int64_t nseg_w = (2 * (T - 1)) / L + 2;   // segments -1 .. floor(2 (T - 1) / L)
-  k_cond_segment<true><<<(unsigned)nseg_w, 256, lds, s>>>(x, T, L, lg, -1, gain, nullptr, y);
-  k_overlap_add<<<blocks_for(T, 256), 256, 0, s>>>(y, T, L, -1, gate_thr > 0.f ? xw : out);
-  if (gate_thr > 0.f) {
-    k_gate_mark<<<blocks_for(T, 256), 256, 0, s>>>(xw, T, gate_thr, gate_half, mask);
-    k_gate_apply<<<blocks_for(T, 256), 256, 0, s>>>(xw, mask, T, out, count);
+  const int64_t nseg_w = (2 * (c.T - 1)) / L + 2;   // segments -1 .. floor(2 (T - 1) / L)
+  k_cond_segment<LG, true, TI><<<blocks_for(nseg_w, S::SEGS), S::THREADS, 0, s>>>(x, c.T, -1, nseg_w, c.tw, c.win, c.gain,
+                                                                                   nullptr, c.y, c.bad);
+  const bool gating = c.gate_thr > 0.f;
+  k_overlap_add<<<blocks_for(c.T, 256 * kOverlapPer), 256, 0, s>>>(c.y, c.T, LG - 1, -1, c.gate_thr, c.out,
+                                                                    gating ? c.loud : nullptr);
+  if (gating) k_gate<<<blocks_for(c.T, kGateSpan), 256, 0, s>>>(c.loud, c.T, c.gate_half, c.out, c.count);
+}
+
+hipError_t launch_condition(const void *x, lloid_dtype dt, int L, const CondArgs &c, hipStream_t s) {
+  auto go = [&](auto lg) {
+    constexpr int LG = decltype(lg)::value;
+    if (dt == LLOID_F64) cond_passes<LG>((const double *)x, c, s);
+    else cond_passes<LG>((const float *)x, c, s);
+  };
+  switch (L) {
+    case 64: go(std::integral_constant<int, 6>{}); break;
+    case 128: go(std::integral_constant<int, 7>{}); break;
+    case 256: go(std::integral_constant<int, 8>{}); break;
+    case 512: go(std::integral_constant<int, 9>{}); break;
+    case 1024: go(std::integral_constant<int, 10>{}); break;
+    case 2048: go(std::integral_constant<int, 11>{}); break;
+    case 4096: go(std::integral_constant<int, 12>{}); break;
+    default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
