@@ -986,9 +986,16 @@ static lloid_status filter_banks(lloid_bank *const *banks, int nb, int32_t detec
     for (int i = 0; i < nb; ++i) {
       const size_t ld = (size_t)peaks[i].n_windows;   // the caller's rows may be wider than W
       const size_t F = (size_t)banks[i]->n_templates;
-      if (peaks[i].snr) HIP_TRY(hipMemcpy2DAsync(peaks[i].snr, ld * 4, bw[i].psnr, W * 4, W * 4, F, hipMemcpyDefault, st));
-      if (peaks[i].sample) HIP_TRY(hipMemcpy2DAsync(peaks[i].sample, ld * 8, bw[i].pn, W * 8, W * 8, F, hipMemcpyDefault, st));
-      if (peaks[i].phase) HIP_TRY(hipMemcpy2DAsync(peaks[i].phase, ld * 4, bw[i].pphase, W * 4, W * 4, F, hipMemcpyDefault, st));
+      // tables of the caller's width are one run: a 2D copy to pageable memory
+      // goes row by row (7 us each: 22 of the 23.6 ms of a 48 s call with 1024 rows)
+      auto table = [&](void *dst, const void *src, size_t esz2) -> hipError_t {
+        if (!dst) return hipSuccess;
+        if (ld == (size_t)W) return hipMemcpyAsync(dst, src, F * W * esz2, hipMemcpyDefault, st);
+        return hipMemcpy2DAsync(dst, ld * esz2, src, W * esz2, W * esz2, F, hipMemcpyDefault, st);
+      };
+      HIP_TRY(table(peaks[i].snr, bw[i].psnr, 4));
+      HIP_TRY(table(peaks[i].sample, bw[i].pn, 8));
+      HIP_TRY(table(peaks[i].phase, bw[i].pphase, 4));
       peaks[i].n_windows = W;
     }
   if (host_snr)
