@@ -234,7 +234,8 @@ lloid_status lloid_filter(lloid_bank *bank, int32_t detector,
  * buffer of the call comes from one static array per GPU of
  * LLOID_NOALLOC_SCRATCH_BYTES, part of the library's code object (held until
  * the process ends); windows are processed in chunks sized to fit it, and the
- * descriptor tables are staged in pageable host memory.  The call makes no
+ * descriptor tables are staged in the context's 256 KiB of pinned memory or,
+ * when they do not fit there, in pageable host memory.  The call makes no
  * hipMalloc, hipHostMalloc or hipFree and records no profiling events.
  * ENOMEM, before any device work, when one window per chunk (the strain
  * levels, the peak tables, trig_cap trigger records and, for host strain, a

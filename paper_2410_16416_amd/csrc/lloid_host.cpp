@@ -132,6 +132,11 @@ extern "C" lloid_status lloid_ctx_create(int device, void *hip_stream, lloid_ctx
   c->device = device;
   c->n_cu = prop.multiProcessorCount;
   c->static_scratch = scr;
+  if (hipHostMalloc(&c->stage, kStageBytes, hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    delete c;
+    return fail(LLOID_ENOMEM, "pinned staging of %zu bytes failed", kStageBytes);
+  }
   // tile shapes: the defaults, or those named by LLOID_FIR_VARIANT / LLOID_MIX_VARIANT
   if (const char *v = getenv("LLOID_FIR_VARIANT")) c->fir_variant = std::min(std::max(atoi(v), 0), kFirVariants - 1);
   if (const char *v = getenv("LLOID_MIX_VARIANT")) c->mix_variant = std::min(std::max(atoi(v), 0), kMixVariants - 1);
@@ -139,6 +144,7 @@ extern "C" lloid_status lloid_ctx_create(int device, void *hip_stream, lloid_ctx
     c->stream = (hipStream_t)hip_stream;
   } else {
     if (hipStreamCreateWithFlags(&c->stream, hipStreamNonBlocking) != hipSuccess) {
+      (void)hipHostFree(c->stage);
       delete c;
       return fail(LLOID_EDEVICE, "hipStreamCreate failed");
     }
@@ -224,6 +230,7 @@ extern "C" lloid_status lloid_ctx_destroy(lloid_ctx *ctx) {
   for (auto &e : ctx->cev) (void)hipEventDestroy(e);
   if (ctx->ws.base) (void)hipFree(ctx->ws.base);
   if (ctx->pinned) (void)hipHostFree(ctx->pinned);
+  if (ctx->stage) (void)hipHostFree(ctx->stage);
   if (ctx->d_halfband) (void)hipFree(ctx->d_halfband);
   if (ctx->d_hfrag[0][0]) (void)hipFree(ctx->d_hfrag[0][0]);
   if (ctx->d_fft_tw) (void)hipFree(ctx->d_fft_tw);
@@ -589,6 +596,7 @@ void lloid::add_bank_jobs(const lloid_bank *b, const LevelView *lv, int64_t t0, 
   m.peak_si = bb.psi;
   m.peak_xi = bb.pxi;
   m.peak_z = b->acorr ? bb.pz : nullptr;
+  m.t0 = bb.elem0;
   m.xi_key = b->acorr ? bb.pkey : nullptr;
   m.acorr = b->acorr;
   m.acorr_half = b->acorr_half;
@@ -650,7 +658,7 @@ void lloid::number_jobs(std::vector<FirJob> &fj, std::vector<UpJob> *uj, std::ve
 
 lloid_status lloid::launch_stages(lloid_ctx *ctx, lloid_dtype ct, const char *dtab, const TabOffsets &to,
                                   const StageItems &n, bool with_snr, float phase_thr, float trig_thr,
-                                  const XiWork &xw, hipEvent_t *ev) {
+                                  int64_t *counts, const XiWork &xw, hipEvent_t *ev) {
   hipStream_t st = ctx->stream;
   auto mark = [&](int stage, int end) -> hipError_t {
     return ev ? hipEventRecord(ev[2 * (stage - LLOID_STAGE_FIR) + end], st) : hipSuccess;
@@ -666,7 +674,8 @@ lloid_status lloid::launch_stages(lloid_ctx *ctx, lloid_dtype ct, const char *dt
   HIP_TRY(launch_mix_jobs(ct, ctx->mix_variant, (const MixJob *)(dtab + to.mix), to.n_mix, n.mix, with_snr, st));
   HIP_TRY(mark(LLOID_STAGE_MIX, 1));
   HIP_TRY(mark(LLOID_STAGE_PHASE, 0));
-  HIP_TRY(launch_peak_phase(ct, (const MixJob *)(dtab + to.mix), to.n_mix, n.entries, phase_thr, st));
+  HIP_TRY(launch_peak_phase(ct, (const MixJob *)(dtab + to.mix), to.n_mix, n.entries, phase_thr,
+                            trig_thr, counts, n.xi2 ? xw.counters : nullptr, st));
   if (n.xi2) {
     if (xw.cap < n.xi_units) return fail(LLOID_EINVAL, "signal-consistency unit list too small");
     HIP_TRY(launch_xi2(ct, (const MixJob *)(dtab + to.mix), to.n_mix, n.windows, n.xi_kmax, n.xi_acorr, trig_thr, xw,
@@ -678,8 +687,9 @@ lloid_status lloid::launch_stages(lloid_ctx *ctx, lloid_dtype ct, const char *dt
 // Filter one block of strain of one detector with every bank of `banks`
 // (same context, full rate and operand type) and compact the triggers.
 // no_alloc: every device buffer comes from the context's static scratch
-// (chunks of windows sized to fit it) and the descriptor tables are staged in
-// pageable host memory: no device or pinned allocation, no profiling events.
+// (chunks of windows sized to fit it) and descriptor tables that do not fit
+// the context's stage go through pageable host memory: no device or pinned
+// allocation, no profiling events.
 static lloid_status filter_banks(lloid_bank *const *banks, int nb, int32_t detector, const void *strain,
                                  lloid_dtype sdt, int64_t n, const lloid_trigger_opts *opts, lloid_trigger *trig,
                                  int64_t trig_cap, int64_t *n_trig, float *snr, lloid_peaks *peaks,
@@ -788,7 +798,7 @@ static lloid_status filter_banks(lloid_bank *const *banks, int nb, int32_t detec
     const int64_t chunk_n_ = std::min<int64_t>(n, win.start(wpc_) + 1);
     size_t bytes = 0;
     auto add = [&](size_t cnt, size_t sz) { bytes = (size_t)round_up((int64_t)bytes, 256) + cnt * sz; };
-    if (host_strain) add((size_t)n, dtype_size(sdt));
+    if (host_strain) add((size_t)n, dtype_size(sdt));   // (also where the stage takes the strain)
     for (int k = 0; k < n_levels; ++k) add((size_t)sup[k].size(), 4);
     for (int i = 0; i < nb; ++i) {
       const size_t tab = (size_t)banks[i]->n_templates * W;
@@ -806,8 +816,7 @@ static lloid_status filter_banks(lloid_bank *const *banks, int nb, int32_t detec
         if (sl.level > 0)
           for (int64_t ld : low_ld(ops, sl.level)) add((size_t)sl.lp * ld, low_esz(ct));
     }
-    add((size_t)trig_blocks(total_rows * W) + 2, 8);
-    add(1, 4);
+    add((size_t)trig_blocks(total_rows * W), 8);
     add((size_t)xi_cap(wpc_), sizeof(XiUnit));
     add(2, 4);
     if (!direct_trig) add((size_t)std::max<int64_t>(dev_cap, 1), sizeof(lloid_trigger));
@@ -836,16 +845,23 @@ static lloid_status filter_banks(lloid_bank *const *banks, int nb, int32_t detec
   const int64_t chunk_n = std::min<int64_t>(n, win.start(wpc) + 1);   // samples of the longest chunk
   const size_t tab_bytes = table_bytes(n_chunks);
   const size_t bytes = layout_bytes(wpc);
+  // small inputs go through the context's stage, read by the first kernel
+  // where they lie: the tables, then a host block of strain
+  const size_t strain_bytes = (size_t)n * dtype_size(sdt);
+  const size_t strain_at = (size_t)round_up((int64_t)(kStageHead + tab_bytes), 256);
+  const bool stage_tab = kStageHead + tab_bytes <= kStageBytes;
+  const bool stage_strain = host_strain && stage_tab && strain_at + strain_bytes <= kStageBytes;
+  char *stage = (char *)ctx->stage;
   std::vector<char> host_tab;   // pageable staging of the tables (no_alloc)
   void *ws_base = nullptr;
   if (no_alloc) {
     if (!ctx->static_scratch) return fail(LLOID_EDEVICE, "the context has no static scratch");
     ws_base = ctx->static_scratch;
-    host_tab.resize(tab_bytes);
+    if (!stage_tab) host_tab.resize(tab_bytes);
   } else {
     lloid_status rs = ensure_ws(ctx, ctx->ws, bytes);
     if (rs != LLOID_OK) return rs;
-    rs = ensure_pinned(ctx, ctx->pinned, ctx->pinned_bytes, tab_bytes);
+    if (!stage_tab) rs = ensure_pinned(ctx, ctx->pinned, ctx->pinned_bytes, tab_bytes);
     if (rs != LLOID_OK) return rs;
     ws_base = ctx->ws.base;
   }
@@ -861,6 +877,7 @@ static lloid_status filter_banks(lloid_bank *const *banks, int nb, int32_t detec
     lv[k] = LevelView{xl[k], sup[k].lo, sup[k].size()};
   }
   std::vector<BankBufs> bw(nb);
+  int64_t elem0 = 0;
   for (int i = 0; i < nb; ++i) {
     const size_t tab = (size_t)banks[i]->n_templates * W;
     bw[i].psnr = cv.take<float>(tab);
@@ -873,6 +890,8 @@ static lloid_status filter_banks(lloid_bank *const *banks, int nb, int32_t detec
     if (banks[i]->acorr) bw[i].pkey = cv.take<int64_t>(tab);
     bw[i].ld_peak = W;
     bw[i].w_base = 0;
+    bw[i].elem0 = elem0;
+    elem0 += (int64_t)tab;
     const int64_t ops = chunk_n + 2 * operand_margin(banks[i]);
     bw[i].ocat = cv.take<char>((size_t)ops * banks[i]->kld * esz);
     bw[i].low.assign(banks[i]->slices.size(), {});
@@ -884,9 +903,11 @@ static lloid_status filter_banks(lloid_bank *const *banks, int nb, int32_t detec
     }
   }
   const int64_t n_blk = trig_blocks(total_rows * W);
-  int64_t *counts = cv.take<int64_t>((size_t)n_blk + 2);
-  int64_t *total = counts + n_blk;
-  int *bad = cv.take<int>(1);
+  int64_t *counts = cv.take<int64_t>((size_t)n_blk);
+  // the kernels write the trigger count and the data flag straight into the stage
+  ResultWords *res = (ResultWords *)stage;
+  res->total = 0;
+  res->bad = 0;
   XiWork xw;
   xw.cap = xi_cap(wpc);
   xw.units = cv.take<XiUnit>((size_t)xw.cap);
@@ -901,7 +922,7 @@ static lloid_status filter_banks(lloid_bank *const *banks, int nb, int32_t detec
     StageItems items;
   };
   std::vector<Chunk> chunks(n_chunks);
-  char *htab = no_alloc ? host_tab.data() : (char *)ctx->pinned;
+  char *htab = stage_tab ? stage + kStageHead : no_alloc ? host_tab.data() : (char *)ctx->pinned;
   size_t off = 0;
   auto put = [&](const void *src, size_t sz) -> size_t {
     off = (size_t)round_up((int64_t)off, 64);
@@ -931,14 +952,9 @@ static lloid_status filter_banks(lloid_bank *const *banks, int nb, int32_t detec
     to.n_mix = (int)mj.size();
   }
   std::vector<TrigJob> tj(nb);
-  {
-    int64_t e = 0;
-    for (int i = 0; i < nb; ++i) {
-      tj[i] = TrigJob{bw[i].psnr, bw[i].pn, bw[i].pphase, bw[i].pdt, bw[i].psi,
-                      banks[i]->acorr ? bw[i].pxi : nullptr, 0, W, e, banks[i]->n_templates, i, detector, 0};
-      e += (int64_t)banks[i]->n_templates * W;
-    }
-  }
+  for (int i = 0; i < nb; ++i)
+    tj[i] = TrigJob{bw[i].psnr, bw[i].pn, bw[i].pphase, bw[i].pdt, bw[i].psi,
+                    banks[i]->acorr ? bw[i].pxi : nullptr, 0, W, bw[i].elem0, banks[i]->n_templates, i, detector, 0};
   const size_t trig_off = put(tj.data(), tj.size() * sizeof(TrigJob));
 
   // ---- launches
@@ -946,18 +962,44 @@ static lloid_status filter_banks(lloid_bank *const *banks, int nb, int32_t detec
     return prof ? hipEventRecord(ctx->ev[2 * stage + end], st) : hipSuccess;
   };
   HIP_TRY(mark(LLOID_STAGE_INGEST, 0));
-  HIP_TRY(hipMemcpyAsync(dtab, htab, off, hipMemcpyHostToDevice, st));
-  if (host_strain) {
-    HIP_TRY(hipMemcpyAsync(strain_tmp, strain, (size_t)n * dtype_size(sdt), hipMemcpyHostToDevice, st));
+  IngestArgs in;
+  if (htab == (char *)host_tab.data()) {
+    HIP_TRY(hipMemcpyAsync(dtab, htab, off, hipMemcpyHostToDevice, st));
+  } else {
+    in.tab_src = htab;
+    in.tab_dst = dtab;
+    in.tab_vecs = (int64_t)ceil_div((int64_t)off, 16);
+  }
+  if (stage_strain) {
+    std::memcpy(stage + strain_at, strain, strain_bytes);
+    d_strain = stage + strain_at;
+  } else if (host_strain) {
+    HIP_TRY(hipMemcpyAsync(strain_tmp, strain, strain_bytes, hipMemcpyHostToDevice, st));
     d_strain = strain_tmp;
   }
-  HIP_TRY(launch_fill_u8(bad, sizeof(int), st));
-  HIP_TRY(launch_convert(d_strain, sdt, n, xl[0], sup[0].lo, sup[0].size(), sscale, bad, st));
+  in.zero = counts;
+  in.zero_n = n_blk;
+  in.src = d_strain;
+  in.n = n;
+  in.dst = xl[0];
+  in.dst_lo = sup[0].lo;
+  in.dst_len = sup[0].size();
+  in.scale = sscale;
+  in.bad = &res->bad;
+  HIP_TRY(launch_ingest(in, sdt, st));
   HIP_TRY(mark(LLOID_STAGE_INGEST, 1));
   HIP_TRY(mark(LLOID_STAGE_DECIMATE, 0));
-  for (int k = 1; k < n_levels; ++k)
-    HIP_TRY(launch_decimate(xl[k - 1], sup[k - 1].lo, sup[k - 1].size(), xl[k], sup[k].lo, sup[k].size(),
-                            ctx->d_halfband, st));
+  for (int k = 0; k + 1 < n_levels;) {
+    DecimArgs da;
+    da.u = xl[k];
+    da.u_lo = sup[k].lo;
+    da.u_len = sup[k].size();
+    da.g = ctx->d_halfband;
+    da.n_levels = decim_group(k, n_levels - 1 - k);
+    for (int q = 1; q <= da.n_levels; ++q) da.level[q - 1] = DecimLevel{xl[k + q], sup[k + q].lo, sup[k + q].lo, sup[k + q].hi};
+    HIP_TRY(launch_decimate(da, st));
+    k += da.n_levels;
+  }
   HIP_TRY(mark(LLOID_STAGE_DECIMATE, 1));
   const float phase_thr = (peaks && peaks[0].phase) ? -1.f : thr;
   // every chunk's FIR, interpolation, mixing and phase stages get events of their own
@@ -970,18 +1012,14 @@ static lloid_status filter_banks(lloid_bank *const *banks, int nb, int32_t detec
     }
   for (int64_t c = 0; c < n_chunks; ++c) {
     const lloid_status r2 = launch_stages(ctx, ct, dtab, chunks[c].to, chunks[c].items, snr != nullptr, phase_thr,
-                                          thr, xw, prof ? &ctx->cev[(size_t)2 * kChunkStages * c] : nullptr);
+                                          thr, counts, xw, prof ? &ctx->cev[(size_t)2 * kChunkStages * c] : nullptr);
     if (r2 != LLOID_OK) return r2;
   }
   HIP_TRY(mark(LLOID_STAGE_TRIGGER, 0));
-  HIP_TRY(launch_trigger_jobs((const TrigJob *)(dtab + trig_off), nb, total_rows * W, thr, counts, total, dev_cap,
-                              dtrig, st));
+  HIP_TRY(launch_trigger_jobs((const TrigJob *)(dtab + trig_off), nb, total_rows * W, thr, counts, &res->total,
+                              dev_cap, dtrig, st));
   HIP_TRY(mark(LLOID_STAGE_TRIGGER, 1));
   HIP_TRY(mark(LLOID_STAGE_D2H, 0));
-  int64_t h_total = 0;
-  int h_bad = 0;
-  HIP_TRY(hipMemcpyAsync(&h_total, total, sizeof h_total, hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipMemcpyAsync(&h_bad, bad, sizeof h_bad, hipMemcpyDeviceToHost, st));
   if (peaks)
     for (int i = 0; i < nb; ++i) {
       const size_t ld = (size_t)peaks[i].n_windows;   // the caller's rows may be wider than W
@@ -1001,6 +1039,8 @@ static lloid_status filter_banks(lloid_bank *const *banks, int nb, int32_t detec
   if (host_snr)
     HIP_TRY(hipMemcpyAsync(snr, dsnr, (size_t)banks[0]->n_templates * n * 2 * 4, hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
+  const int64_t h_total = res->total;
+  const int h_bad = res->bad;
   const int64_t ncopy = direct_trig ? 0 : std::min(h_total, dev_cap);
   if (ncopy > 0) HIP_TRY(hipMemcpyAsync(trig, dtrig, (size_t)ncopy * sizeof(lloid_trigger), hipMemcpyDefault, st));
   HIP_TRY(mark(LLOID_STAGE_D2H, 1));

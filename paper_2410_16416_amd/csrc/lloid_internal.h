@@ -91,6 +91,7 @@ struct MixJob {
   float *snr;            // optional [F][snr_ld][2], column n - snr_abs0
   int64_t ocat_abs0, n_end, w0, nw, win_p, win_q, ld_peak, w_base, snr_ld, snr_abs0, item0, e0;
   int64_t x0;                 // first (job, window) item of this job in the signal-consistency launches
+  int64_t t0;                 // first entry of this job's peak table in the order of the trigger compaction
   int64_t ocat_end;           // absolute sample past the operand's last row
   int64_t *xi_key;            // listing slab [ld_peak][n_templates] of trigger keys (banks with lags)
   float inv_scale;
@@ -146,7 +147,10 @@ struct lloid_ctx {
   int n_cu = 0;
   lloid::Workspace ws;          // grow-only device scratch of filter calls on this context
   void *static_scratch = nullptr;  // this device's static scratch array (lloid_filter_noalloc)
-  void *pinned = nullptr;       // pinned host staging for descriptor tables
+  void *stage = nullptr;        // pinned host memory the kernels read and write: kStageBytes, kept
+                                // with the context: a call's result words, then tables and strain
+                                // that fit
+  void *pinned = nullptr;       // pinned host staging for descriptor tables that do not
   size_t pinned_bytes = 0;
   int64_t chunk_budget = int64_t(6) << 30;  // device bytes of per-chunk operands
   int fir_variant = 0, mix_variant = 0;     // compiled tile shapes in use (lloid_ctx_set_tiles, lloid_autotune)
@@ -156,6 +160,15 @@ struct lloid_ctx {
   double stage_ms[LLOID_N_STAGES] = {};
   int64_t stage_calls[LLOID_N_STAGES] = {};
 };
+
+namespace lloid {
+// The context's pinned stage: result words (ResultWords), then staged inputs.
+constexpr size_t kStageBytes = size_t(256) << 10, kStageHead = 256;
+struct ResultWords {
+  int64_t total;   // triggers or pairs
+  int bad;         // strain sample not finite / lists out of order
+};
+}  // namespace lloid
 
 struct lloid_bank {
   lloid_ctx *ctx = nullptr;
@@ -178,10 +191,48 @@ struct lloid_bank {
 namespace lloid {
 
 // ---- launch wrappers (lloid_kernels.hip) ----
-hipError_t launch_convert(const void *src, lloid_dtype dt, int64_t n, float *dst, int64_t dst_lo,
-                          int64_t dst_len, float scale, int *bad, hipStream_t s);
-hipError_t launch_decimate(const float *u, int64_t u_lo, int64_t u_len, float *d, int64_t d_lo,
-                           int64_t d_len, const float *g, hipStream_t s);
+// First kernel of a call or tick: tab_vecs 16-byte units of descriptor tables
+// from host memory the device sees into device memory, zero_n cleared
+// counters, and samples [dst_lo, dst_lo + dst_len) of the scaled strain (n
+// samples of type dt at src, zeros outside) in FP32; *bad set to 1 when one is
+// not finite.  Any of the three parts may be empty.
+struct IngestArgs {
+  const void *tab_src = nullptr;
+  void *tab_dst = nullptr;
+  int64_t tab_vecs = 0;
+  int64_t *zero = nullptr;
+  int64_t zero_n = 0;
+  const void *src = nullptr;
+  int64_t n = 0;
+  float *dst = nullptr;
+  int64_t dst_lo = 0, dst_len = 0;
+  float scale = 1.f;
+  int *bad = nullptr;
+};
+hipError_t launch_ingest(const IngestArgs &a, lloid_dtype dt, hipStream_t s);
+// Half-band decimation of u (absolute index u_lo at u[0], zeros outside) to
+// n_levels successive levels: sample i of level k, lo <= i < hi, goes to
+// d[i - d_lo] of level[k - 1].  What lies between u and a level is computed
+// from u, so u must reach 33 (2^k - 1) samples before the first output of
+// level k (at u's rate), or hold all that is not zero.
+constexpr int kDecimGroup = 4;
+struct DecimLevel {
+  float *d = nullptr;
+  int64_t d_lo = 0, lo = 0, hi = 0;
+};
+struct DecimArgs {
+  const float *u = nullptr;
+  int64_t u_lo = 0, u_len = 0;
+  const float *g = nullptr;
+  int n_levels = 0;
+  int span = 0;                    // set by the launch: owned samples of the deepest level per workgroup
+  int64_t tile0 = 0;
+  DecimLevel level[kDecimGroup];
+};
+hipError_t launch_decimate(DecimArgs a, hipStream_t s);
+// Levels of one launch when `left` levels remain below level `k`: four from
+// the full rate, then two at a time (a stream's low-rate history is short).
+inline int decim_group(int k, int left) { return std::min(left, k == 0 ? kDecimGroup : 2); }
 // Compiled tile-shape variants of the FIR and mixing kernels (0 = default);
 // every variant gives bit-identical results (each output's K sum runs in the
 // same order), only the speed differs.  Rows x columns per workgroup:
@@ -199,8 +250,10 @@ hipError_t launch_mix_jobs(lloid_dtype t, int variant, const MixJob *jobs, int n
 // White noise of unit variance (a counter-based hash of the sample index and
 // seed, uniform on [-sqrt 3, sqrt 3]): synthetic strain for tuning runs.
 hipError_t launch_noise(float *x, int64_t n, uint32_t seed, hipStream_t s);
+// counts: triggers (|z| >= trig_thr) per compaction block, added to zeroed
+// slots; xi_counters: NULL, or the signal-consistency counters to zero.
 hipError_t launch_peak_phase(lloid_dtype t, const MixJob *jobs, int n_jobs, int64_t n_entries, float phase_thr,
-                             hipStream_t s);
+                             float trig_thr, int64_t *counts, int32_t *xi_counters, hipStream_t s);
 // Signal-consistency value at the peaks with |z| >= thr of the jobs that carry
 // autocorrelations; one workgroup per (job, window).
 // n_windows: (job, window) items; kmax: largest kcat of a job with lags;
@@ -208,8 +261,9 @@ hipError_t launch_peak_phase(lloid_dtype t, const MixJob *jobs, int n_jobs, int6
 // xw.cap >= sum over those jobs of nw * ceil(n_templates / 64)
 hipError_t launch_xi2(lloid_dtype t, const MixJob *jobs, int n_jobs, int64_t n_windows, int kmax, int64_t acorr_max,
                       float thr, const XiWork &xw, int n_cu, hipStream_t s);
-// Trigger compaction: counts, offsets and records (job-major, template, window);
-// counts holds trig_blocks(n_elems) slots.
+// Trigger compaction: records (job-major, template, window); counts holds the
+// trig_blocks(n_elems) counts of the phase kernel; *total (device or pinned
+// host memory) receives their sum.
 hipError_t launch_trigger_jobs(const TrigJob *jobs, int n_jobs, int64_t n_elems, float thr, int64_t *counts,
                                int64_t *total, int64_t cap, lloid_trigger *out, hipStream_t s);
 // Conditioning of one block of T samples (F64 or F32, on the device): PSD
@@ -313,6 +367,7 @@ struct BankBufs {
   int64_t *pkey = nullptr;         // trigger listing slab [ld_peak][F] (banks with lags)
   int64_t *pn = nullptr;
   int64_t ld_peak = 0, w_base = 0; // peak tables [F][ld_peak], column w - w_base
+  int64_t elem0 = 0;               // their first entry in the order of the trigger compaction
 };
 
 struct TileShapes {
@@ -370,8 +425,8 @@ void number_jobs(std::vector<FirJob> &fj, std::vector<UpJob> *uj, std::vector<Mi
 // NULL, or 8 events bracketing those four stages.
 constexpr int kChunkStages = 4;    // LLOID_STAGE_FIR .. LLOID_STAGE_PHASE
 lloid_status launch_stages(lloid_ctx *ctx, lloid_dtype ct, const char *dtab, const TabOffsets &to,
-                           const StageItems &n, bool with_snr, float phase_thr, float trig_thr, const XiWork &xw,
-                           hipEvent_t *ev);
+                           const StageItems &n, bool with_snr, float phase_thr, float trig_thr, int64_t *counts,
+                           const XiWork &xw, hipEvent_t *ev);
 // Signal-consistency units that nw windows of a bank of F templates can list at most.
 inline int64_t xi_unit_cap(int64_t nw, int F) { return nw * ceil_div(F, 64); }
 

@@ -75,36 +75,90 @@ __device__ __forceinline__ int find_job(const J *__restrict__ jobs, int n_jobs, 
 
 // ---------------------------------------------------------- small kernels
 
+// First kernel of a call: the descriptor tables from (device-visible) host
+// memory into device memory, cleared counters, and the strain in FP32 with
+// zeros outside [0, n) and a flag on samples that are not finite.  One launch
+// for what were a copy, a fill and a conversion: on small blocks each cost
+// its launch (4 to 9 us), not its bytes.  Workgroups [0, tab_blocks) copy 16
+// bytes per thread, the next zero_blocks clear, the rest convert.  The flag
+// may lie in host memory: a plain store of the same value by whoever finds one.
 template <typename TI>
-__global__ void k_convert(const TI *__restrict__ src, int64_t n, float *__restrict__ dst, int64_t dst_lo,
-                          int64_t dst_len, float scale, int *__restrict__ bad) {
-  int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= dst_len) return;
-  int64_t a = dst_lo + t;
+__global__ __launch_bounds__(256) void k_ingest(IngestArgs a, int tab_blocks, int zero_blocks) {
+  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if ((int)blockIdx.x < tab_blocks) {
+    if (t < a.tab_vecs) ((uint4 *)a.tab_dst)[t] = ((const uint4 *)a.tab_src)[t];
+    return;
+  }
+  if ((int)blockIdx.x < tab_blocks + zero_blocks) {
+    const int64_t z = t - (int64_t)tab_blocks * 256;
+    if (z < a.zero_n) a.zero[z] = 0;
+    return;
+  }
+  const int64_t o = t - (int64_t)(tab_blocks + zero_blocks) * 256;
+  if (o >= a.dst_len) return;
+  const int64_t i = a.dst_lo + o;
   float v = 0.f;
-  if (a >= 0 && a < n) {
+  if (i >= 0 && i < a.n) {
     // FP32 from here on: the scale is a power of two, so the product is the
     // scaled value rounded once; a sample that is not finite in FP32 is flagged
-    v = (float)src[a] * scale;
+    v = (float)((const TI *)a.src)[i] * a.scale;
     if (!isfinite(v)) {
-      atomicOr(bad, 1);
+      __hip_atomic_store(a.bad, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
       v = 0.f;
     }
   }
-  dst[t] = v;
+  a.dst[o] = v;
 }
 
 // d[k] = sum_{|n| <= 32} g[n] u[2k - n]; g is zero at even n != 0 and 1/2 at 0,
-// so the sum runs over the centre and symmetric odd pairs.
-__global__ void k_decimate(const float *__restrict__ u, int64_t u_lo, int64_t u_len, float *__restrict__ d,
-                           int64_t d_lo, int64_t d_len, const float *__restrict__ g) {
-  int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= d_len) return;
-  int64_t c = 2 * (d_lo + t) - u_lo;  // buffer index of u[2k]
-  auto at = [&](int64_t i) -> float { return (i >= 0 && i < u_len) ? u[i] : 0.f; };
-  float acc = g[kHalfQ] * at(c);
-  for (int n = 1; n <= kHalfQ; n += 2) acc += g[kHalfQ + n] * (at(c - n) + at(c + n));
-  d[t] = acc;
+// so the sum runs over the centre and symmetric odd pairs.  Up to
+// kDecimGroup levels in one launch: a workgroup owns a run of samples of the
+// deepest level and the samples over them at the levels between, loads the
+// finer level's samples those need into LDS (32 more on each side per level)
+// and cascades there, recomputing the halos (23 % more sums at four levels of
+// 4096-sample runs).  A launch per level cost four launches and their gaps:
+// 38.5 us of kernels for 1024 s at 2048 Hz against 21, 12 against 8.5 us for 8 s.
+constexpr int kDecimSpan = 4096;                            // finer-level samples a workgroup owns at most
+constexpr int kDecimBuf = kDecimSpan + 64 * ((1 << kDecimGroup) - 1) + 64;
+
+__global__ __launch_bounds__(256) void k_decimate(DecimArgs a) {
+  __shared__ float buf[kDecimBuf + kDecimBuf / 2];
+  const int K = a.n_levels;
+  const int64_t own0 = (a.tile0 + blockIdx.x) * a.span;     // owned samples of the deepest level
+  // range [lo, hi) needed at each level
+  int64_t lo[kDecimGroup + 1], hi[kDecimGroup + 1];
+#pragma unroll
+  for (int k = 0; k <= kDecimGroup; ++k) lo[k] = own0, hi[k] = own0 + a.span;
+#pragma unroll
+  for (int k = kDecimGroup - 1; k >= 0; --k)
+    if (k < K) lo[k] = 2 * lo[k + 1] - kHalfQ, hi[k] = 2 * hi[k + 1] + kHalfQ - 1;
+  for (int t = threadIdx.x; t < (int)(hi[0] - lo[0]); t += 256) {
+    const int64_t i = lo[0] + t - a.u_lo;
+    buf[t] = (i >= 0 && i < a.u_len) ? a.u[i] : 0.f;
+  }
+  __syncthreads();
+  float *src = buf, *dst = buf + kDecimBuf;
+#pragma unroll
+  for (int k = 1; k <= kDecimGroup; ++k) {
+    if (k <= K) {
+      const DecimLevel &lv = a.level[k - 1];
+      // owned and wanted samples of this level
+      const int64_t w0 = max(own0 << (K - k), lv.lo), w1 = min((own0 + a.span) << (K - k), lv.hi);
+      for (int t = threadIdx.x; t < (int)(hi[k] - lo[k]); t += 256) {
+        const float *c = src + kHalfQ + 2 * t;      // lo[k - 1] = 2 lo[k] - kHalfQ
+        float acc = __builtin_fmaf(a.g[kHalfQ], c[0], a.g[kHalfQ + 1] * (c[-1] + c[1]));
+#pragma unroll
+        for (int n = 3; n <= kHalfQ; n += 2) acc = __builtin_fmaf(a.g[kHalfQ + n], c[-n] + c[n], acc);
+        dst[t] = acc;
+        const int64_t i = lo[k] + t;
+        if (i >= w0 && i < w1) lv.d[i - lv.d_lo] = acc;
+      }
+      __syncthreads();
+      float *x = src;
+      src = dst;
+      dst = x;
+    }
+  }
 }
 
 template <typename T>
@@ -1030,12 +1084,16 @@ __device__ __forceinline__ float wave_sum(float v) {
 
 template <typename T>
 __global__ __launch_bounds__(256) void k_peak_phase(const MixJob *__restrict__ jobs, int n_jobs, int64_t entries,
-                                                    float thr) {
+                                                    float thr, float trig_thr, int64_t *__restrict__ counts,
+                                                    int32_t *__restrict__ xi_counters) {
   const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int lane = threadIdx.x & 63;
   int job = 0;
   int64_t o = 0, row = 0;   // peak-table offset and template of this lane's entry
+  int64_t blk = -1;         // trigger-compaction block it counts in, if it is a trigger
   bool hit = false;
+  // the signal-consistency launches, next in the stream, start from zero counters
+  if (xi_counters && blockIdx.x == 0 && threadIdx.x < 2) xi_counters[threadIdx.x] = 0;
   if (e < entries) {
     // job owning entry e: last job with e0 <= e
     int lo = 0, hi = n_jobs - 1;
@@ -1049,12 +1107,24 @@ __global__ __launch_bounds__(256) void k_peak_phase(const MixJob *__restrict__ j
     const int64_t le = e - jb.e0;
     row = le / jb.nw;
     o = row * jb.ld_peak + (jb.w0 + le - row * jb.nw - jb.w_base);
-    hit = jb.peak_snr[o] >= thr;
+    const float snr = jb.peak_snr[o];
+    hit = snr >= thr;
+    if (snr >= trig_thr) blk = (jb.t0 + o) / kTrigPerBlock;
     if (!hit) {
       jb.peak_phase[o] = 0.f;
       jb.peak_dt[o] = 0.f;
       jb.peak_si[o] = 0.f;
     }
+  }
+  // triggers per compaction block: a wave's entries fall into few blocks
+  uint64_t left = __ballot(blk >= 0);
+  while (left) {
+    const int s0 = __builtin_ctzll(left);
+    const int64_t b0 = ((int64_t)__builtin_amdgcn_readlane((int)(blk >> 32), s0) << 32) |
+                       (uint32_t)__builtin_amdgcn_readlane((int)blk, s0);
+    const uint64_t same = __ballot(blk == b0);
+    if (lane == s0) atomicAdd((unsigned long long *)(counts + b0), (unsigned long long)__popcll(same));
+    left &= ~same;
   }
   constexpr int EPV = 16 / (int)sizeof(T);
   uint64_t m = __ballot(hit);
@@ -1371,7 +1441,7 @@ __global__ __launch_bounds__(kXiThreads) void k_xi2(const MixJob *__restrict__ j
 // Listing launch of the two-launch form: keys of window w go to the job's
 // listing slab at xi_key[(w - w_base) F + t], t = 0..count - 1 (one sorted
 // run per listing pass), and units (item, 64 j, min(64, count - 64 j)) to
-// units[counters[0]++ ...].  counters[0] starts at zero.
+// units[counters[0]++ ...].  The phase kernel has zeroed the counters.
 __global__ __launch_bounds__(kXiThreads) void k_xi2_list(const MixJob *__restrict__ jobs, int n_jobs, float thr,
                                                          XiUnit *__restrict__ units, int64_t cap,
                                                          int32_t *__restrict__ counters) {
@@ -1617,11 +1687,16 @@ __global__ __launch_bounds__(kXiThreads, 2) void k_xi2_tiles(const MixJob *__res
 
 // ---------------------------------------------------------- trigger compaction
 // Stream compaction over the flat (job, template, window) order of every peak
-// table: per-block flag counts, an exclusive scan of the block counts, then a
-// rewrite of each block's flagged entries at its scanned offset.  A block
-// covers kTrigPerBlock consecutive entries in kTrigPerBlock / 256 rounds of
-// 256, so the cost follows the number of entries whatever the row shape.
+// table.  The phase kernel has counted the triggers of every block of
+// kTrigPerBlock consecutive entries; a block's workgroup takes the sum of the
+// counts before its own as its offset (each reads them all: up to
+// kTrigInline blocks that is cheaper than a launch for the scan, 2 KB to 32
+// KB from the L2 against 5 us) or, with more blocks, the offset that the scan
+// launch has left, and rewrites its flagged entries from there, in
+// kTrigPerBlock / 256 rounds of 256, so the cost follows the number of
+// entries whatever the row shape.
 
+constexpr int64_t kTrigInline = 4096;
 constexpr int kTrigThreads = 256;
 
 // Job owning flat entry e: the last job with elem0 <= e.
@@ -1638,29 +1713,6 @@ __device__ __forceinline__ int find_trig_job(const TrigJob *__restrict__ jobs, i
 __device__ __forceinline__ uint64_t lanes_below() {
   const int lane = (int)(threadIdx.x & 63);
   return lane ? (~0ull >> (64 - lane)) : 0ull;
-}
-
-__global__ __launch_bounds__(kTrigThreads) void k_trigger_count(const TrigJob *__restrict__ jobs, int n_jobs,
-                                                                int64_t n_elems, float thr,
-                                                                int64_t *__restrict__ counts) {
-  __shared__ int sh[kTrigThreads / 64];
-  int c = 0;
-  for (int k = 0; k < kTrigPerBlock / kTrigThreads; ++k) {
-    const int64_t e = (int64_t)blockIdx.x * kTrigPerBlock + k * kTrigThreads + threadIdx.x;
-    bool f = false;
-    if (e < n_elems) {
-      const TrigJob &jb = jobs[find_trig_job(jobs, n_jobs, e)];
-      f = jb.snr[e - jb.elem0] >= thr;
-    }
-    c += __popcll(__ballot(f));
-  }
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = c;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int t = 0;
-    for (int q = 0; q < kTrigThreads / 64; ++q) t += sh[q];
-    counts[blockIdx.x] = t;
-  }
 }
 
 // Exclusive prefix sum of counts[0..n) in place, total in *total; one block of
@@ -1704,13 +1756,30 @@ __global__ __launch_bounds__(1024) void k_trigger_scan(int64_t *counts, int64_t 
   if (threadIdx.x == 0) *total = carry;
 }
 
+// SCANNED: counts holds the blocks' offsets; else their counts, and the last
+// block writes the total (which may lie in host memory).
+template <bool SCANNED>
 __global__ __launch_bounds__(kTrigThreads) void k_trigger_write(const TrigJob *__restrict__ jobs, int n_jobs,
                                                                 int64_t n_elems, float thr,
-                                                                const int64_t *__restrict__ offsets, int64_t cap,
-                                                                lloid_trigger *__restrict__ out) {
+                                                                const int64_t *__restrict__ counts, int64_t cap,
+                                                                lloid_trigger *__restrict__ out,
+                                                                int64_t *__restrict__ total) {
   __shared__ int sh[kTrigThreads / 64];
+  __shared__ int64_t sh_off[kTrigThreads / 64];
   const int wave = threadIdx.x >> 6;
-  int64_t run = offsets[blockIdx.x];
+  int64_t run = 0;
+  if constexpr (SCANNED) {
+    run = counts[blockIdx.x];
+  } else {
+    int64_t s = 0;
+    for (int64_t q = threadIdx.x; q < (int64_t)blockIdx.x; q += kTrigThreads) s += counts[q];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+    if ((threadIdx.x & 63) == 0) sh_off[wave] = s;
+    __syncthreads();
+    for (int q = 0; q < kTrigThreads / 64; ++q) run += sh_off[q];
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total = run + counts[blockIdx.x];
+  }
   for (int k = 0; k < kTrigPerBlock / kTrigThreads; ++k) {
     const int64_t e = (int64_t)blockIdx.x * kTrigPerBlock + k * kTrigThreads + threadIdx.x;
     int j = 0;
@@ -2153,15 +2222,12 @@ __global__ void k_noise(float *__restrict__ x, int64_t n, uint32_t seed) {
 
 static inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
 
-hipError_t launch_convert(const void *src, lloid_dtype dt, int64_t n, float *dst, int64_t dst_lo,
-                          int64_t dst_len, float scale, int *bad, hipStream_t s) {
-  if (dst_len <= 0) return hipSuccess;
-  if (dt == LLOID_F64)
-    k_convert<double><<<blocks_for(dst_len, 256), 256, 0, s>>>((const double *)src, n, dst, dst_lo, dst_len,
-                                                                 scale, bad);
-  else
-    k_convert<float><<<blocks_for(dst_len, 256), 256, 0, s>>>((const float *)src, n, dst, dst_lo, dst_len,
-                                                                scale, bad);
+hipError_t launch_ingest(const IngestArgs &a, lloid_dtype dt, hipStream_t s) {
+  const unsigned tb = blocks_for(a.tab_vecs, 256), zb = blocks_for(a.zero_n, 256);
+  const unsigned blocks = tb + zb + blocks_for(std::max<int64_t>(a.dst_len, 0), 256);
+  if (!blocks) return hipSuccess;
+  if (dt == LLOID_F64) k_ingest<double><<<blocks, 256, 0, s>>>(a, (int)tb, (int)zb);
+  else k_ingest<float><<<blocks, 256, 0, s>>>(a, (int)tb, (int)zb);
   return hipGetLastError();
 }
 
@@ -2171,10 +2237,24 @@ hipError_t launch_noise(float *x, int64_t n, uint32_t seed, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_decimate(const float *u, int64_t u_lo, int64_t u_len, float *d, int64_t d_lo,
-                           int64_t d_len, const float *g, hipStream_t s) {
-  if (d_len <= 0) return hipSuccess;
-  k_decimate<<<blocks_for(d_len, 256), 256, 0, s>>>(u, u_lo, u_len, d, d_lo, d_len, g);
+hipError_t launch_decimate(DecimArgs a, hipStream_t s) {
+  const int K = a.n_levels;
+  if (K < 1 || K > kDecimGroup) return hipErrorInvalidValue;
+  // the deepest level's samples over every level's wanted range
+  int64_t lo = INT64_MAX, hi = INT64_MIN;
+  for (int k = 1; k <= K; ++k) {
+    const DecimLevel &lv = a.level[k - 1];
+    if (lv.hi <= lv.lo) continue;
+    lo = std::min(lo, lv.lo >> (K - k));
+    hi = std::max(hi, ((lv.hi - 1) >> (K - k)) + 1);
+  }
+  if (hi <= lo) return hipSuccess;
+  // runs of 4096 finer-level samples, or of 1024 (twice the halo work) where
+  // the long ones would leave CUs without a workgroup
+  a.span = kDecimSpan >> K;
+  if (hi - lo <= 256 * (int64_t)a.span) a.span = (kDecimSpan / 4) >> K;
+  a.tile0 = floor_div(lo, a.span);
+  k_decimate<<<(unsigned)(ceil_div(hi, a.span) - a.tile0), 256, 0, s>>>(a);
   return hipGetLastError();
 }
 
@@ -2296,25 +2376,31 @@ hipError_t launch_mix_jobs(lloid_dtype t, int variant, const MixJob *jobs, int n
 }
 
 hipError_t launch_peak_phase(lloid_dtype t, const MixJob *jobs, int n_jobs, int64_t n_entries, float phase_thr,
-                             hipStream_t s) {
+                             float trig_thr, int64_t *counts, int32_t *xi_counters, hipStream_t s) {
   if (n_entries <= 0) return hipSuccess;
   const unsigned blocks = (unsigned)((n_entries + 255) / 256);   // one entry per thread
+  auto go = [&](auto z) {
+    k_peak_phase<decltype(z)><<<blocks, 256, 0, s>>>(jobs, n_jobs, n_entries, phase_thr, trig_thr, counts, xi_counters);
+    return hipGetLastError();
+  };
   switch (t) {
-    case LLOID_F16: k_peak_phase<_Float16><<<blocks, 256, 0, s>>>(jobs, n_jobs, n_entries, phase_thr); break;
-    case LLOID_BF16: k_peak_phase<__bf16><<<blocks, 256, 0, s>>>(jobs, n_jobs, n_entries, phase_thr); break;
-    case LLOID_F32: k_peak_phase<float><<<blocks, 256, 0, s>>>(jobs, n_jobs, n_entries, phase_thr); break;
+    case LLOID_F16: return go(_Float16{});
+    case LLOID_BF16: return go(__bf16{});
+    case LLOID_F32: return go(float{});
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 hipError_t launch_trigger_jobs(const TrigJob *jobs, int n_jobs, int64_t n_elems, float thr, int64_t *counts,
                                int64_t *total, int64_t cap, lloid_trigger *out, hipStream_t s) {
-  const int64_t nblk = n_elems > 0 ? trig_blocks(n_elems) : 0;
-  if (nblk > 0) k_trigger_count<<<(unsigned)nblk, kTrigThreads, 0, s>>>(jobs, n_jobs, n_elems, thr, counts);
-  k_trigger_scan<<<1, 1024, 0, s>>>(counts, nblk, total);
-  if (nblk > 0)
-    k_trigger_write<<<(unsigned)nblk, kTrigThreads, 0, s>>>(jobs, n_jobs, n_elems, thr, counts, cap, out);
+  const int64_t nblk = trig_blocks(n_elems);
+  if (nblk <= 0) return hipErrorInvalidValue;
+  if (nblk > kTrigInline) {
+    k_trigger_scan<<<1, 1024, 0, s>>>(counts, nblk, total);
+    k_trigger_write<true><<<(unsigned)nblk, kTrigThreads, 0, s>>>(jobs, n_jobs, n_elems, thr, counts, cap, out, total);
+  } else {
+    k_trigger_write<false><<<(unsigned)nblk, kTrigThreads, 0, s>>>(jobs, n_jobs, n_elems, thr, counts, cap, out, total);
+  }
   return hipGetLastError();
 }
 
@@ -2325,8 +2411,6 @@ hipError_t launch_xi2(lloid_dtype t, const MixJob *jobs, int n_jobs, int64_t n_w
   const int nks = kmax / 16;
   // the tile launch indexes the autocorrelation tables with 32-bit offsets
   if (t != LLOID_F32 && nks <= 32 && acorr_max <= INT_MAX && xw.cap > 0) {
-    hipError_t e = launch_fill_u8(xw.counters, 2 * sizeof(int32_t), s);
-    if (e != hipSuccess) return e;
     k_xi2_list<<<blocks, kXiThreads, 0, s>>>(jobs, n_jobs, thr, xw.units, xw.cap, xw.counters);
     // persistent: two workgroups per CU take units until the list is done
     const unsigned tb = (unsigned)std::min<int64_t>(xw.cap, 2 * (int64_t)std::max(n_cu, 1));

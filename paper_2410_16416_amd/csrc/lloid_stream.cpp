@@ -225,15 +225,29 @@ lloid_status make_room(lloid_stream *s, DetState &d, int k, int64_t add, const T
 
 // Extend every level of detector d to the samples its inputs now allow.
 lloid_status decimate_new(lloid_stream *s, DetState &d, const TickSlot *last) {
-  for (int k = 1; k < s->n_levels; ++k) {
-    // sample i needs level k-1 up to 2i + Q
-    const int64_t top = floor_div(d.avail[k - 1] - 1 - kHalfQ, 2) + 1;
-    if (top <= d.avail[k]) continue;
-    const lloid_status r = make_room(s, d, k, top - d.avail[k], last);
-    if (r != LLOID_OK) return r;
-    HIP_TRY(launch_decimate(d.x[k - 1], d.lo[k - 1], d.avail[k - 1] - d.lo[k - 1], d.x[k] + (d.avail[k] - d.lo[k]),
-                            d.avail[k], top - d.avail[k], s->ctx->d_halfband, s->ingest));
-    d.avail[k] = top;
+  for (int k = 0; k + 1 < s->n_levels;) {
+    DecimArgs da;
+    da.u = d.x[k];
+    da.u_lo = d.lo[k];
+    da.u_len = d.avail[k] - d.lo[k];
+    da.g = s->ctx->d_halfband;
+    da.n_levels = decim_group(k, s->n_levels - 1 - k);
+    for (int q = 1; q <= da.n_levels; ++q) {
+      // sample i needs the level above up to 2i + Q
+      const int64_t top = floor_div(d.avail[k + q - 1] - 1 - kHalfQ, 2) + 1;
+      DecimLevel &lv = da.level[q - 1];
+      lv.lo = d.avail[k + q];
+      lv.hi = std::max(top, lv.lo);
+      if (lv.hi > lv.lo) {
+        const lloid_status r = make_room(s, d, k + q, lv.hi - lv.lo, last);
+        if (r != LLOID_OK) return r;
+      }
+      lv.d = d.x[k + q];
+      lv.d_lo = d.lo[k + q];
+      d.avail[k + q] = lv.hi;
+    }
+    HIP_TRY(launch_decimate(da, s->ingest));
+    k += da.n_levels;
   }
   return LLOID_OK;
 }
@@ -249,7 +263,13 @@ lloid_status ingest(lloid_stream *s, int d, const void *src, lloid_dtype dt, int
     HIP_TRY(launch_fill_u8(dst, (size_t)n * 4, s->ingest));
   } else {
     // checked finite at push time: the flag is not read here
-    HIP_TRY(launch_convert(src, dt, n, dst, 0, n, s->sscale, s->bad + 32, s->ingest));
+    IngestArgs in;
+    in.src = src;
+    in.n = in.dst_len = n;
+    in.dst = dst;
+    in.scale = s->sscale;
+    in.bad = s->bad + 32;
+    HIP_TRY(launch_ingest(in, dt, s->ingest));
   }
   ds.avail[0] += n;
   ds.pushed = ds.avail[0];
@@ -353,7 +373,7 @@ lloid_status enqueue_tick(lloid_stream *s, int64_t wa, int64_t wb, Clock::time_p
     }
     rows += (int64_t)b->n_templates * s->n_det;
   }
-  add((size_t)trig_blocks(rows * nw) + 2, 8);
+  add((size_t)trig_blocks(rows * nw), 8);
   add((size_t)xi_cap, sizeof(XiUnit));
   add(2, 4);
   const size_t tab_bytes = n_fir * sizeof(FirJob) + n_up * sizeof(UpJob) +
@@ -412,6 +432,7 @@ lloid_status enqueue_tick(lloid_stream *s, int64_t wa, int64_t wb, Clock::time_p
       if (b->acorr) bb.pkey = cv.take<int64_t>((size_t)b->n_templates * nw);
       bb.ld_peak = nw;
       bb.w_base = wa;
+      bb.elem0 = row * nw;
       std::vector<LevelView> lv(s->n_levels);
       const DetState &ds = s->det[d];
       for (int k = 0; k < s->n_levels; ++k) lv[k] = LevelView{ds.x[k], ds.lo[k], ds.avail[k] - ds.lo[k]};
@@ -423,8 +444,7 @@ lloid_status enqueue_tick(lloid_stream *s, int64_t wa, int64_t wb, Clock::time_p
     }
   }
   const int64_t n_blk = trig_blocks(rows * nw);
-  int64_t *counts = cv.take<int64_t>((size_t)n_blk + 2);
-  int64_t *total = counts + n_blk;
+  int64_t *counts = cv.take<int64_t>((size_t)n_blk);
   XiWork xw;
   xw.cap = xi_cap;
   xw.units = cv.take<XiUnit>((size_t)xi_cap);
@@ -451,15 +471,20 @@ lloid_status enqueue_tick(lloid_stream *s, int64_t wa, int64_t wb, Clock::time_p
   to.n_fir = (int)fj.size();
   to.n_mix = (int)mj.size();
   const size_t trig_off = put(tj.data(), tj.size() * sizeof(TrigJob));
-  // the tick's device work: table upload, every stage, trigger records into
-  // pinned host memory, the count into pinned host memory
+  // the tick's device work: tables and cleared counts, every stage, trigger
+  // records and their number into pinned host memory
   auto work = [&]() -> lloid_status {
-    HIP_TRY(hipMemcpyAsync(dtab, htab, off, hipMemcpyHostToDevice, st));
-    const lloid_status r = launch_stages(ctx, s->ct, dtab, to, items, false, s->thr, s->thr, xw, nullptr);
+    IngestArgs in;
+    in.tab_src = htab;
+    in.tab_dst = dtab;
+    in.tab_vecs = ceil_div((int64_t)off, 16);
+    in.zero = counts;
+    in.zero_n = n_blk;
+    HIP_TRY(launch_ingest(in, LLOID_F32, st));
+    const lloid_status r = launch_stages(ctx, s->ct, dtab, to, items, false, s->thr, s->thr, counts, xw, nullptr);
     if (r != LLOID_OK) return r;
-    HIP_TRY(launch_trigger_jobs((const TrigJob *)(dtab + trig_off), (int)tj.size(), rows * nw, s->thr, counts, total,
-                                cap, tk.htrig, st));
-    HIP_TRY(hipMemcpyAsync(tk.hcount, total, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+    HIP_TRY(launch_trigger_jobs((const TrigJob *)(dtab + trig_off), (int)tj.size(), rows * nw, s->thr, counts,
+                                tk.hcount, cap, tk.htrig, st));
     return LLOID_OK;
   };
   // the tick reads strain the ingest stream has written
@@ -823,8 +848,13 @@ extern "C" lloid_status lloid_stream_push(lloid_stream *s, int32_t detector, int
     HIP_TRY(launch_fill_u8(s->bad, sizeof(int), s->staging_stream));
     for (int64_t done = 0; done < n; done += s->push_max) {
       const int64_t m = std::min(n - done, s->push_max);
-      HIP_TRY(launch_convert((const char *)data + done * esz, dt, m, s->check_buf, 0, m, s->sscale, s->bad,
-                             s->staging_stream));
+      IngestArgs in;
+      in.src = (const char *)data + done * esz;
+      in.n = in.dst_len = m;
+      in.dst = s->check_buf;
+      in.scale = s->sscale;
+      in.bad = s->bad;
+      HIP_TRY(launch_ingest(in, dt, s->staging_stream));
     }
     HIP_TRY(hipMemcpyAsync(s->hbad, s->bad, sizeof(int), hipMemcpyDeviceToHost, s->staging_stream));
     HIP_TRY(hipStreamSynchronize(s->staging_stream));

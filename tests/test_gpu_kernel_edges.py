@@ -8,7 +8,10 @@ import pytest
 
 import oracle
 
-from gpu_util import ctx
+from workloads import configs
+from workloads.bank import SliceSpec
+
+from gpu_util import EPS_ABS, ctx
 
 pytestmark = pytest.mark.gpu
 
@@ -53,3 +56,60 @@ def test_gate_reach(half):
     want, count = oracle.gate(oracle.whiten(x, 1024, L, flat), thr, half)
     assert gated == count
     assert np.array_equal(out == 0, want == 0)
+
+
+# ------------------------------------------------- decimation, several levels a launch
+
+@pytest.mark.parametrize("level", [1, 2, 3, 4, 5, 6, 7])
+@pytest.mark.parametrize("n", [1, 700, 4097, 300000 + 17])
+def test_decimated_levels(level, n):
+    """A slice at every level (one to three decimation launches: four levels,
+    then two at a time), blocks shorter than a workgroup's run and ones of
+    many runs, long and short, against the oracle's peaks (FP32 tolerance)."""
+    from paper_2410_16416_amd import lloid
+    f0 = 4096
+    bank = configs.random_basis_bank(8, [SliceSpec(f0, 0, 32, 8), SliceSpec(f0 >> level, 128, 24, 8)], f0,
+                                     np.random.default_rng(900 + level))
+    x = np.random.default_rng(901 + n).standard_normal(n)
+    b = lloid.bank_from_svd(ctx(), bank, "f32")
+    try:
+        res = lloid.lloid_filter(b, 0, x, window=(1, 4), peaks=True)
+    finally:
+        lloid.lloid_bank_destroy(b)
+    lo = max(0, n - 20000)
+    lo -= lo % 1024
+    z = oracle.lloid_snr(bank, x, lo, n)
+    _, want, _, _ = oracle.peak_table(z, lo, f0, 1, 4)
+    assert np.max(np.abs(res.peak_snr[:, lo // 1024:] - want)) < EPS_ABS["f32"]
+
+
+# ------------------------------------------------- trigger compaction and phases
+
+@pytest.mark.parametrize("templates,windows", [(1, 1), (3, 21), (37, 122), (64, 33), (700, 6100)])
+@pytest.mark.parametrize("compute", ["f16", "f32"])
+def test_triggers_are_the_peaks_above_threshold(templates, windows, compute):
+    """The trigger list against the dense peak tables of the same call, from
+    one entry to more compaction blocks (4096) than the offsets are summed
+    without a scan for, and few to many entries per wave of the phase kernel:
+    the same records in template, window order, the same phases whether every
+    entry or only the triggers are asked for."""
+    from paper_2410_16416_amd import lloid
+    f0, wl = 1024, 8
+    bank = configs.random_basis_bank(templates, [SliceSpec(f0, 0, 64, 16)], f0, np.random.default_rng(50))
+    for sl in bank.slices:
+        sl.mixing *= 2.0 / np.sqrt(np.mean(np.sum(sl.mixing.reshape(templates, -1) ** 2, axis=1)))
+    x = np.random.default_rng(51).standard_normal(windows * wl - 3)
+    b = lloid.bank_from_svd(ctx(), bank, compute)
+    try:
+        dense = lloid.lloid_filter(b, 0, x, window=(1, 128), threshold=3.5, peaks=True)
+        only = lloid.lloid_filter(b, 0, x, window=(1, 128), threshold=3.5)
+    finally:
+        lloid.lloid_bank_destroy(b)
+    t, w = np.nonzero(dense.peak_snr >= np.float32(3.5))
+    for res in (dense, only):
+        assert res.n_triggers == t.size
+        assert np.array_equal(res.triggers["template_id"], t) and np.array_equal(res.triggers["window"], w)
+        assert np.array_equal(res.triggers["snr"], dense.peak_snr[t, w])
+        assert np.array_equal(res.triggers["sample"], dense.peak_sample[t, w])
+        assert np.array_equal(res.triggers["phase"], dense.peak_phase[t, w])
+    assert np.array_equal(dense.triggers, only.triggers)
