@@ -621,7 +621,8 @@ void lloid::add_bank_jobs(const lloid_bank *b, const LevelView *lv, int64_t t0, 
   mj.push_back(m);
 }
 
-void lloid::number_jobs(std::vector<FirJob> &fj, std::vector<UpJob> *uj, std::vector<MixJob> &mj, StageItems &n) {
+void lloid::number_jobs(std::vector<FirJob> &fj, std::vector<UpJob> *uj, std::vector<MixJob> &mj, int64_t win_len,
+                        const TileShapes &ts, int n_cu, StageItems &n) {
   // longest items first
   std::stable_sort(fj.begin(), fj.end(), [](const FirJob &a, const FirJob &b) { return a.np > b.np; });
   std::stable_sort(mj.begin(), mj.end(), [](const MixJob &a, const MixJob &b) { return a.kcat > b.kcat; });
@@ -635,12 +636,17 @@ void lloid::number_jobs(std::vector<FirJob> &fj, std::vector<UpJob> *uj, std::ve
     n.up[h] = it;
   }
   it = 0;
-  int64_t e = 0;
+  int64_t e = 0, tiles = 0;
+  for (const auto &m : mj) tiles += m.nw * m.n_rtiles;
+  // every compiled mixing tile takes a CU to itself (LDS or registers)
+  n.mix_parts = mix_parts(tiles, ceil_div(win_len, ts.mbn), n_cu);
   for (auto &m : mj) {
     m.item0 = it;
-    // windows in runs of 8 (one per XCD) per row tile; fewer than 8 windows
-    // run window-major over the row tiles, padded to a multiple of 8
-    it += m.nw >= 8 ? ceil_div(m.nw, 8) * 8 * m.n_rtiles : round_up(m.nw * m.n_rtiles, 8);
+    m.parts = n.mix_parts;
+    // (window, part) units in runs of 8 (one per XCD) per row tile; fewer than
+    // 8 units run unit-major over the row tiles, padded to a multiple of 8
+    const int64_t units = m.nw * m.parts;
+    it += units >= 8 ? ceil_div(units, 8) * 8 * m.n_rtiles : round_up(units * m.n_rtiles, 8);
     m.e0 = e;
     e += (int64_t)m.n_templates * m.nw;
     m.x0 = n.windows;
@@ -803,7 +809,6 @@ static lloid_status filter_banks(lloid_bank *const *banks, int nb, int32_t detec
     for (int i = 0; i < nb; ++i) {
       const size_t tab = (size_t)banks[i]->n_templates * W;
       add(tab, 4);
-      add(tab, 8);
       add(tab, 4);
       add(tab, 4);
       add(tab, 4);
@@ -816,7 +821,7 @@ static lloid_status filter_banks(lloid_bank *const *banks, int nb, int32_t detec
         if (sl.level > 0)
           for (int64_t ld : low_ld(ops, sl.level)) add((size_t)sl.lp * ld, low_esz(ct));
     }
-    add((size_t)trig_blocks(total_rows * W), 8);
+    add((size_t)(trig_blocks(total_rows * W) + total_rows * W), 8);
     add((size_t)xi_cap(wpc_), sizeof(XiUnit));
     add(2, 4);
     if (!direct_trig) add((size_t)std::max<int64_t>(dev_cap, 1), sizeof(lloid_trigger));
@@ -881,7 +886,6 @@ static lloid_status filter_banks(lloid_bank *const *banks, int nb, int32_t detec
   for (int i = 0; i < nb; ++i) {
     const size_t tab = (size_t)banks[i]->n_templates * W;
     bw[i].psnr = cv.take<float>(tab);
-    bw[i].pn = cv.take<int64_t>(tab);
     bw[i].pphase = cv.take<float>(tab);
     bw[i].pdt = cv.take<float>(tab);
     bw[i].psi = cv.take<float>(tab);
@@ -903,7 +907,9 @@ static lloid_status filter_banks(lloid_bank *const *banks, int nb, int32_t detec
     }
   }
   const int64_t n_blk = trig_blocks(total_rows * W);
-  int64_t *counts = cv.take<int64_t>((size_t)n_blk);
+  // the blocks' trigger counts, then every bank's peak samples, cleared together
+  int64_t *counts = cv.take<int64_t>((size_t)(n_blk + total_rows * W));
+  for (int i = 0; i < nb; ++i) bw[i].pn = counts + n_blk + bw[i].elem0;
   // the kernels write the trigger count and the data flag straight into the stage
   ResultWords *res = (ResultWords *)stage;
   res->total = 0;
@@ -922,6 +928,7 @@ static lloid_status filter_banks(lloid_bank *const *banks, int nb, int32_t detec
     StageItems items;
   };
   std::vector<Chunk> chunks(n_chunks);
+  bool split = false;   // some window's peaks are combined from parts
   char *htab = stage_tab ? stage + kStageHead : no_alloc ? host_tab.data() : (char *)ctx->pinned;
   size_t off = 0;
   auto put = [&](const void *src, size_t sz) -> size_t {
@@ -940,7 +947,8 @@ static lloid_status filter_banks(lloid_bank *const *banks, int nb, int32_t detec
     for (int i = 0; i < nb; ++i)
       add_bank_jobs(banks[i], lv.data(), t0, t1, n, wa, wb, win, bw[i], 1.f / (banks[i]->mix_scale * sscale),
                     (snr && i == 0) ? dsnr + t0 * 2 : nullptr, n, ts, fj, uj, mj);
-    number_jobs(fj, uj, mj, chunks[c].items);
+    number_jobs(fj, uj, mj, win_len, ts, ctx->n_cu, chunks[c].items);
+    split = split || chunks[c].items.mix_parts > 1;
     TabOffsets &to = chunks[c].to;
     to.fir = put(fj.data(), fj.size() * sizeof(FirJob));
     for (int h = 0; h < kMaxHops; ++h) {
@@ -978,7 +986,7 @@ static lloid_status filter_banks(lloid_bank *const *banks, int nb, int32_t detec
     d_strain = strain_tmp;
   }
   in.zero = counts;
-  in.zero_n = n_blk;
+  in.zero_n = n_blk + (split ? total_rows * W : 0);
   in.src = d_strain;
   in.n = n;
   in.dst = xl[0];

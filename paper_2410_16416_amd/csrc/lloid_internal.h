@@ -82,7 +82,7 @@ struct MixJob {
   const void *ocat;      // [..][kld] compute type, absolute sample ocat_abs0 at row 0;
                          // columns past kcat are never read
   float *peak_snr;       // [F][ld_peak], column w - w_base
-  int64_t *peak_n;
+  int64_t *peak_n;       // a peak key from the mixing kernels, the peak sample from the phase kernel
   float *peak_phase;
   float *peak_dt, *peak_si;   // sub-sample peak offset and value (triggers only)
   float *peak_xi;             // signal-consistency value (triggers only; banks with lags)
@@ -97,6 +97,8 @@ struct MixJob {
   float inv_scale;
   int rows, kcat, n_templates, n_rtiles, acorr_half;
   int kld;                    // row pitch of mix and ocat (kcat rounded up to 64)
+  int parts;                  // workgroups that share a window's column steps (peak keys of more than
+                              // one are combined in place: the table starts at zero)
 };
 
 // One unit of the signal-consistency tiles: triggers first .. first + n - 1
@@ -386,6 +388,7 @@ struct StageItems {
   int xi_kmax = 0;                 // largest kcat of such a job
   int64_t xi_acorr = 0;            // largest autocorrelation table of such a job (entries)
   int64_t xi_units = 0;            // signal-consistency units those jobs can list at most
+  int mix_parts = 1;               // workgroups per window of a row tile in the mixing launch
   int64_t up[kMaxHops] = {};       // items of each interpolation hop
 };
 
@@ -419,8 +422,10 @@ void add_bank_jobs(const lloid_bank *b, const LevelView *lv, int64_t t0, int64_t
                    int64_t wb, const Windows &win, const BankBufs &bb, float inv_scale, float *snr, int64_t snr_ld,
                    const TileShapes &ts, std::vector<FirJob> &fj, std::vector<UpJob> *uj,
                    std::vector<MixJob> &mj);
-// Sort longest-first and number the work items.
-void number_jobs(std::vector<FirJob> &fj, std::vector<UpJob> *uj, std::vector<MixJob> &mj, StageItems &n);
+// Sort longest-first, choose the mixing launch's parts per window (win_len:
+// samples of a window) and number the work items.
+void number_jobs(std::vector<FirJob> &fj, std::vector<UpJob> *uj, std::vector<MixJob> &mj, int64_t win_len,
+                 const TileShapes &ts, int n_cu, StageItems &n);
 // FIR, interpolation, mixing and phase launches over uploaded tables; ev:
 // NULL, or 8 events bracketing those four stages.
 constexpr int kChunkStages = 4;    // LLOID_STAGE_FIR .. LLOID_STAGE_PHASE

@@ -648,6 +648,55 @@ struct VN {
   int n;
 };
 
+// Row tile, window (within the job) and part of the window of workgroup b of
+// a job.  A window's column steps are shared by jb.parts workgroups, each a
+// run of them.  XCD-aware order: the 8 XCDs take workgroups round-robin
+// (every job's items start at a multiple of 8), so all row tiles of one
+// (window, part) unit get the same XCD and neighbouring slots (shared operand
+// rows in that XCD's L2).  A job of fewer than 8 units would leave XCDs idle
+// that way: its items run unit-major over the row tiles instead, spread over
+// all XCDs.
+struct MixUnit {
+  int rt, part;
+  int64_t wl;
+};
+
+__device__ __forceinline__ MixUnit mix_unit(const MixJob &jb, int64_t b) {
+  MixUnit m;
+  int64_t u;
+  if (jb.nw * jb.parts >= 8) {
+    const int64_t slot = b >> 3;
+    m.rt = (int)(slot % jb.n_rtiles);
+    u = (slot / jb.n_rtiles) * 8 + (b & 7);
+  } else {
+    m.rt = (int)(b % jb.n_rtiles);
+    u = b / jb.n_rtiles;
+  }
+  m.wl = u / jb.parts;
+  m.part = (int)(u - m.wl * jb.parts);
+  return m;
+}
+
+// A window peak as one ordered word: |z|^2 (its bits order as integers, it is
+// not negative), then the complement of the sample (relative to the window's
+// start), so that the largest word is the largest |z|^2 at its lowest
+// sample.  0: no sample compared greater than the initial -1.
+__device__ __forceinline__ uint64_t peak_key(VN p) {
+  return p.v < 0.f ? 0 : ((uint64_t)__float_as_uint(p.v) << 32) | (uint32_t)~p.n;
+}
+
+__device__ __forceinline__ VN peak_of_key(uint64_t k) {
+  return k ? VN{__uint_as_float((uint32_t)(k >> 32)), (int)~(uint32_t)k} : VN{-1.f, 0x7fffffff};
+}
+
+// A workgroup's peak of template i in window w: stored, or combined with the
+// other parts' (an integer maximum, so the order does not matter).
+__device__ __forceinline__ void put_peak(const MixJob &jb, int64_t i, int64_t w, VN p) {
+  uint64_t *k = (uint64_t *)jb.peak_n + (i * jb.ld_peak + (w - jb.w_base));
+  if (jb.parts == 1) *k = peak_key(p);
+  else if (p.v >= 0.f) atomicMax((unsigned long long *)k, (unsigned long long)peak_key(p));
+}
+
 template <typename T, int MT, int NT, int WM, int WN, int BK, bool SNR>
 __global__ __launch_bounds__(64 * WM * WN) void k_mix_peak(const MixJob *__restrict__ jobs, int n_jobs) {
   typedef Op<T> O;
@@ -659,25 +708,11 @@ __global__ __launch_bounds__(64 * WM * WN) void k_mix_peak(const MixJob *__restr
   __shared__ VN red[WN][BM / 2];
 
   const MixJob &jb = jobs[find_job(jobs, n_jobs, blockIdx.x)];
-  // XCD-aware order: the 8 XCDs take workgroups round-robin (every job's items
-  // start at a multiple of 8), so give all row tiles of one window the same
-  // XCD and neighbouring slots (shared operand rows in that XCD's L2).  A job
-  // of fewer than 8 windows would leave XCDs idle that way: its items run
-  // window-major over the row tiles instead, spread over all XCDs.
   const int64_t b = (int64_t)blockIdx.x - jb.item0;
-  const int n_rtiles = jb.n_rtiles;
-  int rt;
-  int64_t wl;   // window within the job
-  if (jb.nw >= 8) {
-    const int64_t slot = b >> 3;
-    rt = (int)(slot % n_rtiles);
-    wl = (slot / n_rtiles) * 8 + (b & 7);
-  } else {
-    rt = (int)(b % n_rtiles);
-    wl = b / n_rtiles;
-  }
-  if (wl >= jb.nw) return;
-  const int64_t w = jb.w0 + wl;
+  const MixUnit un = mix_unit(jb, b);
+  if (un.wl >= jb.nw) return;
+  const int rt = un.rt;
+  const int64_t w = jb.w0 + un.wl;
   const T *mix = (const T *)jb.mix;
   const int rows = jb.rows, kcat = jb.kcat, kld = jb.kld, n_templates = jb.n_templates;
   const float inv_scale = jb.inv_scale;
@@ -707,10 +742,15 @@ __global__ __launch_bounds__(64 * WM * WN) void k_mix_peak(const MixJob *__restr
   ChunkLoader<T, BN, BK, THREADS> lb;
   la.setup(kld);
   lb.setup(kld);
+  // the part's columns of the window, whole column steps
+  const int64_t all_steps = (we - ws + BN - 1) / BN;
+  const int64_t nbeg = ws + all_steps * un.part / jb.parts * BN;
+  const int64_t nfin = min(we, ws + all_steps * (un.part + 1) / jb.parts * BN);
+  if (nbeg >= nfin) return;   // a short last window has fewer steps than parts
   la.load(ra, 0);
-  lb.load(rb, 0);
+  lb.load(rb, (int)(nbeg - ws) * kld * ESZ);
   int it = 0;  // chunk counter across column steps: LDS buffer parity
-  for (int64_t n0 = ws; n0 < we; n0 += BN) {
+  for (int64_t n0 = nbeg; n0 < nfin; n0 += BN) {
     const int brow = (int)(n0 - ws) * kld * ESZ;   // byte offset of this step's first operand row
     f32x16 acc[MT][NT];
 #pragma unroll
@@ -728,7 +768,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_mix_peak(const MixJob *__restr
       if (c + 1 < nchunks) {
         la.load(ra, (c + 1) * BK * ESZ);
         lb.load(rb, brow + (c + 1) * BK * ESZ);
-      } else if (n0 + BN < we) {
+      } else if (n0 + BN < nfin) {
         la.load(ra, 0);
         lb.load(rb, brow + BN * kld * ESZ);
       }
@@ -799,11 +839,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_mix_peak(const MixJob *__restr
     for (int q = 1; q < WN; ++q)
       if (better(red[q][t].v, red[q][t].n, bb.v, bb.n)) bb = red[q][t];
     const int64_t i = r0 / 2 + t;
-    if (i < n_templates) {
-      const int64_t o = i * jb.ld_peak + (w - jb.w_base);
-      jb.peak_snr[o] = sqrtf(fmaxf(bb.v, 0.f)) * inv_scale;
-      jb.peak_n[o] = ws + bb.n;
-    }
+    if (i < n_templates) put_peak(jb, i, w, bb);
   }
 }
 
@@ -892,19 +928,10 @@ __global__ __launch_bounds__(64 * WM * WN, WGS) void k_mix_dl(const MixJob *__re
 
   const MixJob &jb = jobs[find_job(jobs, n_jobs, blockIdx.x)];
   const int64_t b = (int64_t)blockIdx.x - jb.item0;
-  const int n_rtiles = jb.n_rtiles;
-  int rt;
-  int64_t wl;
-  if (jb.nw >= 8) {
-    const int64_t slot = b >> 3;
-    rt = (int)(slot % n_rtiles);
-    wl = (slot / n_rtiles) * 8 + (b & 7);
-  } else {
-    rt = (int)(b % n_rtiles);
-    wl = b / n_rtiles;
-  }
-  if (wl >= jb.nw) return;
-  const int64_t w = jb.w0 + wl;
+  const MixUnit un = mix_unit(jb, b);
+  if (un.wl >= jb.nw) return;
+  const int rt = un.rt;
+  const int64_t w = jb.w0 + un.wl;
   const T *mix = (const T *)jb.mix;
   const int rows = jb.rows, kcat = jb.kcat, kld = jb.kld, n_templates = jb.n_templates;
   const float inv_scale = jb.inv_scale;
@@ -929,7 +956,11 @@ __global__ __launch_bounds__(64 * WM * WN, WGS) void k_mix_dl(const MixJob *__re
   const __amdgpu_buffer_rsrc_t rb = make_rsrc(ocat, (we - ws) * (int64_t)kld * ESZ);
   const int nchunks = (kcat + BK - 1) / BK;
   const bool half_tail = (kcat % BK) != 0;   // K chunks of 64: the last one holds 32 columns
-  const int nsteps = (int)((we - ws + BN - 1) / BN);
+  // column steps [st0, st0 + nsteps) of the window are this part's
+  const int all_steps = (int)((we - ws + BN - 1) / BN);
+  const int st0 = all_steps * un.part / jb.parts;
+  const int nsteps = all_steps * (un.part + 1) / jb.parts - st0;
+  if (nsteps <= 0) return;   // a short last window has fewer steps than parts
   const int G = nsteps * nchunks;
   // Load instruction j of this wave fills LDS rows RPI (NW j + wave) .. + RPI - 1
   // of a tile, lane i the 16-byte position i % CPR of row RPI (NW j + wave) +
@@ -942,7 +973,7 @@ __global__ __launch_bounds__(64 * WM * WN, WGS) void k_mix_dl(const MixJob *__re
   const int voffs_tail = lq < R::CPR / 2 ? voffs : 0x7ff00000;   // upper half of a half chunk: zeros
   const int jstep = R::RPI * NW * kld * ESZ;
   auto issue = [&](int g) {
-    const int c = g % nchunks, st = g / nchunks;
+    const int c = g % nchunks, st = st0 + g / nchunks;
     const int ka = c * BK * ESZ;
     const int kb = st * BN * kld * ESZ + ka;
     const int vo = (half_tail && c == nchunks - 1) ? voffs_tail : voffs;
@@ -1006,7 +1037,7 @@ __global__ __launch_bounds__(64 * WM * WN, WGS) void k_mix_dl(const MixJob *__re
     for (int c = 1; c < nchunks; ++c) chunk(std::false_type{}, half_tail && c == nchunks - 1);
     // epilogue of the column step: complex SNR of 8 templates per lane per
     // row tile, running peaks
-    const int64_t n0 = ws + (int64_t)st * BN;
+    const int64_t n0 = ws + (int64_t)(st0 + st) * BN;
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
       const int64_t col = n0 + wn * 32 * NT + nt * 32 + fr;
@@ -1054,11 +1085,7 @@ __global__ __launch_bounds__(64 * WM * WN, WGS) void k_mix_dl(const MixJob *__re
     for (int q = 1; q < WN; ++q)
       if (better(red[q][t].v, red[q][t].n, bb.v, bb.n)) bb = red[q][t];
     const int64_t i = r0 / 2 + t;
-    if (i < n_templates) {
-      const int64_t o = i * jb.ld_peak + (w - jb.w_base);
-      jb.peak_snr[o] = sqrtf(fmaxf(bb.v, 0.f)) * inv_scale;
-      jb.peak_n[o] = ws + bb.n;
-    }
+    if (i < n_templates) put_peak(jb, i, w, bb);
   }
 }
 
@@ -1067,7 +1094,8 @@ __global__ __launch_bounds__(64 * WM * WN, WGS) void k_mix_dl(const MixJob *__re
 // operand rows (FP32 accumulation; the operand holds one extra sample on each
 // side of a chunk).  The refinement is the vertex of the parabola through the
 // three |z| values (offset clipped to half a sample; none when the triple is
-// not concave).  Peaks below `thr` get zeros (not reported).
+// not concave).  Peaks below `thr` get zeros (not reported).  The kernel first
+// turns the mixing kernels' peak keys into |z| and the peak sample.
 // One thread per (template, window) entry tests the threshold and writes the
 // zeros; then the whole wave takes its entries above it two at a time: lane k
 // reads 16-byte vector k of each of the 5 rows of both (all 10 reads in
@@ -1095,7 +1123,7 @@ __global__ __launch_bounds__(256) void k_peak_phase(const MixJob *__restrict__ j
   const int lane = threadIdx.x & 63;
   const int64_t e = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * per + lane;
   int job = 0;
-  int64_t o = 0, row = 0;   // peak-table offset and template of this lane's entry
+  int64_t o = 0, row = 0, pn = 0;   // peak-table offset, template and peak sample of this lane's entry
   int64_t blk = -1;         // trigger-compaction block it counts in, if it is a trigger
   bool hit = false;
   // the signal-consistency launches, next in the stream, start from zero counters
@@ -1112,8 +1140,14 @@ __global__ __launch_bounds__(256) void k_peak_phase(const MixJob *__restrict__ j
     const MixJob &jb = jobs[lo];
     const int64_t le = e - jb.e0;
     row = le / jb.nw;
-    o = row * jb.ld_peak + (jb.w0 + le - row * jb.nw - jb.w_base);
-    const float snr = jb.peak_snr[o];
+    const int64_t w = jb.w0 + le - row * jb.nw;
+    o = row * jb.ld_peak + (w - jb.w_base);
+    // the mixing kernels leave the peak as a key (peak_key) in the sample's place
+    const VN pk = peak_of_key(((const uint64_t *)jb.peak_n)[o]);
+    const float snr = sqrtf(fmaxf(pk.v, 0.f)) * jb.inv_scale;
+    pn = (w * jb.win_p) / jb.win_q + pk.n;
+    jb.peak_snr[o] = snr;
+    jb.peak_n[o] = pn;
     hit = snr >= thr;
     if (snr >= trig_thr) blk = (jb.t0 + o) / kTrigPerBlock;
     if (!hit) {
@@ -1154,10 +1188,12 @@ __global__ __launch_bounds__(256) void k_peak_phase(const MixJob *__restrict__ j
                         (uint32_t)__builtin_amdgcn_readlane((int)row, src[t]);
       ox[t] = ((int64_t)__builtin_amdgcn_readlane((int)(o >> 32), src[t]) << 32) |
               (uint32_t)__builtin_amdgcn_readlane((int)o, src[t]);
+      const int64_t n = ((int64_t)__builtin_amdgcn_readlane((int)(pn >> 32), src[t]) << 32) |
+                        (uint32_t)__builtin_amdgcn_readlane((int)pn, src[t]);
       // kcat and the row pitch kld are multiples of 32: whole 16-byte vectors
       nv[t] = jb.kcat / EPV;
       pv[t] = jb.kld / EPV;
-      o0[t] = (const uint4 *)((const T *)jb.ocat + (jb.peak_n[ox[t]] - 1 - jb.ocat_abs0) * (int64_t)jb.kld);
+      o0[t] = (const uint4 *)((const T *)jb.ocat + (n - 1 - jb.ocat_abs0) * (int64_t)jb.kld);
       mc[t] = (const uint4 *)((const T *)jb.mix + (2 * r) * (int64_t)jb.kld);
       ms[t] = mc[t] + pv[t];
 #pragma unroll

@@ -123,6 +123,18 @@ int64_t ready_until(const ReadyState &st) {
   return best;
 }
 
+int mix_parts(int64_t tiles, int64_t steps, int64_t slots) {
+  if (tiles <= 0 || steps <= 1 || slots <= 0) return 1;
+  auto time = [&](int64_t p) {
+    return (double)ceil_div(tiles * p, slots) * ((double)ceil_div(steps, p) + kMixOverhead);
+  };
+  int64_t best = 1;
+  double t = 0.96 * time(1);
+  for (int64_t p = 2; p <= steps && p <= 64; ++p)
+    if (time(p) < t) best = p, t = time(p);
+  return (int)best;
+}
+
 static uint16_t bf16_round(float f) {
   uint32_t u;
   std::memcpy(&u, &f, 4);

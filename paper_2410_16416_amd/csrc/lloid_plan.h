@@ -116,6 +116,18 @@ struct ReadyState {
 };
 int64_t ready_until(const ReadyState &st);
 
+// Workgroups that share one window of one row tile in the mixing launch:
+// `tiles` (row tile, window) pairs of `steps` column steps each on `slots`
+// workgroup slots.  A launch takes ceil(tiles p / slots) rounds of ceil(steps
+// / p) steps and a workgroup costs about kMixOverhead of a step besides (the
+// first chunk's latency, the peaks' reduction).  The p with the smallest such
+// time, and 1 unless that gains more than 4 %.  Measured on 256 CUs, mixing
+// kernel, one workgroup per window against this rule: 72 tiles of 8 steps (an
+// 8 s block of 1024 templates) 98 -> 49 us, 384 tiles (48 s) in FP32 1880 ->
+// 1487 us and with the SNR series 331 -> 285 us; 8192 tiles (1024 s) stay whole.
+constexpr double kMixOverhead = 0.75;
+int mix_parts(int64_t tiles, int64_t steps, int64_t slots);
+
 // BF16 (8-bit significand) pair of a finite FP32 value, as bit patterns:
 // hi = x rounded to nearest (ties to even), lo = (x - hi) rounded likewise,
 // so that hi + lo carries 16 significant bits of x (the interpolation

@@ -365,7 +365,6 @@ lloid_status enqueue_tick(lloid_stream *s, int64_t wa, int64_t wb, Clock::time_p
       }
       for (int k = 0; k < 5; ++k) add((size_t)b->n_templates * nw, 4);
       add((size_t)b->n_templates * nw, 8);
-      add((size_t)b->n_templates * nw, 8);
       if (b->acorr) {
         add((size_t)b->n_templates * nw, 8);
         xi_cap += xi_unit_cap(nw, b->n_templates);
@@ -373,7 +372,7 @@ lloid_status enqueue_tick(lloid_stream *s, int64_t wa, int64_t wb, Clock::time_p
     }
     rows += (int64_t)b->n_templates * s->n_det;
   }
-  add((size_t)trig_blocks(rows * nw), 8);
+  add((size_t)(trig_blocks(rows * nw) + rows * nw), 8);
   add((size_t)xi_cap, sizeof(XiUnit));
   add(2, 4);
   const size_t tab_bytes = n_fir * sizeof(FirJob) + n_up * sizeof(UpJob) +
@@ -406,6 +405,9 @@ lloid_status enqueue_tick(lloid_stream *s, int64_t wa, int64_t wb, Clock::time_p
     tk.htrig_cap = cap;
   }
   Carve cv{(char *)s->ws.base};
+  // the blocks' trigger counts, then every peak table's samples, cleared together
+  const int64_t n_blk = trig_blocks(rows * nw);
+  int64_t *counts = cv.take<int64_t>((size_t)(n_blk + rows * nw));
   std::vector<FirJob> fj;
   std::vector<UpJob> uj[kMaxHops];
   std::vector<MixJob> mj;
@@ -427,7 +429,7 @@ lloid_status enqueue_tick(lloid_stream *s, int64_t wa, int64_t wb, Clock::time_p
       bb.pdt = cv.take<float>((size_t)b->n_templates * nw);
       bb.psi = cv.take<float>((size_t)b->n_templates * nw);
       bb.pxi = cv.take<float>((size_t)b->n_templates * nw);
-      bb.pn = cv.take<int64_t>((size_t)b->n_templates * nw);
+      bb.pn = counts + n_blk + row * nw;
       bb.pz = cv.take<float2>((size_t)b->n_templates * nw);
       if (b->acorr) bb.pkey = cv.take<int64_t>((size_t)b->n_templates * nw);
       bb.ld_peak = nw;
@@ -443,15 +445,13 @@ lloid_status enqueue_tick(lloid_stream *s, int64_t wa, int64_t wb, Clock::time_p
       row += b->n_templates;
     }
   }
-  const int64_t n_blk = trig_blocks(rows * nw);
-  int64_t *counts = cv.take<int64_t>((size_t)n_blk);
   XiWork xw;
   xw.cap = xi_cap;
   xw.units = cv.take<XiUnit>((size_t)xi_cap);
   xw.counters = cv.take<int32_t>(2);
   char *dtab = (char *)s->ws.base + tab_base + (size_t)ti * s->tab_area;
   StageItems items;
-  number_jobs(fj, uj, mj, items);
+  number_jobs(fj, uj, mj, s->win_len, ts, ctx->n_cu, items);
   char *htab = (char *)tk.htab;
   size_t off = 0;
   auto put = [&](const void *src, size_t sz) -> size_t {
@@ -479,7 +479,7 @@ lloid_status enqueue_tick(lloid_stream *s, int64_t wa, int64_t wb, Clock::time_p
     in.tab_dst = dtab;
     in.tab_vecs = ceil_div((int64_t)off, 16);
     in.zero = counts;
-    in.zero_n = n_blk;
+    in.zero_n = n_blk + (items.mix_parts > 1 ? rows * nw : 0);
     HIP_TRY(launch_ingest(in, LLOID_F32, st));
     const lloid_status r = launch_stages(ctx, s->ct, dtab, to, items, false, s->thr, s->thr, counts, xw, nullptr);
     if (r != LLOID_OK) return r;
@@ -500,6 +500,7 @@ lloid_status enqueue_tick(lloid_stream *s, int64_t wa, int64_t wb, Clock::time_p
     key.push_back(xw.cap);
     key.push_back(ctx->fir_variant * 16 + ctx->mix_variant);
     key.push_back(items.windows);
+    key.push_back(items.mix_parts);
     for (int h = 0; h < kMaxHops; ++h) {
       key.push_back(items.up[h]);
       key.push_back((int64_t)to.up[h]);

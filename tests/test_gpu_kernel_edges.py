@@ -113,3 +113,36 @@ def test_triggers_are_the_peaks_above_threshold(templates, windows, compute):
         assert np.array_equal(res.triggers["sample"], dense.peak_sample[t, w])
         assert np.array_equal(res.triggers["phase"], dense.peak_phase[t, w])
     assert np.array_equal(dense.triggers, only.triggers)
+
+
+# ------------------------------------------------- windows shared by workgroups
+
+@pytest.mark.parametrize("compute", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("tail", [0, 1, 255, 256, 257, 1300])
+@pytest.mark.parametrize("seconds,win", [(1, (1, 1)), (3, (3, 2)), (2, (1, 16))])
+def test_split_windows(compute, tail, seconds, win):
+    """Few windows: each is shared by several workgroups, a short last window by
+    more than it has column steps.  Peaks against the oracle; the allocation-free
+    call and every mixing tile shape (other step widths, other splits) equal bit
+    for bit."""
+    from paper_2410_16416_amd import lloid
+    bank = configs.mini_multirate_bank()
+    n = seconds * bank.f0 * 2 + tail
+    x = np.random.default_rng(60 + tail).standard_normal(n)
+    _, want, at, _ = oracle.peak_table(oracle.lloid_snr(bank, x), 0, bank.f0, *win)
+    b = lloid.bank_from_svd(ctx(), bank, compute)
+    try:
+        res = lloid.lloid_filter(b, 0, x, window=win, peaks=True, threshold=2.5)
+        assert np.max(np.abs(res.peak_snr - want)) < EPS_ABS[compute]
+        if compute == "f32":
+            assert np.mean(res.peak_sample != at) < 0.02   # near ties only
+        same = [lloid.lloid_filter_noalloc(b, 0, x, window=win, peaks=True, threshold=2.5)]
+        for v in range(1, lloid.MIX_VARIANTS):
+            lloid.lloid_ctx_set_tiles(ctx(), 0, v)
+            same.append(lloid.lloid_filter(b, 0, x, window=win, peaks=True, threshold=2.5))
+    finally:
+        lloid.lloid_ctx_set_tiles(ctx(), 0, 0)
+        lloid.lloid_bank_destroy(b)
+    for r in same:
+        assert np.array_equal(r.peak_snr, res.peak_snr) and np.array_equal(r.peak_sample, res.peak_sample)
+        assert np.array_equal(r.triggers, res.triggers)
