@@ -623,8 +623,19 @@ void lloid::add_bank_jobs(const lloid_bank *b, const LevelView *lv, int64_t t0, 
 
 void lloid::number_jobs(std::vector<FirJob> &fj, std::vector<UpJob> *uj, std::vector<MixJob> &mj, int64_t win_len,
                         const TileShapes &ts, int n_cu, StageItems &n) {
-  // longest items first
-  std::stable_sort(fj.begin(), fj.end(), [](const FirJob &a, const FirJob &b) { return a.np > b.np; });
+  if (ts.nbn) {
+    int64_t work = 0;
+    for (const auto &j : fj) work += (int64_t)j.n_rtiles * j.n_ctiles * j.np;
+    for (auto &j : fj)
+      if (fir_narrow(j.np, work, n_cu)) {
+        j.narrow = 1;
+        j.n_rtiles = (int)ceil_div(j.rows, ts.nbm);
+        j.n_ctiles = (int)ceil_div(j.k_hi - j.k_lo, ts.nbn);
+      }
+  }
+  // longest items first (a narrow tile takes about 3/8 of a wide one's time)
+  auto cost = [](const FirJob &j) { return j.narrow ? 3 * (int64_t)j.np : 8 * (int64_t)j.np; };
+  std::stable_sort(fj.begin(), fj.end(), [&](const FirJob &a, const FirJob &b) { return cost(a) > cost(b); });
   std::stable_sort(mj.begin(), mj.end(), [](const MixJob &a, const MixJob &b) { return a.kcat > b.kcat; });
   int64_t it = 0;
   for (auto &j : fj) j.item0 = it, it += (int64_t)j.n_rtiles * j.n_ctiles;

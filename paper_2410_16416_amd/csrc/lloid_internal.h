@@ -59,7 +59,7 @@ struct FirJob {
   int64_t x_lo, x_len, base, k_lo, k_hi, out_lo, item0;
   int rows, np, ldo, col0, col_limit, n_rtiles, n_ctiles, out_f32;
   int out_cm;            // channel-major output: out[l * ldo + (k - out_lo)]
-  int pad;
+  int narrow;            // narrow tiles (fir_narrow_shape) instead of the variant's
 };
 
 // Interpolation of channel-major rows by R = 2 or 4 (one or two half-band x2
@@ -240,6 +240,8 @@ inline int decim_group(int k, int left) { return std::min(left, k == 0 ? kDecimG
 // same order), only the speed differs.  Rows x columns per workgroup:
 constexpr int kFirVariants = LLOID_FIR_VARIANTS, kMixVariants = LLOID_MIX_VARIANTS;
 void fir_tile_shape(lloid_dtype t, int variant, int *bm, int *bn);
+// The narrow tile that a variant's launch also takes, zeros if none.
+void fir_narrow_shape(int variant, int *bm, int *bn);
 void mix_tile_shape(lloid_dtype t, int variant, int *bm, int *bn);
 // One launch per stage over a device descriptor table (see the job structs).
 hipError_t launch_fir_jobs(lloid_dtype t, int variant, const FirJob *jobs, int n_jobs, int64_t n_items,
@@ -373,9 +375,10 @@ struct BankBufs {
 };
 
 struct TileShapes {
-  int fbm, fbn, mbm, mbn;
+  int fbm, fbn, nbm, nbn, mbm, mbn;
   TileShapes(lloid_dtype t, int fir_variant, int mix_variant) {
     fir_tile_shape(t, fir_variant, &fbm, &fbn);
+    fir_narrow_shape(fir_variant, &nbm, &nbn);
     mix_tile_shape(t, mix_variant, &mbm, &mbn);
   }
 };
@@ -422,8 +425,8 @@ void add_bank_jobs(const lloid_bank *b, const LevelView *lv, int64_t t0, int64_t
                    int64_t wb, const Windows &win, const BankBufs &bb, float inv_scale, float *snr, int64_t snr_ld,
                    const TileShapes &ts, std::vector<FirJob> &fj, std::vector<UpJob> *uj,
                    std::vector<MixJob> &mj);
-// Sort longest-first, choose the mixing launch's parts per window (win_len:
-// samples of a window) and number the work items.
+// Choose the FIR jobs' tile width and the mixing launch's parts per window
+// (win_len: samples of a window), sort longest-first and number the work items.
 void number_jobs(std::vector<FirJob> &fj, std::vector<UpJob> *uj, std::vector<MixJob> &mj, int64_t win_len,
                  const TileShapes &ts, int n_cu, StageItems &n);
 // FIR, interpolation, mixing and phase launches over uploaded tables; ev:

@@ -260,28 +260,99 @@ template <typename T, int ROWS, int BK = kBK, int THREADS = kThreads> struct Chu
 // g + 2 nt (32 columns = 2 k-steps of 16 taps).  Each wave then keeps, per
 // k-step parity, a window of NT fragments in registers and reads one new
 // fragment from LDS per k-step instead of NT.
-template <typename T, int MT, int NT, int NW, int BK, bool HR = false>
-__global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void k_fir(const FirJob *__restrict__ jobs, int n_jobs) {
+// N strain samples from index i of the level (out of range: zero), all reads
+// in flight at once.
+template <int N>
+__device__ __forceinline__ void fir_window_read(__amdgpu_buffer_rsrc_t rx, int64_t i, int64_t x_len, float (&v)[N]) {
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    const int off = (i + u >= 0 && i + u < x_len) ? (int)(i + u) * 4 : -4;
+    v[u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rx, off, 0, 0));
+  }
+}
+
+// One 16-byte unit of each of the VEC shifted copies (copy r starts at r WC):
+// v[r ..] from position `at`.
+template <typename T, int WC, int N> __device__ __forceinline__ void fir_window_write(T *at, const float (&v)[N]) {
+  constexpr int G = 16 / (int)sizeof(T);
+#pragma unroll
+  for (int r = 0; r < Op<T>::VEC; ++r) {
+    T h[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) h[g] = Op<T>::cvt(v[r + g]);
+    *(uint4 *)(at + r * WC) = __builtin_bit_cast(uint4, h);
+  }
+}
+
+// Output of one wave: basis rows from rbeg, columns from cbeg.  A lane holds
+// column cbeg + 32 nt + lane % 32, rows rb..rb+3 for each group of four; level-0
+// slices write the time-major operand, lower-rate slices a channel-major
+// buffer for the interpolation (FP32 when the operand type is BF16).
+template <typename T, int MT, int NT>
+__device__ __forceinline__ void fir_store(const FirJob &jb, const f32x16 (&acc)[MT][NT], int rbeg, int64_t cbeg) {
+  typedef Op<T> O;
+  const int lane = threadIdx.x & 63;
+  const int col_limit = jb.col_limit, ldo = jb.ldo;
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    const int64_t col = cbeg + nt * 32 + (lane & 31);
+    if (col >= jb.k_hi) continue;
+    const int64_t ro = (col - jb.out_lo) * (int64_t)ldo + jb.col0;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int rb = rbeg + mt * 32 + 8 * g + 4 * (lane >> 5);
+        if (rb + 4 <= col_limit) {
+          if (jb.out_cm && jb.out_f32) {
+            float *o = (float *)jb.out + (col - jb.out_lo);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) o[(int64_t)(rb + q) * ldo] = acc[mt][nt][4 * g + q];
+          } else if (jb.out_cm) {
+            T *o = (T *)jb.out + (col - jb.out_lo);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) o[(int64_t)(rb + q) * ldo] = O::cvt(acc[mt][nt][4 * g + q]);
+          } else if (jb.out_f32) {
+            float *o = (float *)jb.out + ro + rb;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) o[q] = acc[mt][nt][4 * g + q];
+          } else {
+            T *o = (T *)jb.out + ro + rb;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) o[q] = O::cvt(acc[mt][nt][4 * g + q]);
+          }
+        }
+      }
+  }
+}
+
+// WM x WN waves, each 32 MT basis rows x 32 NT columns.
+template <typename T, int MT, int NT, int WM, int WN, int BK, bool HR> struct FirTile {
   typedef Op<T> O;
   static_assert(!HR || O::KS == 16, "the fragment window needs 16 taps per k-step");
-  constexpr int THREADS = 64 * NW;
-  constexpr int BM = 32 * MT, BN = NW * 32 * NT;
-  constexpr int P = Pitch<T, BK>::value;
+  static constexpr int THREADS = 64 * WM * WN;
+  static constexpr int BM = 32 * MT * WM, BN = 32 * NT * WN;
+  static constexpr int P = Pitch<T, BK>::value;
   // strain window: BN columns + kFirKSup taps (+ the fragments the HR window
   // reads ahead past its last k-step).  With 16-bit operands the copies are
   // padded to WC = 32 mod 64 elements: the 16-byte fragment reads, each lane
   // in its own copy, then run without LDS bank conflicts (the bank-conflict
   // counter reads zero there; at 0, 16, 40 and 48 mod 64 it does not)
-  constexpr int WC0 = BN + kFirKSup + 16 + (HR ? 2 * NT * 16 : 0);
-  constexpr int WC = O::VEC == 8 ? (WC0 + 31) / 64 * 64 + 32 : WC0;
-  __shared__ __attribute__((aligned(16))) T As[2][BM * P];
-  __shared__ __attribute__((aligned(16))) T Bc[O::VEC * WC];
+  static constexpr int WC0 = BN + kFirKSup + 16 + (HR ? 2 * NT * 16 : 0);
+  static constexpr int WC = O::VEC == 8 ? (WC0 + 31) / 64 * 64 + 32 : WC0;
+  static constexpr int A_BYTES = (BM * P * (int)sizeof(T) + 15) / 16 * 16;   // one basis chunk
+  static constexpr int LDS = 2 * A_BYTES + O::VEC * WC * (int)sizeof(T);
 
-  const FirJob &jb = jobs[find_job(jobs, n_jobs, blockIdx.x)];
-  const int64_t li = (int64_t)blockIdx.x - jb.item0;
+  static __device__ __forceinline__ void run(const FirJob &jb, int64_t li, char *lds);
+};
+
+template <typename T, int MT, int NT, int WM, int WN, int BK, bool HR>
+__device__ __forceinline__ void FirTile<T, MT, NT, WM, WN, BK, HR>::run(const FirJob &jb, int64_t li, char *lds) {
+  T *const Bc = (T *)(lds + 2 * A_BYTES);
   const int rows = jb.rows, np = jb.np;
   const T *a = (const T *)jb.basis;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int wm = (threadIdx.x >> 6) / WN, wn = (threadIdx.x >> 6) % WN;
   const int64_t r0 = (li % jb.n_rtiles) * BM;
   const int64_t i0 = jb.k_lo + (li / jb.n_rtiles) * BN;
 
@@ -305,17 +376,18 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void k_fir(const FirJob *
   const int nchunks = (np + BK - 1) / BK;
   // lane's shifted copy: its column offset within a fragment is constant mod VEC
   const int lr = (lane & 31) % O::VEC;
-  const T *bl = Bc + lr * WC + (wave * NT * 32 + (lane & 31) + (lane >> 5) * O::VEC - lr);
+  const T *bl = Bc + lr * WC + (wn * NT * 32 + (lane & 31) + (lane >> 5) * O::VEC - lr);
   // 32-column fragments of this wave that start before k_hi: a wave wholly
   // past the end of a ragged last tile skips its MFMAs (it still loads and
   // syncs); the HR window needs all NT fragments, so a partly live wave takes
   // the plain k-steps
-  const int64_t wcol = i0 + wave * NT * 32;
+  const int64_t wcol = i0 + wn * NT * 32;
   const int live = (int)(jb.k_hi <= wcol ? 0 : std::min<int64_t>(NT, (jb.k_hi - wcol + 31) / 32));
   int ksup = 0;
   typename O::vec hw[2][HR ? NT : 1];   // HR: fragment windows of the even and odd k-steps
   for (int c = 0; c < nchunks; ++c) {
-    const int cur = c & 1, kc = c * BK;
+    const int kc = c * BK;
+    T *const at = (T *)(lds + (c & 1) * A_BYTES);
     if (kc % kFirKSup == 0) {
       // new strain window for taps [kc, kc + kFirKSup); out-of-range samples read as zero
       if (c > 0) __syncthreads();
@@ -328,22 +400,11 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void k_fir(const FirJob *
       static_assert(WC % G == 0, "the strain window is whole 16-byte units");
       for (int t0 = threadIdx.x * G; t0 < WC; t0 += THREADS * G) {
         float v[G + O::VEC - 1];
-#pragma unroll
-        for (int u = 0; u < G + O::VEC - 1; ++u) {
-          const int64_t idx = w0 + t0 + u;
-          const int off = (idx >= 0 && idx < x_len) ? (int)idx * 4 : -4;
-          v[u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rx, off, 0, 0));
-        }
-#pragma unroll
-        for (int r = 0; r < O::VEC; ++r) {
-          T h[G];
-#pragma unroll
-          for (int g = 0; g < G; ++g) h[g] = O::cvt(v[r + g]);
-          *(uint4 *)(Bc + r * WC + t0) = __builtin_bit_cast(uint4, h);
-        }
+        fir_window_read<G + O::VEC - 1>(rx, w0 + t0, x_len, v);
+        fir_window_write<T, WC>(Bc + t0, v);
       }
     }
-    la.store(As[cur]);
+    la.store(at);
     __syncthreads();
     if (c + 1 < nchunks) la.load(ra, (kc + BK) * (int)sizeof(T));
     auto ksteps = [&]() __attribute__((always_inline)) {
@@ -353,7 +414,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void k_fir(const FirJob *
         typename O::vec af[MT], bf[NT];
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
-          af[mt] = *(const typename O::vec *)(As[cur] + (mt * 32 + (lane & 31)) * P + ks * O::KS + (lane >> 5) * O::VEC);
+          af[mt] = *(const typename O::vec *)(at + (wm * 32 * MT + mt * 32 + (lane & 31)) * P + ks * O::KS +
+                                             (lane >> 5) * O::VEC);
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) bf[nt] = *(const typename O::vec *)(bl + (kc - ksup) + nt * 32 + ks * O::KS);
 #pragma unroll
@@ -382,8 +444,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void k_fir(const FirJob *
           typename O::vec af[MT];
 #pragma unroll
           for (int mt = 0; mt < MT; ++mt)
-            af[mt] = *(const typename O::vec *)(As[cur] + (mt * 32 + (lane & 31)) * P + ks * O::KS +
-                                                 (lane >> 5) * O::VEC);
+            af[mt] = *(const typename O::vec *)(at + (wm * 32 * MT + mt * 32 + (lane & 31)) * P + ks * O::KS +
+                                               (lane >> 5) * O::VEC);
 #pragma unroll
           for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
@@ -401,41 +463,147 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void k_fir(const FirJob *
     }
   }
 
-  // store: lane holds column i, rows rb..rb+3 for each group of four; level-0
-  // slices write the time-major operand, lower-rate slices a channel-major
-  // buffer for the interpolation (FP32 when the operand type is BF16)
-  const int col_limit = jb.col_limit, ldo = jb.ldo;
+  fir_store<T, MT, NT>(jb, acc, (int)r0 + wm * 32 * MT, i0 + wn * NT * 32);
+}
+
+// Narrow tile of 16-bit operands: 64 basis rows x 128 columns, 2 x 2 waves of
+// 32 x 64 with the Hankel fragment window.  It is for deep filters with few
+// columns, where a CU has little work at a time and the basis comes from
+// memory: a chunk of 64 taps is 256 cycles of MFMAs per wave against a read
+// latency of some 2000, so the chunks go straight into a ring of kRing LDS
+// buffers, six ahead (rows of 128 bytes, 16-byte chunks swizzled as in the
+// mixing kernel), and a window's strain reads go out a chunk early.
+// FIR of an 8 s block of 1024 templates 52 -> 34 us, of a serving tick of 12
+// banks 57 -> 38 us, of the 64-template single-rate call 18 -> 12 us; the same
+// tile with the wide one's register-staged chunks took 41 us on the first.
+// Fragment reads of 1 KB per MFMA bound it where it fills a CU (the wide tile
+// reads 0.4 KB), so a full chip keeps the wide tile.
+template <typename T> struct FirNarrow16 {
+  typedef Op<T> O;
+  typedef typename O::vec vec;
+  static constexpr int BM = 64, BN = 128, BK = 64, NT = 2, kRing = 7;
+  static constexpr int THREADS = 256;
+  static constexpr int WC0 = BN + kFirKSup + 16 + 2 * NT * 16;
+  static constexpr int WC = (WC0 + 31) / 64 * 64 + 32;
+  static constexpr int CHUNK = BM * BK * 2;
+  static constexpr int LDS = kRing * CHUNK + 8 * WC * 2;
+  static_assert(WC >= WC0 && WC % 8 == 0 && WC <= THREADS * 8, "one 16-byte unit of the window per thread at most");
+  static_assert(kFirKSup % BK == 0, "whole chunks per strain window");
+
+  static __device__ __forceinline__ void run(const FirJob &jb, int64_t li, char *lds) {
+    typedef __attribute__((address_space(3))) void lds_ptr;
+    T *const Bc = (T *)(lds + kRing * CHUNK);
+    const int rows = jb.rows, np = jb.np;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+    const int64_t r0 = (li % jb.n_rtiles) * BM;
+    const int64_t i0 = jb.k_lo + (li / jb.n_rtiles) * BN;
+    const __amdgpu_buffer_rsrc_t ra =
+        make_rsrc((const T *)jb.basis + r0 * np, (rows - r0) * (int64_t)np * (int64_t)sizeof(T));
+    const __amdgpu_buffer_rsrc_t rx = make_rsrc(jb.x, jb.x_len * 4);
+    const int64_t x_len = jb.x_len;
+    const int nchunks = (np + BK - 1) / BK;
+    // load j of a chunk: rows 32 j + 8 wave .. + 7, lane's 16 bytes at position lane % 8 of its row
+    const int vrow = 8 * wave + (lane >> 3);
+    const int vo = vrow * np * 2 + ((lane & 7) ^ ((vrow >> 1) & 7)) * 16;
+    auto issue = [&](int c) __attribute__((always_inline)) {
+      char *buf = lds + (c % kRing) * CHUNK + wave * 1024;
+      // past the last chunk: zeros into the ring, so that every step adds two loads
+      const int v = c < nchunks ? vo : 0x7ff00000;
+      const int so = c < nchunks ? c * BK * 2 : 0;
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    const int64_t col = i0 + wave * NT * 32 + nt * 32 + (lane & 31);
-    if (col >= jb.k_hi) continue;
-    const int64_t ro = (col - jb.out_lo) * (int64_t)ldo + jb.col0;
+      for (int j = 0; j < 2; ++j)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_ptr *)(buf + j * 4096), 16, v, so + (c < nchunks ? 64 * np * j : 0),
+                                                 0, 0);
+    };
+    f32x16 acc[1][NT];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+    for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int rb = (int)r0 + mt * 32 + 8 * g + 4 * (lane >> 5);
-        if (rb + 4 <= col_limit) {
-          if (jb.out_cm && jb.out_f32) {
-            float *o = (float *)jb.out + (col - jb.out_lo);
+      for (int e = 0; e < 16; ++e) acc[0][nt][e] = 0.f;
+    const int lr = (lane & 31) % 8;
+    const T *bl = Bc + lr * WC + (wn * NT * 32 + (lane & 31) + (lane >> 5) * 8 - lr);
+    const int fr = wm * 32 + (lane & 31), fq = lane >> 5, fs = (fr >> 1) & 7;
+    const bool live = i0 + wn * NT * 32 < jb.k_hi;   // a wave past a ragged end loads and syncs only
+    const int t0 = threadIdx.x * 8;
+    const int64_t xw = i0 + jb.base - jb.x_lo + t0;
+    float xv[15];
+    if (t0 < WC) fir_window_read<15>(rx, xw, x_len, xv);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) o[(int64_t)(rb + q) * ldo] = acc[mt][nt][4 * g + q];
-          } else if (jb.out_cm) {
-            T *o = (T *)jb.out + (col - jb.out_lo);
+    for (int c = 0; c < kRing - 1; ++c) issue(c);
+    vec hw[2][NT];
+    for (int c = 0; c < nchunks; ++c) {
+      const int kc = c * BK, kw = kc % kFirKSup;
+      if (kw == 0) {
+        if (c > 0) __syncthreads();   // the window's last reads are done
+        if (t0 < WC) fir_window_write<T, WC>(Bc + t0, xv);
+      }
+      // this wave's part of chunk c is in (vmcnt) and its LDS accesses are done
+      // (lgkmcnt); then every wave's, and chunk c - 1's buffer is free.  Not
+      // __syncthreads, which would wait for the whole ring.
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_waitcnt(0x0070 | (2 * (kRing - 2)));
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      issue(c + kRing - 1);
+      if (kw + BK == kFirKSup && c + 1 < nchunks && t0 < WC) fir_window_read<15>(rx, xw + kc + BK, x_len, xv);
+      if (!live) continue;
+      const char *at = lds + (c % kRing) * CHUNK + fr * 128;
+      auto F = [&](int j) __attribute__((always_inline)) { return *(const vec *)(bl + j * 16); };
+      if (kw == 0) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) o[(int64_t)(rb + q) * ldo] = O::cvt(acc[mt][nt][4 * g + q]);
-          } else if (jb.out_f32) {
-            float *o = (float *)jb.out + ro + rb;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) o[q] = acc[mt][nt][4 * g + q];
-          } else {
-            T *o = (T *)jb.out + ro + rb;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) o[q] = O::cvt(acc[mt][nt][4 * g + q]);
-          }
+        for (int nt = 0; nt < NT; ++nt) {
+          hw[0][nt] = F(2 * nt);
+          hw[1][nt] = F(1 + 2 * nt);
         }
       }
+      // the chunk's fragments are all read before its products (one LDS latency
+      // per chunk, not per k-step)
+      vec af[BK / 16], nx[BK / 16];
+#pragma unroll
+      for (int ks = 0; ks < BK / 16; ++ks) {
+        af[ks] = *(const vec *)(at + ((2 * ks + fq) ^ fs) * 16);
+        nx[ks] = F(kw / 16 + ks + 2 * NT);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      auto kstep = [&](int ks) __attribute__((always_inline)) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[0][nt] = O::mfma(af[ks], hw[ks & 1][nt], acc[0][nt]);
+        hw[ks & 1][0] = hw[ks & 1][1];
+        hw[ks & 1][1] = nx[ks];
+      };
+      kstep(0);
+      kstep(1);
+      if (kc + 32 < np) {   // np is a multiple of 32: the last chunk may hold half
+        kstep(2);
+        kstep(3);
+      }
+    }
+    __builtin_amdgcn_s_waitcnt(0x0f70);   // the zeros past the last chunk have landed
+    fir_store<T, 1, NT>(jb, acc, (int)r0 + wm * 32, i0 + wn * NT * 32);
   }
+};
+
+// A launch of one tile shape, or (narrow jobs) of two: the same threads, the
+// narrow tile's 64 rows x 128 columns.
+constexpr int kFirNarrowBM = 64, kFirNarrowBN = 128;
+template <typename T> struct FirNarrow { typedef FirNarrow16<T> tile; };
+template <> struct FirNarrow<float> { typedef FirTile<float, 1, 1, 2, 4, kBK, false> tile; };   // waves of 32 x 32
+
+template <typename T, int MT, int NT, int NW, int BK, bool HR, bool NARROW>
+__global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void k_fir(const FirJob *__restrict__ jobs, int n_jobs) {
+  typedef FirTile<T, MT, NT, 1, NW, BK, HR> Wide;
+  typedef typename FirNarrow<T>::tile Narrow;
+  static_assert(!NARROW || (Narrow::THREADS == Wide::THREADS && Narrow::BM == kFirNarrowBM && Narrow::BN == kFirNarrowBN),
+                "one launch of both shapes");
+  __shared__ __attribute__((aligned(1024))) char lds[NARROW && Narrow::LDS > Wide::LDS ? Narrow::LDS : Wide::LDS];
+  const FirJob &jb = jobs[find_job(jobs, n_jobs, blockIdx.x)];
+  const int64_t li = (int64_t)blockIdx.x - jb.item0;
+  if constexpr (NARROW) {
+    if (jb.narrow) return Narrow::run(jb, li, lds);
+  }
+  Wide::run(jb, li, lds);
 }
 
 // ----------------------------------------------------- interpolation on MFMA
@@ -2300,9 +2468,9 @@ hipError_t launch_decimate(DecimArgs a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <typename T, int MT, int NT, int NW, int BK, bool HR = false>
+template <typename T, int MT, int NT, int NW, int BK, bool HR = false, bool NARROW = false>
 static hipError_t fir_v(const FirJob *jobs, int n_jobs, int64_t n_items, hipStream_t s) {
-  k_fir<T, MT, NT, NW, BK, HR><<<(unsigned)n_items, 64 * NW, 0, s>>>(jobs, n_jobs);
+  k_fir<T, MT, NT, NW, BK, HR, NARROW><<<(unsigned)n_items, 64 * NW, 0, s>>>(jobs, n_jobs);
   return hipGetLastError();
 }
 
@@ -2332,8 +2500,8 @@ static hipError_t fir_t(int variant, const FirJob *jobs, int n_jobs, int64_t n_i
       // 16-bit operands: the Hankel fragment window in four-wave 64 x 512
       // tiles, two workgroups per CU (one's strain-window fill and stores run
       // while the other's MFMAs do), basis chunks of 128 taps
-      if constexpr (sizeof(T) == 2) return fir_v<T, 2, 4, 4, 4 * kBK, true>(jobs, n_jobs, n_items, s);
-      else return fir_v<T, kFirMT, kFirNT, kFirWaves, kBK>(jobs, n_jobs, n_items, s);
+      if constexpr (sizeof(T) == 2) return fir_v<T, 2, 4, 4, 4 * kBK, true, true>(jobs, n_jobs, n_items, s);
+      else return fir_v<T, kFirMT, kFirNT, kFirWaves, kBK, false, true>(jobs, n_jobs, n_items, s);
   }
 }
 
@@ -2342,6 +2510,11 @@ void fir_tile_shape(lloid_dtype t, int variant, int *bm, int *bn) {
   *bn = kFirWaves * 32 * kFirNT;
   if ((variant == 2 || variant == 3 || variant == 4) && t != LLOID_F32) *bm = 32 * 2, *bn = kFirWaves * 32 * 4;
   if (variant == 0 && t != LLOID_F32) *bm = 32 * 2, *bn = 4 * 32 * 4;
+}
+
+void fir_narrow_shape(int variant, int *bm, int *bn) {
+  *bm = variant == 0 ? kFirNarrowBM : 0;
+  *bn = variant == 0 ? kFirNarrowBN : 0;
 }
 
 void mix_tile_shape(lloid_dtype, int variant, int *bm, int *bn) {

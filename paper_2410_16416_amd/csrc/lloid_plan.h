@@ -128,6 +128,14 @@ int64_t ready_until(const ReadyState &st);
 constexpr double kMixOverhead = 0.75;
 int mix_parts(int64_t tiles, int64_t steps, int64_t slots);
 
+// Whether a FIR job of `taps` takes narrow tiles (a quarter of the columns)
+// in a launch whose jobs need `work` = sum over jobs of wide tiles x taps, on
+// `n_cu` CUs: where a wide tile, on a CU shared by two, lasts longer than the
+// launch would with its work spread evenly, so that the longest tiles and not
+// the work decide.  A narrow tile reads its fragments from LDS more often per
+// product, so a full chip keeps the wide ones.
+inline bool fir_narrow(int64_t taps, int64_t work, int64_t n_cu) { return 2 * taps * n_cu > work; }
+
 // BF16 (8-bit significand) pair of a finite FP32 value, as bit patterns:
 // hi = x rounded to nearest (ties to even), lo = (x - hi) rounded likewise,
 // so that hi + lo carries 16 significant bits of x (the interpolation

@@ -146,3 +146,34 @@ def test_split_windows(compute, tail, seconds, win):
     for r in same:
         assert np.array_equal(r.peak_snr, res.peak_snr) and np.array_equal(r.peak_sample, res.peak_sample)
         assert np.array_equal(r.triggers, res.triggers)
+
+
+# ------------------------------------------------- narrow FIR tiles
+
+@pytest.mark.parametrize("compute", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("taps", [1, 31, 33, 64, 96, 1023, 1024, 1025, 1088, 2080])
+def test_narrow_fir_tiles(compute, taps):
+    """Short blocks, whose FIR takes narrow tiles: filters around a chunk (64
+    taps), its half and the strain window (1024 taps), basis counts around a
+    row tile, columns past a ragged end.  Peaks against the oracle (one filter
+    per slice rate), and bit for bit those of every other FIR tile shape, which
+    has wide tiles only."""
+    from paper_2410_16416_amd import lloid
+    f0 = 1024
+    l0, l1 = min(taps, 70), min(taps, 130)
+    bank = configs.random_basis_bank(70, [SliceSpec(f0, 0, taps, l0), SliceSpec(f0 // 4, 4 * taps, taps, l1)], f0,
+                                     np.random.default_rng(70 + taps))
+    x = np.random.default_rng(71 + taps).standard_normal(2 * f0 + 129)
+    _, want, _, _ = oracle.peak_table(oracle.lloid_snr(bank, x), 0, f0, 1, 2)
+    b = lloid.bank_from_svd(ctx(), bank, compute)
+    try:
+        res = lloid.lloid_filter(b, 0, x, window=(1, 2), peaks=True, threshold=2.5)
+        assert np.max(np.abs(res.peak_snr - want)) < EPS_ABS[compute]
+        for v in range(1, lloid.FIR_VARIANTS):
+            lloid.lloid_ctx_set_tiles(ctx(), v, 0)
+            r = lloid.lloid_filter(b, 0, x, window=(1, 2), peaks=True, threshold=2.5)
+            assert np.array_equal(r.peak_snr, res.peak_snr) and np.array_equal(r.peak_sample, res.peak_sample)
+            assert np.array_equal(r.triggers, res.triggers)
+    finally:
+        lloid.lloid_ctx_set_tiles(ctx(), 0, 0)
+        lloid.lloid_bank_destroy(b)
