@@ -12,15 +12,19 @@ import os
 import shutil
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "liblloid.so")
-SOURCES = ["lloid_kernels.hip", "lloid_host.cpp", "lloid_stream.cpp", "lloid_plan.cpp"]
+SOURCES = ["lloid_kernels.hip", "lloid_mix.hip", "lloid_host.cpp", "lloid_stream.cpp", "lloid_plan.cpp"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+# the register-held mixing kernel needs the MFMA results in vector registers
+# (the accumulation registers hold its other operand)
+SOURCE_FLAGS = {"lloid_mix.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -34,19 +38,24 @@ def build(verbose: bool = True) -> str:
     objdir = os.path.join(PKG, "_build")
     os.makedirs(objdir, exist_ok=True)
     objs = []
-    for src in SOURCES:
+
+    def compile_one(src: str):
         obj = os.path.join(objdir, os.path.splitext(src)[0] + ".o")
-        cmd = [HIPCC, *FLAGS, "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
-        if verbose:
-            print(" ".join(cmd), flush=True)
+        cmd = [HIPCC, *FLAGS, *SOURCE_FLAGS.get(src, []), "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
         r = subprocess.run(cmd, capture_output=True, text=True)
         out = "\n".join(line for line in (r.stdout + r.stderr).splitlines()
                         if "packed-fp32-ops' is not a recognized feature" not in line)
-        if r.returncode != 0:
-            raise RuntimeError(f"hipcc failed on {src}:\n{out}")
-        if out.strip() and verbose:
-            print(out, flush=True)
-        objs.append(obj)
+        return src, obj, cmd, r.returncode, out
+
+    with ThreadPoolExecutor(max_workers=len(SOURCES)) as pool:   # one hipcc per source at a time
+        for src, obj, cmd, rc, out in pool.map(compile_one, SOURCES):
+            if verbose:
+                print(" ".join(cmd), flush=True)
+            if rc != 0:
+                raise RuntimeError(f"hipcc failed on {src}:\n{out}")
+            if out.strip() and verbose:
+                print(out, flush=True)
+            objs.append(obj)
     tmp = LIB + ".tmp"
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp]
     if verbose:

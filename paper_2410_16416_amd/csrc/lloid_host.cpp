@@ -621,8 +621,8 @@ void lloid::add_bank_jobs(const lloid_bank *b, const LevelView *lv, int64_t t0, 
   mj.push_back(m);
 }
 
-void lloid::number_jobs(std::vector<FirJob> &fj, std::vector<UpJob> *uj, std::vector<MixJob> &mj, int64_t win_len,
-                        const TileShapes &ts, int n_cu, StageItems &n) {
+void lloid::number_jobs(lloid_dtype ct, std::vector<FirJob> &fj, std::vector<UpJob> *uj, std::vector<MixJob> &mj,
+                        int64_t win_len, const TileShapes &ts, int n_cu, StageItems &n) {
   if (ts.nbn) {
     int64_t work = 0;
     for (const auto &j : fj) work += (int64_t)j.n_rtiles * j.n_ctiles * j.np;
@@ -647,17 +647,42 @@ void lloid::number_jobs(std::vector<FirJob> &fj, std::vector<UpJob> *uj, std::ve
     n.up[h] = it;
   }
   it = 0;
-  int64_t e = 0, tiles = 0;
-  for (const auto &m : mj) tiles += m.nw * m.n_rtiles;
-  // every compiled mixing tile takes a CU to itself (LDS or registers)
-  n.mix_parts = mix_parts(tiles, ceil_div(win_len, ts.mbn), n_cu);
+  int64_t e = 0, rows = 0, windows = 0, reg_rows = 0, reg_total = 0;   // (windows: the same for every job)
+  const int64_t tpw = ceil_div(win_len, kMixRegTile);
+  auto reg = [&](const MixJob &m) { return mix_reg_job(ct, ts.mix_variant, m); };
+  for (auto &m : mj)
+    if (reg(m)) {
+      // (jobs are sorted by kcat: these are the last ones)
+      m.n_rtiles = (int)ceil_div(m.rows, kMixRegRows);
+      reg_rows += m.n_rtiles;
+      reg_total = std::max(reg_total, m.nw * tpw);
+      ++n.n_mix_reg;
+    } else {
+      rows += m.n_rtiles;
+      windows = std::max(windows, m.nw);
+    }
+  // every mixing workgroup takes a CU to itself (LDS or registers)
+  n.mix_parts = mix_parts(windows, rows, ceil_div(win_len, ts.mbn), n_cu);
+  n.mix_run = (int)mix_reg_run(reg_total, reg_rows, n_cu);
+  int64_t reg_items = 0;
   for (auto &m : mj) {
-    m.item0 = it;
-    m.parts = n.mix_parts;
-    // (window, part) units in runs of 8 (one per XCD) per row tile; fewer than
-    // 8 units run unit-major over the row tiles, padded to a multiple of 8
-    const int64_t units = m.nw * m.parts;
-    it += units >= 8 ? ceil_div(units, 8) * 8 * m.n_rtiles : round_up(units * m.n_rtiles, 8);
+    // units (a window's part, or a run of tiles) in runs of 8 (one per XCD) per
+    // row tile; fewer than 8 run unit-major over the row tiles, padded to a multiple of 8
+    auto number = [&](int64_t units, int64_t &next) {
+      m.item0 = next;
+      next += units >= 8 ? ceil_div(units, 8) * 8 * m.n_rtiles : round_up(units * m.n_rtiles, 8);
+    };
+    if (reg(m)) {
+      m.tpw = (int)tpw;
+      m.run = n.mix_run;
+      // a run that does not hold whole windows shares them with its neighbours
+      m.parts = m.run % tpw ? 2 : 1;
+      number(ceil_div(m.nw * tpw, m.run), reg_items);
+    } else {
+      m.parts = n.mix_parts;
+      number(m.nw * m.parts, it);
+    }
+    n.split = n.split || m.parts > 1;
     m.e0 = e;
     e += (int64_t)m.n_templates * m.nw;
     m.x0 = n.windows;
@@ -670,6 +695,7 @@ void lloid::number_jobs(std::vector<FirJob> &fj, std::vector<UpJob> *uj, std::ve
     }
   }
   n.mix = it;
+  n.mix_reg = reg_items;
   n.entries = e;
 }
 
@@ -688,7 +714,9 @@ lloid_status lloid::launch_stages(lloid_ctx *ctx, lloid_dtype ct, const char *dt
     HIP_TRY(launch_up_jobs(ct, (const UpJob *)(dtab + to.up[h]), to.n_up[h], n.up[h], st));
   HIP_TRY(mark(LLOID_STAGE_INTERP, 1));
   HIP_TRY(mark(LLOID_STAGE_MIX, 0));
-  HIP_TRY(launch_mix_jobs(ct, ctx->mix_variant, (const MixJob *)(dtab + to.mix), to.n_mix, n.mix, with_snr, st));
+  const MixJob *mix = (const MixJob *)(dtab + to.mix);
+  HIP_TRY(launch_mix_jobs(ct, ctx->mix_variant, mix, to.n_mix - n.n_mix_reg, n.mix, with_snr, st));
+  HIP_TRY(launch_mix_reg(ct, mix + (to.n_mix - n.n_mix_reg), n.n_mix_reg, n.mix_reg, st));
   HIP_TRY(mark(LLOID_STAGE_MIX, 1));
   HIP_TRY(mark(LLOID_STAGE_PHASE, 0));
   HIP_TRY(launch_peak_phase(ct, (const MixJob *)(dtab + to.mix), to.n_mix, n.entries, phase_thr,
@@ -958,8 +986,8 @@ static lloid_status filter_banks(lloid_bank *const *banks, int nb, int32_t detec
     for (int i = 0; i < nb; ++i)
       add_bank_jobs(banks[i], lv.data(), t0, t1, n, wa, wb, win, bw[i], 1.f / (banks[i]->mix_scale * sscale),
                     (snr && i == 0) ? dsnr + t0 * 2 : nullptr, n, ts, fj, uj, mj);
-    number_jobs(fj, uj, mj, win_len, ts, ctx->n_cu, chunks[c].items);
-    split = split || chunks[c].items.mix_parts > 1;
+    number_jobs(ct, fj, uj, mj, win_len, ts, ctx->n_cu, chunks[c].items);
+    split = split || chunks[c].items.split;
     TabOffsets &to = chunks[c].to;
     to.fir = put(fj.data(), fj.size() * sizeof(FirJob));
     for (int h = 0; h < kMaxHops; ++h) {

@@ -97,6 +97,7 @@ struct MixJob {
   float inv_scale;
   int rows, kcat, n_templates, n_rtiles, acorr_half;
   int kld;                    // row pitch of mix and ocat (kcat rounded up to 64)
+  int tpw, run;               // register-held form: 32-sample tiles per window, tiles per workgroup
   int parts;                  // workgroups that share a window's column steps (peak keys of more than
                               // one are combined in place: the table starts at zero)
 };
@@ -249,6 +250,13 @@ hipError_t launch_fir_jobs(lloid_dtype t, int variant, const FirJob *jobs, int n
 hipError_t launch_up_jobs(lloid_dtype t, const UpJob *jobs, int n_jobs, int64_t n_items, hipStream_t s);
 // Work items of an interpolation job: four 32-channel x kUpCols-sample wave tasks each.
 // Mixing and window peaks; then the phase at peaks with |z| >= phase_thr (0 for the others).
+// The jobs for which mix_reg_job holds come last in the table and are launched
+// by launch_mix_reg, their items numbered from 0.
+inline bool mix_reg_job(lloid_dtype t, int variant, const MixJob &m) {
+  return t != LLOID_F32 && variant == 0 && m.kcat <= 512 && !m.snr;
+}
+constexpr int kMixRegRows = 256, kMixRegTile = 32;   // mixing rows of a workgroup, samples of an operand tile
+hipError_t launch_mix_reg(lloid_dtype t, const MixJob *jobs, int n_jobs, int64_t n_items, hipStream_t s);
 hipError_t launch_mix_jobs(lloid_dtype t, int variant, const MixJob *jobs, int n_jobs, int64_t n_items,
                            bool with_snr, hipStream_t s);
 // White noise of unit variance (a counter-based hash of the sample index and
@@ -375,8 +383,8 @@ struct BankBufs {
 };
 
 struct TileShapes {
-  int fbm, fbn, nbm, nbn, mbm, mbn;
-  TileShapes(lloid_dtype t, int fir_variant, int mix_variant) {
+  int fbm, fbn, nbm, nbn, mbm, mbn, mix_variant;
+  TileShapes(lloid_dtype t, int fir_variant, int mix_variant_) : mix_variant(mix_variant_) {
     fir_tile_shape(t, fir_variant, &fbm, &fbn);
     fir_narrow_shape(fir_variant, &nbm, &nbn);
     mix_tile_shape(t, mix_variant, &mbm, &mbn);
@@ -391,7 +399,11 @@ struct StageItems {
   int xi_kmax = 0;                 // largest kcat of such a job
   int64_t xi_acorr = 0;            // largest autocorrelation table of such a job (entries)
   int64_t xi_units = 0;            // signal-consistency units those jobs can list at most
+  int64_t mix_reg = 0;             // items of the register-held mixing launch
+  int n_mix_reg = 0;               // its jobs: the last ones of the table
   int mix_parts = 1;               // workgroups per window of a row tile in the mixing launch
+  int mix_run = 0;                 // tiles per workgroup of the register-held launch
+  bool split = false;              // peaks of some windows are combined from several workgroups
   int64_t up[kMaxHops] = {};       // items of each interpolation hop
 };
 
@@ -427,8 +439,8 @@ void add_bank_jobs(const lloid_bank *b, const LevelView *lv, int64_t t0, int64_t
                    std::vector<MixJob> &mj);
 // Choose the FIR jobs' tile width and the mixing launch's parts per window
 // (win_len: samples of a window), sort longest-first and number the work items.
-void number_jobs(std::vector<FirJob> &fj, std::vector<UpJob> *uj, std::vector<MixJob> &mj, int64_t win_len,
-                 const TileShapes &ts, int n_cu, StageItems &n);
+void number_jobs(lloid_dtype ct, std::vector<FirJob> &fj, std::vector<UpJob> *uj, std::vector<MixJob> &mj,
+                 int64_t win_len, const TileShapes &ts, int n_cu, StageItems &n);
 // FIR, interpolation, mixing and phase launches over uploaded tables; ev:
 // NULL, or 8 events bracketing those four stages.
 constexpr int kChunkStages = 4;    // LLOID_STAGE_FIR .. LLOID_STAGE_PHASE

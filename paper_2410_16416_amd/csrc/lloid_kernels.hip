@@ -16,62 +16,10 @@
 #include <climits>
 #include <cstdlib>
 
+#include "lloid_device.h"
 #include "lloid_internal.h"
 
 namespace lloid {
-
-typedef _Float16 half8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-
-// ---------------------------------------------------------------- MFMA ops
-// Operand type T: K per instruction (KS), elements per lane per operand (VEC).
-// Lane l of a 32x32xKS instruction supplies row/column l % 32 and the VEC
-// consecutive k values starting at (l / 32) * VEC; the 32x32 FP32 result puts
-// rows 8 (r/4) + 4 (l/32) + r%4, r = 0..15, of column l % 32 in lane l.
-template <typename T> struct Op;
-
-template <> struct Op<_Float16> {
-  static constexpr int KS = 16, VEC = 8;
-  typedef half8 vec;
-  static __device__ __forceinline__ f32x16 mfma(vec a, vec b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
-  }
-  static __device__ __forceinline__ _Float16 cvt(float v) { return (_Float16)v; }
-  static __device__ __forceinline__ float tof(_Float16 v) { return (float)v; }
-};
-
-template <> struct Op<__bf16> {
-  static constexpr int KS = 16, VEC = 8;
-  typedef bf16x8 vec;
-  static __device__ __forceinline__ f32x16 mfma(vec a, vec b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-  }
-  static __device__ __forceinline__ __bf16 cvt(float v) { return (__bf16)v; }
-  static __device__ __forceinline__ float tof(__bf16 v) { return (float)v; }
-};
-
-template <> struct Op<float> {
-  static constexpr int KS = 2, VEC = 1;
-  typedef float vec;
-  static __device__ __forceinline__ f32x16 mfma(vec a, vec b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-  }
-  static __device__ __forceinline__ float cvt(float v) { return v; }
-  static __device__ __forceinline__ float tof(float v) { return v; }
-};
-
-// Job owning flat work item `item`: the last job with item0 <= item.
-template <typename J>
-__device__ __forceinline__ int find_job(const J *__restrict__ jobs, int n_jobs, int64_t item) {
-  int lo = 0, hi = n_jobs - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (jobs[mid].item0 <= item) lo = mid;
-    else hi = mid - 1;
-  }
-  return lo;
-}
 
 // ---------------------------------------------------------- small kernels
 
@@ -192,13 +140,6 @@ template <typename T, int BK = kBK> struct Pitch {
   // words, so one extra word per row does the same
   static constexpr int value = sizeof(T) == 4 ? BK + 1 : BK + 16 / (int)sizeof(T);
 };
-
-// Buffer resource over `bytes` bytes from `base`: loads past the end (or at
-// negative offsets, which wrap to huge unsigned ones) return zero in hardware.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *base, int64_t bytes) {
-  const int nb = bytes <= 0 ? 0 : (bytes > 0x7ffffff0 ? 0x7ffffff0 : (int)bytes);
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, nb, 0x00020000);
-}
 
 // Register-staged copy of a [ROWS][BK] chunk of a row-major matrix through a
 // buffer resource: setup() fixes each thread's byte offsets, load(k0) issues
@@ -811,11 +752,6 @@ __device__ __forceinline__ bool better(float va, int na, float vb, int nb) {
   return va > vb || (va == vb && na < nb);
 }
 
-struct VN {
-  float v;
-  int n;
-};
-
 // Row tile, window (within the job) and part of the window of workgroup b of
 // a job.  A window's column steps are shared by jb.parts workgroups, each a
 // run of them.  XCD-aware order: the 8 XCDs take workgroups round-robin
@@ -843,26 +779,6 @@ __device__ __forceinline__ MixUnit mix_unit(const MixJob &jb, int64_t b) {
   m.wl = u / jb.parts;
   m.part = (int)(u - m.wl * jb.parts);
   return m;
-}
-
-// A window peak as one ordered word: |z|^2 (its bits order as integers, it is
-// not negative), then the complement of the sample (relative to the window's
-// start), so that the largest word is the largest |z|^2 at its lowest
-// sample.  0: no sample compared greater than the initial -1.
-__device__ __forceinline__ uint64_t peak_key(VN p) {
-  return p.v < 0.f ? 0 : ((uint64_t)__float_as_uint(p.v) << 32) | (uint32_t)~p.n;
-}
-
-__device__ __forceinline__ VN peak_of_key(uint64_t k) {
-  return k ? VN{__uint_as_float((uint32_t)(k >> 32)), (int)~(uint32_t)k} : VN{-1.f, 0x7fffffff};
-}
-
-// A workgroup's peak of template i in window w: stored, or combined with the
-// other parts' (an integer maximum, so the order does not matter).
-__device__ __forceinline__ void put_peak(const MixJob &jb, int64_t i, int64_t w, VN p) {
-  uint64_t *k = (uint64_t *)jb.peak_n + (i * jb.ld_peak + (w - jb.w_base));
-  if (jb.parts == 1) *k = peak_key(p);
-  else if (p.v >= 0.f) atomicMax((unsigned long long *)k, (unsigned long long)peak_key(p));
 }
 
 template <typename T, int MT, int NT, int WM, int WN, int BK, bool SNR>
@@ -1316,7 +1232,7 @@ __global__ __launch_bounds__(256) void k_peak_phase(const MixJob *__restrict__ j
     pn = (w * jb.win_p) / jb.win_q + pk.n;
     jb.peak_snr[o] = snr;
     jb.peak_n[o] = pn;
-    hit = snr >= thr;
+    hit = snr >= thr && pk.v >= 0.f;   // (a window of NaNs only has no peak sample)
     if (snr >= trig_thr) blk = (jb.t0 + o) / kTrigPerBlock;
     if (!hit) {
       jb.peak_phase[o] = 0.f;
@@ -2568,7 +2484,10 @@ static hipError_t mix_t(int variant, const MixJob *jobs, int n_jobs, int64_t n_i
       if constexpr (sizeof(T) == 2) return mix_v<T, kMixMT, kMixNT, kMixWM, kMixWN, 64>(jobs, n_jobs, n_items, with_snr, s);
       else return mix_v<T, kMixMT, kMixNT, kMixWM, kMixWN, 32>(jobs, n_jobs, n_items, with_snr, s);
     default:
-      // 16-bit operands: direct-to-LDS K chunks of 64, eight 64 x 128 waves
+      // 16-bit operands: direct-to-LDS K chunks of 64, eight 64 x 128 waves.  Takes
+      // the SNR series (485 us with it against 535 for the register-held form, 48 s
+      // of 1024 templates) and a concatenated K above 512, whose mixing fragments
+      // no longer fit the registers; the rest is launch_mix_reg's.
       if constexpr (sizeof(T) == 2) {
         if (with_snr) k_mix_dl<T, 4, 2, 2, 4, 64, 1, true><<<(unsigned)n_items, 512, 0, s>>>(jobs, n_jobs);
         else k_mix_dl<T, 4, 2, 2, 4, 64, 1, false><<<(unsigned)n_items, 512, 0, s>>>(jobs, n_jobs);

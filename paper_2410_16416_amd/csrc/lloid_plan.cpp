@@ -123,16 +123,27 @@ int64_t ready_until(const ReadyState &st) {
   return best;
 }
 
-int mix_parts(int64_t tiles, int64_t steps, int64_t slots) {
-  if (tiles <= 0 || steps <= 1 || slots <= 0) return 1;
+int mix_parts(int64_t windows, int64_t row_tiles, int64_t steps, int64_t slots) {
+  if (windows <= 0 || row_tiles <= 0 || steps <= 1 || slots <= 0) return 1;
   auto time = [&](int64_t p) {
-    return (double)ceil_div(tiles * p, slots) * ((double)ceil_div(steps, p) + kMixOverhead);
+    return (double)mix_rounds(windows * p, row_tiles, slots) * ((double)ceil_div(steps, p) + kMixOverhead);
   };
   int64_t best = 1;
   double t = 0.96 * time(1);
   for (int64_t p = 2; p <= steps && p <= 64; ++p)
     if (time(p) < t) best = p, t = time(p);
   return (int)best;
+}
+
+int64_t mix_reg_run(int64_t total, int64_t row_tiles, int64_t slots) {
+  if (total <= 0 || row_tiles <= 0 || slots <= 0) return 1;
+  auto time = [&](int64_t run) {
+    return (double)mix_rounds(ceil_div(total, run), row_tiles, slots) * ((double)run + kMixRegOverhead);
+  };
+  int64_t best = std::min(total, kMixRegRun);
+  for (int64_t run = best - 1; run >= 1; --run)
+    if (time(run) < time(best)) best = run;
+  return best;
 }
 
 static uint16_t bf16_round(float f) {

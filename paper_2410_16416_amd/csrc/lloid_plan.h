@@ -116,17 +116,36 @@ struct ReadyState {
 };
 int64_t ready_until(const ReadyState &st);
 
+// Rounds that `units` units (windows, parts of them or runs of tiles) of
+// `row_tiles` row tiles (over all jobs) take on `slots` workgroup slots.  All
+// row tiles of a unit go to one of the 8 XCDs, units round-robin, so the XCD
+// with the most units decides; fewer than 8 units spread over all of them.
+inline int64_t mix_rounds(int64_t units, int64_t row_tiles, int64_t slots) {
+  if (units < 8 || slots < 8) return ceil_div(units * row_tiles, slots);
+  return ceil_div(ceil_div(units, 8) * row_tiles, slots / 8);
+}
+
 // Workgroups that share one window of one row tile in the mixing launch:
-// `tiles` (row tile, window) pairs of `steps` column steps each on `slots`
-// workgroup slots.  A launch takes ceil(tiles p / slots) rounds of ceil(steps
-// / p) steps and a workgroup costs about kMixOverhead of a step besides (the
-// first chunk's latency, the peaks' reduction).  The p with the smallest such
-// time, and 1 unless that gains more than 4 %.  Measured on 256 CUs, mixing
-// kernel, one workgroup per window against this rule: 72 tiles of 8 steps (an
-// 8 s block of 1024 templates) 98 -> 49 us, 384 tiles (48 s) in FP32 1880 ->
-// 1487 us and with the SNR series 331 -> 285 us; 8192 tiles (1024 s) stay whole.
+// `windows` windows of `steps` column steps each.  With p parts per window the
+// launch takes mix_rounds of ceil(steps / p) steps, and a workgroup costs about
+// kMixOverhead of a step besides (the first chunk's latency, the peaks'
+// reduction).  The p with the smallest such time, and 1 unless that gains more
+// than 4 %.  Measured on 256 CUs, one workgroup per window against this rule:
+// 72 tiles of 8 steps (an 8 s block of 1024 templates) 98 -> 49 us, 384 tiles
+// (48 s) in FP32 1880 -> 1487 us and with the SNR series 331 -> 285 us; 8192
+// tiles (1024 s) stay whole.
 constexpr double kMixOverhead = 0.75;
-int mix_parts(int64_t tiles, int64_t steps, int64_t slots);
+int mix_parts(int64_t windows, int64_t row_tiles, int64_t steps, int64_t slots);
+
+// Tiles per workgroup of the register-held mixing launch, whose windows hold
+// `total` tiles: the run length with the smallest mix_rounds of a run and
+// kMixRegOverhead tiles' time (the mixing rows' load, the first tiles'
+// latency), of at most kMixRegRun tiles.  341 templates, 40 s in 0.5 s windows,
+// 255 runs of 31 tiles: 33 on one XCD's 32 CUs, 102 us; 240 runs of 32, one
+// round: 57 us.
+constexpr int64_t kMixRegRun = 256;
+constexpr double kMixRegOverhead = 4.0;
+int64_t mix_reg_run(int64_t total, int64_t row_tiles, int64_t slots);
 
 // Whether a FIR job of `taps` takes narrow tiles (a quarter of the columns)
 // in a launch whose jobs need `work` = sum over jobs of wide tiles x taps, on

@@ -451,7 +451,7 @@ lloid_status enqueue_tick(lloid_stream *s, int64_t wa, int64_t wb, Clock::time_p
   xw.counters = cv.take<int32_t>(2);
   char *dtab = (char *)s->ws.base + tab_base + (size_t)ti * s->tab_area;
   StageItems items;
-  number_jobs(fj, uj, mj, s->win_len, ts, ctx->n_cu, items);
+  number_jobs(s->ct, fj, uj, mj, s->win_len, ts, ctx->n_cu, items);
   char *htab = (char *)tk.htab;
   size_t off = 0;
   auto put = [&](const void *src, size_t sz) -> size_t {
@@ -479,7 +479,7 @@ lloid_status enqueue_tick(lloid_stream *s, int64_t wa, int64_t wb, Clock::time_p
     in.tab_dst = dtab;
     in.tab_vecs = ceil_div((int64_t)off, 16);
     in.zero = counts;
-    in.zero_n = n_blk + (items.mix_parts > 1 ? rows * nw : 0);
+    in.zero_n = n_blk + (items.split ? rows * nw : 0);
     HIP_TRY(launch_ingest(in, LLOID_F32, st));
     const lloid_status r = launch_stages(ctx, s->ct, dtab, to, items, false, s->thr, s->thr, counts, xw, nullptr);
     if (r != LLOID_OK) return r;
@@ -501,6 +501,9 @@ lloid_status enqueue_tick(lloid_stream *s, int64_t wa, int64_t wb, Clock::time_p
     key.push_back(ctx->fir_variant * 16 + ctx->mix_variant);
     key.push_back(items.windows);
     key.push_back(items.mix_parts);
+    key.push_back(items.mix_reg);
+    key.push_back(items.n_mix_reg);
+    key.push_back(items.split ? 1 : 0);
     for (int h = 0; h < kMaxHops; ++h) {
       key.push_back(items.up[h]);
       key.push_back((int64_t)to.up[h]);

@@ -177,3 +177,57 @@ def test_narrow_fir_tiles(compute, taps):
     finally:
         lloid.lloid_ctx_set_tiles(ctx(), 0, 0)
         lloid.lloid_bank_destroy(b)
+
+
+# ------------------------------------------------- mixing rows held in registers
+
+@pytest.mark.parametrize("compute", ["f16", "bf16"])
+@pytest.mark.parametrize("k32", list(range(1, 18)))
+def test_register_held_mixing(compute, k32):
+    """Every compiled K (32 to 512; 544 takes the other kernel), one row tile and
+    several, windows of one operand tile, of many and shared between runs, a
+    ragged end: peaks against the oracle, and bit for bit those of the
+    register-staged tile shapes."""
+    from paper_2410_16416_amd import lloid
+    f0 = 1024
+    bank = configs.random_basis_bank(150 if k32 % 3 else 40, [SliceSpec(f0, 0, 600, 32 * k32 - 16 * (k32 % 2))], f0,
+                                     np.random.default_rng(80 + k32))
+    x = np.random.default_rng(81).standard_normal(5 * f0 + 77)
+    z = oracle.lloid_snr(bank, x)
+    b = lloid.bank_from_svd(ctx(), bank, compute)
+    try:
+        assert lloid.lloid_bank_query(b).concat_k == 32 * k32
+        for win in ((1, 1), (1, 32), (1, 10), (4, 3), (6, 1)):
+            _, want, _, _ = oracle.peak_table(z, 0, f0, *win)
+            lloid.lloid_ctx_set_tiles(ctx(), 0, 0)
+            res = lloid.lloid_filter(b, 0, x, window=win, peaks=True, threshold=2.5)
+            assert np.max(np.abs(res.peak_snr - want)) < EPS_ABS[compute]
+            lloid.lloid_ctx_set_tiles(ctx(), 0, 4)
+            r = lloid.lloid_filter(b, 0, x, window=win, peaks=True, threshold=2.5)
+            assert np.array_equal(r.peak_snr, res.peak_snr) and np.array_equal(r.peak_sample, res.peak_sample)
+            assert np.array_equal(r.triggers, res.triggers)
+    finally:
+        lloid.lloid_ctx_set_tiles(ctx(), 0, 0)
+        lloid.lloid_bank_destroy(b)
+
+
+@pytest.mark.parametrize("compute", ["f16", "bf16"])
+def test_mixing_forms_in_one_call(compute):
+    """Banks on both sides of the register-held form's K in one batched call."""
+    from paper_2410_16416_amd import lloid
+    f0 = 1024
+    banks = [configs.random_basis_bank(f, [SliceSpec(f0, 0, 700, l)], f0, np.random.default_rng(90 + l))
+             for f, l in ((30, 500), (200, 513), (140, 40), (20, 640), (129, 512))]
+    x = np.random.default_rng(91).standard_normal(3 * f0 + 5)
+    hs = [lloid.bank_from_svd(ctx(), b, compute) for b in banks]
+    try:
+        both = lloid.lloid_filter_batch(hs, 0, x, window=(1, 4), peaks=True)
+        for k, (h, b) in enumerate(zip(hs, banks)):
+            one = lloid.lloid_filter(h, 0, x, window=(1, 4), peaks=True)
+            _, want, _, _ = oracle.peak_table(oracle.lloid_snr(b, x), 0, f0, 1, 4)
+            assert np.max(np.abs(one.peak_snr - want)) < EPS_ABS[compute]
+            assert np.array_equal(both.peak_snr[k], one.peak_snr)
+            assert np.array_equal(both.peak_sample[k], one.peak_sample)
+    finally:
+        for h in hs:
+            lloid.lloid_bank_destroy(h)
