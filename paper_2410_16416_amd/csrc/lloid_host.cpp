@@ -523,6 +523,7 @@ void lloid::add_bank_jobs(const lloid_bank *b, const LevelView *lv, int64_t t0, 
   const size_t lsz = low_esz(b->compute);
   // BF16 interpolates FP32 buffers with split-BF16 products
   const int ti = b->compute == LLOID_F16 ? 1 : b->compute == LLOID_BF16 ? 2 : 0;
+  const size_t tm0 = uj[kMaxHops - 1].size();
   for (size_t s = 0; s < b->slices.size(); ++s) {
     const SliceDev &sl = b->slices[s];
     FirJob j{};
@@ -569,6 +570,7 @@ void lloid::add_bank_jobs(const lloid_bank *b, const LevelView *lv, int64_t t0, 
         q.n_ctiles = (int)ceil_div(p.out[h].hi - q.n_first, kUpCols);
         q.n_rtiles = (int)ceil_div(sl.lp, 32);
         if (h + 1 == H) {
+          q.n_rtiles = (int)ceil_div(sl.koff % 32 + sl.lp, 32);
           q.dst = bb.ocat;
           q.dst_abs0 = e0;
           q.ld_dst = b->kld;
@@ -580,12 +582,19 @@ void lloid::add_bank_jobs(const lloid_bank *b, const LevelView *lv, int64_t t0, 
           q.ld_dst = (int)ld[h + 1];
           q.dst_tm = 0;
         }
-        uj[h].push_back(q);
+        q.grp_rtiles = q.n_rtiles;
+        uj[kMaxHops - H + h].push_back(q);   // the last hops of all slices in one launch
       }
     }
     j.n_ctiles = (int)ceil_div(j.k_hi - j.k_lo, ts.fbn);
     fj.push_back(j);
   }
+  std::vector<UpJob> &tm = uj[kMaxHops - 1];
+  for (size_t k = tm0 + 1; k < tm.size(); ++k) {
+    tm[k].grp = (int)(k - tm0);
+    tm[k].rt0 = tm[k - 1].rt0 + tm[k - 1].n_rtiles;
+  }
+  for (size_t k = tm0; k < tm.size(); ++k) tm[k].grp_rtiles = tm.back().rt0 + tm.back().n_rtiles;
   MixJob m{};
   m.mix = b->mix;
   m.ocat = bb.ocat;
@@ -643,7 +652,12 @@ void lloid::number_jobs(lloid_dtype ct, std::vector<FirJob> &fj, std::vector<UpJ
   for (int h = 0; h < kMaxHops; ++h) {
     it = 0;
     // 8 runs (one per XCD) of ceil(tasks / 32) items of 4 tasks
-    for (auto &q : uj[h]) q.item0 = it, it += 8 * ceil_div((int64_t)q.n_rtiles * q.n_ctiles, 32);
+    for (size_t k = 0; k < uj[h].size(); ++k) {
+      UpJob &q = uj[h][k];
+      n.up_r[h] = k ? std::min(n.up_r[h], q.r) : q.r;
+      if (q.grp) q.item0 = uj[h][k - 1].item0;
+      else q.item0 = it, it += 8 * ceil_div((int64_t)q.grp_rtiles * q.n_ctiles, 32);
+    }
     n.up[h] = it;
   }
   it = 0;
@@ -711,7 +725,7 @@ lloid_status lloid::launch_stages(lloid_ctx *ctx, lloid_dtype ct, const char *dt
   HIP_TRY(mark(LLOID_STAGE_FIR, 1));
   HIP_TRY(mark(LLOID_STAGE_INTERP, 0));
   for (int h = 0; h < kMaxHops; ++h)
-    HIP_TRY(launch_up_jobs(ct, (const UpJob *)(dtab + to.up[h]), to.n_up[h], n.up[h], st));
+    HIP_TRY(launch_up_jobs(ct, (const UpJob *)(dtab + to.up[h]), to.n_up[h], n.up[h], n.up_r[h], st));
   HIP_TRY(mark(LLOID_STAGE_INTERP, 1));
   HIP_TRY(mark(LLOID_STAGE_MIX, 0));
   const MixJob *mix = (const MixJob *)(dtab + to.mix);

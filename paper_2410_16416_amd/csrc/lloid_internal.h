@@ -74,6 +74,10 @@ struct UpJob {
   int64_t src_lo, dst_abs0, n_lo, n_hi, n_first, item0;   // n_first: first tile start (multiple of 32)
   int64_t src_bytes;     // extent of src for the buffer resource
   int ld_src, ld_dst, col0, channels, r, dst_tm, n_ctiles, n_rtiles;
+  // The last hops of a bank's slices form a group (neighbours in the table, the
+  // same column tiles and item0): its tasks run over all their row tiles, so that
+  // a row of the operand is written at one time.  Other jobs are alone in theirs.
+  int grp, rt0, grp_rtiles;   // place in the group, row tiles before this job, row tiles of the group
 };
 
 // Mixing + peaks of one bank over trigger windows [w0, w0 + nw).
@@ -247,8 +251,10 @@ void mix_tile_shape(lloid_dtype t, int variant, int *bm, int *bn);
 // One launch per stage over a device descriptor table (see the job structs).
 hipError_t launch_fir_jobs(lloid_dtype t, int variant, const FirJob *jobs, int n_jobs, int64_t n_items,
                            hipStream_t s);
-hipError_t launch_up_jobs(lloid_dtype t, const UpJob *jobs, int n_jobs, int64_t n_items, hipStream_t s);
-// Work items of an interpolation job: four 32-channel x kUpCols-sample wave tasks each.
+// Work items of an interpolation launch: four wave tasks each, of kUpCols
+// samples and 32 channels (the last hops': 32 columns of the operand); r_min: the
+// smallest factor of its hops.
+hipError_t launch_up_jobs(lloid_dtype t, const UpJob *jobs, int n_jobs, int64_t n_items, int r_min, hipStream_t s);
 // Mixing and window peaks; then the phase at peaks with |z| >= phase_thr (0 for the others).
 // The jobs for which mix_reg_job holds come last in the table and are launched
 // by launch_mix_reg, their items numbered from 0.
@@ -404,7 +410,8 @@ struct StageItems {
   int mix_parts = 1;               // workgroups per window of a row tile in the mixing launch
   int mix_run = 0;                 // tiles per workgroup of the register-held launch
   bool split = false;              // peaks of some windows are combined from several workgroups
-  int64_t up[kMaxHops] = {};       // items of each interpolation hop
+  int64_t up[kMaxHops] = {};       // items of each interpolation launch
+  int up_r[kMaxHops] = {};         // smallest factor of its hops
 };
 
 struct TabOffsets {

@@ -558,42 +558,28 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void k_fir(const FirJob *
 // time-major mixing operand, computes D[t][c] with the operands swapped, so
 // each store instruction writes 32 consecutive channels of two samples.
 // TS: source and low-rate buffer type; TD: operand type of the last hop.
-// The fragment of tile t at k-step ks is the VEC-sample block 2 ks + SB t
-// past the lane's first one (the tiles' source windows start 32 / R = SB VEC
-// samples apart), so a lane reads each block of its source window that the
-// MFMAs use once, all reads issued before the MFMAs.  With SB even only the
+// What bounds it: long blocks the writes of the operand (1024 s of 1024
+// templates: 1.14 GB in 503 us, 2.3 TB/s; a large copy writes at 2.5), ones
+// that stay in the caches latency and the address units.  Each wave therefore
+// brings its 32 source rows' windows to LDS with coalesced direct loads (read
+// from memory as fragments, every lane's 16 bytes were a line of their own, and each
+// block was read twice: 59 against 82 us for FP32, 48 s), works tile by tile, so
+// that a tile's stores go out while the next is computed (few registers, five
+// waves per SIMD), writes 32-column blocks that start at the operand's own 32-column grid
+// with a dword per lane, without bounds checks inside, and the tasks run over
+// all slices' blocks of a column tile.  Before and after: FP32, 48 s 109 -> 59 us;
+// FP16, 48 s with the series 37 -> 22, 8 s 17 -> 13, 1024 s 630 -> 554; BF16, 200 s
+// 174 -> 131.  Tasks of 64 columns (whole lines per store): 1024 s 496, but 48 s 29
+// and 8 s 17 us.  Neither a row pitch of an odd number of lines nor
+// non-temporal stores changed the long blocks.
+//
+// A lane's source window: the fragment of tile t at k-step ks is the
+// VEC-sample block 2 ks + SB t past the lane's first one (the tiles' source
+// windows start 32 / R = SB VEC samples apart), so a lane reads each block that
+// the MFMAs use once, all reads issued before the MFMAs.  With SB even only the
 // even blocks are used.
-template <typename TS, bool TM, int SB>
-__device__ __forceinline__ void upsample_blocks(__amdgpu_buffer_rsrc_t rs, int64_t base0,
-                                                const typename Op<TS>::vec *hfr, f32x16 *acc) {
-  typedef Op<TS> O;
-  static_assert(O::KS == 2 * O::VEC, "two VEC blocks per k-step");
-  constexpr int NKS = 64 / O::KS, CT = kUpCols / 32;
-  constexpr int NB = 2 * (NKS - 1) + SB * (CT - 1) + 1;
-  typename O::vec blk[NB];
-#pragma unroll
-  for (int j = 0; j < NB; ++j) {
-    if (SB % 2 == 0 && (j & 1)) continue;
-    const int off = (int)((base0 + j * O::VEC) * (int64_t)sizeof(TS));
-    if constexpr (O::VEC == 8)
-      blk[j] = __builtin_bit_cast(typename O::vec, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
-    else
-      blk[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0));
-  }
-  __builtin_amdgcn_sched_barrier(0);   // keep every read ahead of the MFMAs
-#pragma unroll
-  for (int t = 0; t < CT; ++t) {
-#pragma unroll
-    for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) {
-      const typename O::vec a = blk[2 * ks + SB * t];
-      acc[t] = TM ? O::mfma(hfr[ks], a, acc[t]) : O::mfma(a, hfr[ks], acc[t]);
-    }
-  }
-}
-
-// FP32 sources of the BF16 operand path: every source value x and filter
+//
+// FP32 sources of the BF16 operand path (SPLIT): every source value x and filter
 // tap h is split into a BF16 pair, x = x_hi + x_lo with x_hi = bf16(x) and
 // x_lo = bf16(x - x_hi) (16 significant bits), and a product takes three
 // BF16 MFMAs, x_hi h_hi + x_lo h_hi + x_hi h_lo (the dropped x_lo h_lo and
@@ -601,143 +587,226 @@ __device__ __forceinline__ void upsample_blocks(__amdgpu_buffer_rsrc_t rs, int64
 // 32x32x16 instruction in place of eight FP32 32x32x2 ones per k-step.
 // Blocks are 8 source samples (two 16-byte reads), laid out as for 16-bit
 // sources; hf holds the filter's hi fragments, then its lo fragments.
+// 16-byte units of a source row's window of a wave task (64 samples for the
+// first tile, 32 / R more for each further one), odd for FP32 rows (LDS banks).
+template <typename TS> __host__ __device__ constexpr int up_units(int R) {
+  const int u = (64 + (kUpCols - 32) / R) * (int)sizeof(TS) / 16;
+  return sizeof(TS) == 4 ? u | 1 : u;
+}
+
+// LDS of a wave whose hops' factors are r_min or more, in whole 64-unit loads.
+template <typename TS> __host__ __device__ constexpr int up_wave_lds(int r_min) {
+  return (32 * up_units<TS>(r_min) + 63) / 64 * 1024;
+}
+
+template <typename TS, bool SPLIT> struct UpWindow {
+  typedef Op<TS> O;
+  typedef typename O::vec vec;
+  static_assert(O::KS == 2 * O::VEC, "two VEC blocks per k-step");
+  static constexpr int VEC = O::VEC, NKS = 64 / O::KS, SB4 = 8 / VEC;   // SB for R = 4; twice that for R = 2
+  static constexpr int NB = 2 * (NKS - 1) + 2 * SB4 * (kUpCols / 32 - 1) + 1;
+  vec blk[NB];
+
+  // row: the lane's row in LDS, at the lane's first block
+  template <int SB> __device__ __forceinline__ void read(const char *row) {
+#pragma unroll
+    for (int j = 0; j <= 2 * (NKS - 1) + SB * (kUpCols / 32 - 1); ++j) {
+      if (SB % 2 == 0 && (j & 1)) continue;
+      blk[j] = *(const vec *)(row + j * (int)sizeof(vec));
+    }
+  }
+  template <bool TM, int SB> __device__ __forceinline__ f32x16 tile(int t, const vec *hf, const vec *) const {
+    f32x16 acc = {};
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) {
+      const vec a = blk[2 * ks + SB * t];
+      acc = TM ? O::mfma(hf[ks], a, acc) : O::mfma(a, hf[ks], acc);
+    }
+    return acc;
+  }
+};
+
 struct uint4x2 {
   __attribute__((ext_vector_type(4))) unsigned int a, b;
 };
 
-template <bool TM, int SB>
-__device__ __forceinline__ void upsample_blocks_split(__amdgpu_buffer_rsrc_t rs, int64_t base0, const bf16x8 *hhi,
-                                                      const bf16x8 *hlo, f32x16 *acc) {
-  constexpr int NKS = 4, CT = kUpCols / 32;
-  constexpr int NB = 2 * (NKS - 1) + SB * (CT - 1) + 1;
+template <> struct UpWindow<float, true> {
+  typedef Op<__bf16> O;
+  typedef bf16x8 vec;
   typedef float f32x8 __attribute__((ext_vector_type(8)));
-  f32x8 raw[NB];
+  static constexpr int VEC = 8, NKS = 4, SB4 = 1;
+  static constexpr int NB = 2 * (NKS - 1) + 2 * SB4 * (kUpCols / 32 - 1) + 1;
+  vec hi[NB], lo[NB];
+
+  template <int SB> __device__ __forceinline__ void read(const char *row) {
 #pragma unroll
-  for (int j = 0; j < NB; ++j) {
-    if (SB % 2 == 0 && (j & 1)) continue;
-    const int off = (int)((base0 + j * 8) * (int64_t)sizeof(float));
-    const auto v0 = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
-    const auto v1 = __builtin_amdgcn_raw_buffer_load_b128(rs, off + 16, 0, 0);
-    raw[j] = __builtin_bit_cast(f32x8, (uint4x2{v0, v1}));
-  }
-  __builtin_amdgcn_sched_barrier(0);   // keep every read ahead of the MFMAs
-  bf16x8 xhi[NB], xlo[NB];
+    for (int j = 0; j <= 2 * (NKS - 1) + SB * (kUpCols / 32 - 1); ++j) {
+      if (SB % 2 == 0 && (j & 1)) continue;
+      const uint4x2 v = {*(const decltype(uint4x2::a) *)(row + j * 32), *(const decltype(uint4x2::a) *)(row + j * 32 + 16)};
+      const f32x8 x = __builtin_bit_cast(f32x8, v);
+      __bf16 h[8], l[8];
 #pragma unroll
-  for (int j = 0; j < NB; ++j) {
-    if (SB % 2 == 0 && (j & 1)) continue;
-    __bf16 h[8], l[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      h[e] = (__bf16)raw[j][e];
-      l[e] = (__bf16)(raw[j][e] - (float)h[e]);
+      for (int e = 0; e < 8; ++e) {
+        h[e] = (__bf16)x[e];
+        l[e] = (__bf16)(x[e] - (float)h[e]);
+      }
+      hi[j] = __builtin_bit_cast(vec, h);
+      lo[j] = __builtin_bit_cast(vec, l);
     }
-    xhi[j] = __builtin_bit_cast(bf16x8, h);
-    xlo[j] = __builtin_bit_cast(bf16x8, l);
   }
-#pragma unroll
-  for (int t = 0; t < CT; ++t) {
-#pragma unroll
-    for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
+  template <bool TM, int SB> __device__ __forceinline__ f32x16 tile(int t, const vec *hhi, const vec *hlo) const {
+    f32x16 acc = {};
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks) {
       const int j = 2 * ks + SB * t;
       if (TM) {
-        acc[t] = Op<__bf16>::mfma(hlo[ks], xhi[j], acc[t]);
-        acc[t] = Op<__bf16>::mfma(hhi[ks], xlo[j], acc[t]);
-        acc[t] = Op<__bf16>::mfma(hhi[ks], xhi[j], acc[t]);
+        acc = O::mfma(hlo[ks], hi[j], acc);
+        acc = O::mfma(hhi[ks], lo[j], acc);
+        acc = O::mfma(hhi[ks], hi[j], acc);
       } else {
-        acc[t] = Op<__bf16>::mfma(xhi[j], hlo[ks], acc[t]);
-        acc[t] = Op<__bf16>::mfma(xlo[j], hhi[ks], acc[t]);
-        acc[t] = Op<__bf16>::mfma(xhi[j], hhi[ks], acc[t]);
+        acc = O::mfma(hi[j], hlo[ks], acc);
+        acc = O::mfma(lo[j], hhi[ks], acc);
+        acc = O::mfma(hi[j], hhi[ks], acc);
       }
     }
+    return acc;
   }
-}
+};
 
-template <typename TS, typename TD, bool TM>
-__device__ __forceinline__ void upsample_task(const UpJob &jb, int lane, int r0, int64_t n0) {
-  typedef Op<TS> O;
-  constexpr int NKS = 64 / O::KS;  // k-steps over the 64 composite taps
-  constexpr int CT = kUpCols / 32; // 32-sample tiles per task
-  const int R = jb.r;
-  const int lgR = R == 4 ? 2 : 1;  // R is 2 or 4: shifts, not 64-bit divisions (their
-                                   // branches would keep the tiles' reads apart)
-  // FP32 sources feeding BF16 operands take the split-BF16 products
+// One wave task, 32 channels from r0, SB the window step of the hop's factor.
+// TM false: into a channel-major buffer.  TM true: the last hop, into a
+// 32-column block of the time-major operand (r0 below 0 where the block begins in
+// the slice before; rows outside the slice are not read).  A lane then holds
+// samples n0 + 32 t + 8 g + 4 (lane / 32) + q of its channel; with 16-bit operands
+// two samples of neighbouring channels change hands, so that it stores a dword
+// of two columns (two neighbours are both in or both out: offsets and counts of
+// channels are multiples of 16).
+template <typename TS, typename TD, bool TM, int SB>
+__device__ __forceinline__ void upsample_task(const UpJob &jb, char *lds, int lane, int r0, int64_t n0) {
   constexpr bool SPLIT = std::is_same<TS, float>::value && std::is_same<TD, __bf16>::value;
-  const int cR = 32 - 32 / R;
+  typedef UpWindow<TS, SPLIT> W;
+  typedef typename W::vec vec;
+  constexpr int CT = kUpCols / 32;
+  constexpr int R = SB == W::SB4 ? 4 : 2, cR = 32 - 32 / R;
   const __amdgpu_buffer_rsrc_t rs = make_rsrc(jb.src, jb.src_bytes);
-  const int64_t rowoff = (int64_t)(r0 + (lane & 31)) * jb.ld_src;
-  f32x16 acc[CT];
-  if constexpr (SPLIT) {
-    const __bf16 *hf = (const __bf16 *)jb.hf;
-    bf16x8 hhi[4], hlo[4];
+  vec hf[W::NKS], hlo[SPLIT ? W::NKS : 1];
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      hhi[ks] = *(const bf16x8 *)(hf + (ks * 64 + lane) * 8);
-      hlo[ks] = *(const bf16x8 *)(hf + kInterpFragEntries + (ks * 64 + lane) * 8);
-    }
-    const int64_t base0 = rowoff + (((n0 >> lgR) - cR) - jb.src_lo) + (lane >> 5) * 8;
-    if (R == 4) upsample_blocks_split<TM, 1>(rs, base0, hhi, hlo, acc);
-    else upsample_blocks_split<TM, 2>(rs, base0, hhi, hlo, acc);
-  } else {
-    const TS *hf = (const TS *)jb.hf;
-    typename O::vec hfr[NKS];
-#pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) hfr[ks] = *(const typename O::vec *)(hf + (ks * 64 + lane) * O::VEC);
-    const int64_t base0 = rowoff + (((n0 >> lgR) - cR) - jb.src_lo) + (lane >> 5) * O::VEC;
-    constexpr int SB4 = 8 / O::VEC;   // 32 / R in VEC blocks for R = 4; twice that for R = 2
-    if (R == 4) upsample_blocks<TS, TM, SB4>(rs, base0, hfr, acc);
-    else upsample_blocks<TS, TM, 2 * SB4>(rs, base0, hfr, acc);
+  for (int ks = 0; ks < W::NKS; ++ks) {
+    hf[ks] = *(const vec *)((const char *)jb.hf + (ks * 64 + lane) * sizeof(vec));
+    if constexpr (SPLIT) hlo[ks] = *(const vec *)((const __bf16 *)jb.hf + kInterpFragEntries + (ks * 64 + lane) * 8);
   }
+  const int c = r0 + (lane & 31);
+  const bool in = c >= 0 && c < jb.channels;
+  {
+    typedef __attribute__((address_space(3))) void lds_ptr;
+    constexpr int NU = up_units<TS>(R), LOADS = (32 * NU + 63) / 64;
+    const int64_t col = n0 / R - cR - jb.src_lo;
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) {
+      const int u = i * 64 + lane, row = u / NU, k = u - row * NU, ch = r0 + row;
+      const bool ok = row < 32 && ch >= 0 && ch < jb.channels;
+      const int off = ok ? (int)((ch * (int64_t)jb.ld_src + col) * (int64_t)sizeof(TS)) + k * 16 : -16;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr *)(lds + i * 1024), 16, off, 0, 0, 0);
+    }
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0f70);
+    asm volatile("" ::: "memory");
+  }
+  W w;
+  w.template read<SB>(lds + (lane & 31) * up_units<TS>(R) * 16 + (lane >> 5) * (int)(W::VEC * sizeof(TS)));
   if constexpr (TM) {
-    // lane holds channel r0 + lane % 32 at samples n0 + 32 t + 8 g + 4 (lane / 32) + q
-    const int c = r0 + (lane & 31);
-    if (c >= jb.channels) return;
-    TD *d = (TD *)jb.dst + jb.col0 + c;
-#pragma unroll
-    for (int t = 0; t < CT; ++t)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int64_t n = n0 + 32 * t + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
-        if (n >= jb.n_lo && n < jb.n_hi) d[(n - jb.dst_abs0) * jb.ld_dst] = Op<TD>::cvt(acc[t][e]);
+    const int ld = jb.ld_dst * (int)sizeof(TD);
+    const bool whole = n0 >= jb.n_lo && n0 + kUpCols <= jb.n_hi;   // all but the ends: no checks, 32-bit offsets
+    const __amdgpu_buffer_rsrc_t rd =
+        make_rsrc((TD *)jb.dst + (n0 - jb.dst_abs0) * jb.ld_dst, whole ? (int64_t)kUpCols * ld : 0);
+    // 16 bits: of samples q and q + 1 (q even) the even lane stores the first for both channels, the odd lane the second
+    const int odd = sizeof(TD) == 2 ? lane & 1 : 0;
+    const uint32_t sel = odd ? 0x07060302u : 0x01000504u;
+    const int vo = in ? (jb.col0 + c - odd) * (int)sizeof(TD) + (4 * (lane >> 5) + odd) * ld : 0x7ff00000;
+    auto put = [&](uint32_t v, int t, int e) __attribute__((always_inline)) {
+      if (whole) {
+        __builtin_amdgcn_raw_buffer_store_b32(v, rd, vo, (32 * t + 8 * (e >> 2) + (e & 3)) * ld, 0);
+      } else if (in) {
+        const int64_t n = n0 + 32 * t + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3) + odd;
+        if (n >= jb.n_lo && n < jb.n_hi)
+          *(uint32_t *)((TD *)jb.dst + (n - jb.dst_abs0) * jb.ld_dst + jb.col0 + c - odd) = v;
       }
+    };
+#pragma unroll
+    for (int t = 0; t < CT; ++t) {
+      const f32x16 acc = w.template tile<TM, SB>(t, hf, hlo);
+      if constexpr (sizeof(TD) == 4) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const float v = acc[e];
+          put(__builtin_bit_cast(uint32_t, v), t, e);
+        }
+      } else {
+        typedef TD pair __attribute__((ext_vector_type(2)));
+#pragma unroll
+        for (int e = 0; e < 16; e += 2) {
+          const pair p = {Op<TD>::cvt(acc[e]), Op<TD>::cvt(acc[e + 1])};
+          const uint32_t own = __builtin_bit_cast(uint32_t, p);
+          const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)own, 0xB1, 0xf, 0xf, true);
+          put(__builtin_amdgcn_perm(own, other, sel), t, e);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);   // a tile's stores go out before the next tile's results take registers
+    }
   } else {
     // lane holds sample n0 + 32 t + lane % 32 of channels r0 + 8 g + 4 (lane / 32) + q;
     // channels is a multiple of 16, so a lane's four channels are all in or all out
 #pragma unroll
     for (int t = 0; t < CT; ++t) {
+      const f32x16 acc = w.template tile<TM, SB>(t, hf, hlo);
       const int64_t n = n0 + 32 * t + (lane & 31);
-      if (n < jb.n_lo || n >= jb.n_hi) continue;
+      if (n >= jb.n_lo && n < jb.n_hi) {
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int rb = r0 + 8 * g + 4 * (lane >> 5);
-        if (rb >= jb.channels) continue;
-        TS *d = (TS *)jb.dst + (int64_t)rb * jb.ld_dst + (n - jb.dst_abs0);
+        for (int g = 0; g < 4; ++g) {
+          const int rb = r0 + 8 * g + 4 * (lane >> 5);
+          if (rb >= jb.channels) continue;
+          TS *d = (TS *)jb.dst + (int64_t)rb * jb.ld_dst + (n - jb.dst_abs0);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) d[(int64_t)q * jb.ld_dst] = O::cvt(acc[t][4 * g + q]);
+          for (int q = 0; q < 4; ++q) d[(int64_t)q * jb.ld_dst] = Op<TS>::cvt(acc[4 * g + q]);
+        }
       }
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
 }
 
 template <typename TS, typename TD>
-__global__ __launch_bounds__(256) void k_upsample(const UpJob *__restrict__ jobs, int n_jobs) {
-  const UpJob &jb = jobs[find_job(jobs, n_jobs, blockIdx.x)];
-  // The 8 XCDs take workgroups round-robin and every job's items start at a
-  // multiple of 8: give each XCD one contiguous run of the job's tasks, so
+__global__ __launch_bounds__(256) void k_upsample(const UpJob *__restrict__ jobs, int n_jobs, int r_min) {
+  const int last = find_job(jobs, n_jobs, blockIdx.x);   // the last job of the items' group
+  // The 8 XCDs take workgroups round-robin and every group's items start at a
+  // multiple of 8: give each XCD one contiguous run of the group's tasks, so
   // neighbouring column tiles (whose source windows overlap) share one L2.
-  const int64_t n_tasks = (int64_t)jb.n_rtiles * jb.n_ctiles;
+  const int rtiles = jobs[last].grp_rtiles;
+  const int64_t n_tasks = (int64_t)rtiles * jobs[last].n_ctiles;
   const int64_t per_xcd = (n_tasks + 31) / 32;          // items per XCD, 4 tasks each
-  const int64_t b = (int64_t)blockIdx.x - jb.item0;
+  const int64_t b = (int64_t)blockIdx.x - jobs[last].item0;
   const int64_t li = (b & 7) * per_xcd + (b >> 3);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  // wave task: 32 channels x kUpCols output samples
-  const int64_t task = li * 4 + wave;
+  const int lane = threadIdx.x & 63;
+  // wave task: a block of channels x kUpCols output samples
+  const int64_t task = li * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (task >= n_tasks) return;
-  const int r0 = (int)(task % jb.n_rtiles) * 32;
-  const int64_t n0 = jb.n_first + (task / jb.n_rtiles) * kUpCols;
-  if (jb.dst_tm) upsample_task<TS, TD, true>(jb, lane, r0, n0);
-  else upsample_task<TS, TD, false>(jb, lane, r0, n0);
+  int rt = (int)(task % rtiles), k = last;
+  while (jobs[k].rt0 > rt) --k;
+  const UpJob &jb = jobs[k];
+  rt -= jb.rt0;
+  const int64_t n0 = jb.n_first + (task / rtiles) * kUpCols;
+  extern __shared__ __attribute__((aligned(1024))) char lds_all[];
+  char *const lds = lds_all + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * up_wave_lds<TS>(r_min);
+  constexpr int SB4 = UpWindow<TS, std::is_same<TS, float>::value && std::is_same<TD, __bf16>::value>::SB4;
+  if (jb.dst_tm) {
+    const int r0 = rt * 32 - jb.col0 % 32;
+    if (jb.r == 4) upsample_task<TS, TD, true, SB4>(jb, lds, lane, r0, n0);
+    else upsample_task<TS, TD, true, 2 * SB4>(jb, lds, lane, r0, n0);
+  } else if (jb.r == 4) {
+    upsample_task<TS, TD, false, SB4>(jb, lds, lane, rt * 32, n0);
+  } else {
+    upsample_task<TS, TD, false, 2 * SB4>(jb, lds, lane, rt * 32, n0);
+  }
 }
 
 // ------------------------------------------------------- mixing + peaks
@@ -2453,15 +2522,21 @@ hipError_t launch_fir_jobs(lloid_dtype t, int variant, const FirJob *jobs, int n
   }
 }
 
-hipError_t launch_up_jobs(lloid_dtype t, const UpJob *jobs, int n_jobs, int64_t n_items, hipStream_t s) {
+template <typename TS, typename TD>
+static hipError_t up_t(const UpJob *jobs, int n_jobs, int64_t n_items, int r_min, hipStream_t s) {
+  static_assert(4 * up_wave_lds<TS>(2) <= 64 * 1024, "within the default limit of dynamic LDS");
+  k_upsample<TS, TD><<<(unsigned)n_items, 256, 4 * up_wave_lds<TS>(r_min), s>>>(jobs, n_jobs, r_min);
+  return hipGetLastError();
+}
+
+hipError_t launch_up_jobs(lloid_dtype t, const UpJob *jobs, int n_jobs, int64_t n_items, int r_min, hipStream_t s) {
   if (n_items <= 0) return hipSuccess;
   switch (t) {
-    case LLOID_F32: k_upsample<float, float><<<(unsigned)n_items, 256, 0, s>>>(jobs, n_jobs); break;
-    case LLOID_F16: k_upsample<_Float16, _Float16><<<(unsigned)n_items, 256, 0, s>>>(jobs, n_jobs); break;
-    case LLOID_BF16: k_upsample<float, __bf16><<<(unsigned)n_items, 256, 0, s>>>(jobs, n_jobs); break;
+    case LLOID_F32: return up_t<float, float>(jobs, n_jobs, n_items, r_min, s);
+    case LLOID_F16: return up_t<_Float16, _Float16>(jobs, n_jobs, n_items, r_min, s);
+    case LLOID_BF16: return up_t<float, __bf16>(jobs, n_jobs, n_items, r_min, s);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 template <typename T, int MT, int NT, int WM, int WN, int BK>

@@ -506,6 +506,7 @@ lloid_status enqueue_tick(lloid_stream *s, int64_t wa, int64_t wb, Clock::time_p
     key.push_back(items.split ? 1 : 0);
     for (int h = 0; h < kMaxHops; ++h) {
       key.push_back(items.up[h]);
+      key.push_back(items.up_r[h]);
       key.push_back((int64_t)to.up[h]);
       key.push_back(to.n_up[h]);
     }

@@ -231,3 +231,31 @@ def test_mixing_forms_in_one_call(compute):
     finally:
         for h in hs:
             lloid.lloid_bank_destroy(h)
+
+
+# ------------------------------------------------- last interpolation hops by group
+
+@pytest.mark.parametrize("compute", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("widths", [(5, 16, 33, 40), (32, 7, 90, 16), (17, 100, 1, 31)])
+def test_interpolated_column_blocks(compute, widths):
+    """Slices that begin and end inside the operand's 32-column blocks, one or two
+    hops of either factor in one launch, blocks that end on either side of a
+    column tile, alone and in a batch: peaks against the oracle."""
+    from paper_2410_16416_amd import lloid
+    f0 = 2048
+    specs = [SliceSpec(f0 >> lv, 128 * k, 128, w) for k, (lv, w) in enumerate(zip((0, 1, 2, 3), widths))]
+    banks = [configs.random_basis_bank(24, specs[:k], f0, np.random.default_rng(1000 + k)) for k in (4, 2, 3)]
+    hs = [lloid.bank_from_svd(ctx(), b, compute) for b in banks]
+    try:
+        for n in (100, 128, 2048 + 129, 3 * 2048 + 127):
+            x = np.random.default_rng(1100 + n).standard_normal(n)
+            both = lloid.lloid_filter_batch(hs, 0, x, window=(1, 8), peaks=True)
+            for k, (h, b) in enumerate(zip(hs, banks)):
+                _, want, _, _ = oracle.peak_table(oracle.lloid_snr(b, x), 0, f0, 1, 8)
+                one = lloid.lloid_filter(h, 0, x, window=(1, 8), peaks=True)
+                assert np.max(np.abs(one.peak_snr - want)) < EPS_ABS[compute]
+                assert np.array_equal(both.peak_snr[k], one.peak_snr)
+                assert np.array_equal(both.peak_sample[k], one.peak_sample)
+    finally:
+        for h in hs:
+            lloid.lloid_bank_destroy(h)
