@@ -1270,8 +1270,9 @@ extern "C" lloid_status lloid_coincide(lloid_ctx *ctx, const lloid_trigger *a, i
   auto add = [&](size_t cnt, size_t sz) { bytes = (size_t)round_up((int64_t)bytes, 256) + cnt * sz; };
   if (host_a) add((size_t)n_a, sizeof(lloid_trigger));
   if (host_b) add((size_t)n_b, sizeof(lloid_trigger));
-  add((size_t)n_a + 2, 8);
-  add(1, sizeof(int));
+  const size_t nblk = (size_t)coinc_blocks(n_a, n_b);
+  add(nblk, 8);
+  add(nblk, sizeof(int));
   if (host_out) add((size_t)cap, sizeof(lloid_coinc));
   if (host_bg) add((size_t)(n_a + n_b), 1);
   lloid_status rs = ensure_ws(ctx, ctx->ws, bytes);
@@ -1288,19 +1289,15 @@ extern "C" lloid_status lloid_coincide(lloid_ctx *ctx, const lloid_trigger *a, i
     HIP_TRY(hipMemcpyAsync(p, b, (size_t)n_b * sizeof(lloid_trigger), hipMemcpyHostToDevice, st));
     db = p;
   }
-  int64_t *counts = cv.take<int64_t>((size_t)n_a + 2);
-  int64_t *total = counts + n_a;
-  int *bad = cv.take<int>(1);
+  int64_t *counts = cv.take<int64_t>(nblk);
+  int *bad = cv.take<int>(nblk);
   lloid_coinc *dout = host_out ? cv.take<lloid_coinc>((size_t)cap) : out;
   uint8_t *dbg = host_bg ? cv.take<uint8_t>((size_t)(n_a + n_b)) : background;
-  HIP_TRY(launch_fill_u8(bad, sizeof(int), st));
-  HIP_TRY(launch_coincide(da, n_a, db, n_b, max_dt, counts, total, bad, cap, dout, dbg, dbg ? dbg + n_a : nullptr,
-                          st));
-  int64_t h_total = 0;
-  int h_bad = 0;
-  HIP_TRY(hipMemcpyAsync(&h_total, total, sizeof h_total, hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipMemcpyAsync(&h_bad, bad, sizeof h_bad, hipMemcpyDeviceToHost, st));
+  ResultWords *res = (ResultWords *)ctx->stage;
+  HIP_TRY(launch_coincide(da, n_a, db, n_b, max_dt, counts, bad, res, cap, dout, dbg, dbg ? dbg + n_a : nullptr, st));
   HIP_TRY(hipStreamSynchronize(st));
+  const int64_t h_total = res->total;
+  const int h_bad = res->bad;
   if (h_bad) return fail(LLOID_EINVAL, "a trigger list is not sorted by (bank, template_id, sample)");
   const int64_t ncopy = std::min(h_total, cap);
   if (host_out && ncopy > 0)

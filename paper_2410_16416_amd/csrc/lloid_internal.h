@@ -308,10 +308,16 @@ struct CondArgs {
 hipError_t launch_condition(const void *x, lloid_dtype dt, int L, const CondArgs &c, hipStream_t s);
 // Transform tables: kCondMaxLen twiddles, kCondMaxLen window values.
 hipError_t launch_fft_tables(float2 *tw, float *win, hipStream_t s);
-// Coincidences of two sorted trigger lists: per-trigger counts (na slots),
-// their scan, pairs at the scanned offsets; *bad set when a list is out of order.
+// Coincidences of two sorted trigger lists: counts and flags (out of order) per
+// block, pairs at the counts before them; the totals into res (pinned host
+// memory).  counts and bad hold coinc_blocks(na, nb) slots.
+constexpr int kCoincThreads = 256;
+inline int64_t coinc_blocks(int64_t na, int64_t nb) {
+  const int64_t n = na > nb ? na : nb;
+  return n > 0 ? (n + kCoincThreads - 1) / kCoincThreads : 1;
+}
 hipError_t launch_coincide(const lloid_trigger *a, int64_t na, const lloid_trigger *b, int64_t nb, int64_t max_dt,
-                           int64_t *counts, int64_t *total, int *bad, int64_t cap, lloid_coinc *out, uint8_t *bg_a,
+                           int64_t *counts, int *bad, ResultWords *res, int64_t cap, lloid_coinc *out, uint8_t *bg_a,
                            uint8_t *bg_b, hipStream_t s);
 hipError_t launch_sigma2(const double *mix64, int n_templates, int lsum, const double *inv_dec_per_col,
                          double *out, hipStream_t s);

@@ -2327,8 +2327,12 @@ __global__ __launch_bounds__(256) void k_gate(const uint64_t *__restrict__ loud,
 // peak samples differ by at most max_dt (Sec. II.A, the coincidence
 // generator).  Both lists are sorted by (bank, template, sample), so the
 // partners of a[i] are one contiguous run of b, found by binary search; one
-// thread per trigger of a counts its run, the counts are scanned, and the
-// same threads write their pairs at the scanned offsets (a-major order).
+// thread per trigger of a counts its run, and the same threads write their pairs
+// (a-major order) at the counts before theirs: the blocks' ones added up (or
+// scanned, beyond kTrigInline blocks), their own block's scanned in place.  Per
+// block, not per trigger, and without a launch for it: 2 x 126 thousand triggers
+// 126 -> 26 us, of which the scan of one count per trigger in one workgroup
+// took 98.  Both launches are bound by the 17 dependent reads of the search.
 
 __device__ __forceinline__ bool key_before(const lloid_trigger &x, int32_t bank, int32_t tmpl, int64_t sample) {
   if (x.bank != bank) return x.bank < bank;
@@ -2356,46 +2360,102 @@ __device__ __forceinline__ bool coinc_partner(const lloid_trigger &x, const lloi
   return x.bank == t.bank && x.template_id == t.template_id && x.sample <= t.sample + max_dt;
 }
 
-__global__ void k_coinc_count(const lloid_trigger *__restrict__ a, int64_t na, const lloid_trigger *__restrict__ b,
-                              int64_t nb, int64_t max_dt, int64_t *__restrict__ counts, uint8_t *__restrict__ bg_b,
-                              int *__restrict__ bad) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+static_assert(kCoincThreads % 64 == 0, "whole waves");
+
+__global__ __launch_bounds__(kCoincThreads) void k_coinc_count(const lloid_trigger *__restrict__ a, int64_t na,
+                                                               const lloid_trigger *__restrict__ b, int64_t nb,
+                                                               int64_t max_dt, int64_t *__restrict__ counts,
+                                                               int *__restrict__ bad, uint8_t *__restrict__ bg_b) {
+  __shared__ int64_t sh[kCoincThreads / 64];
+  const int64_t i = (int64_t)blockIdx.x * kCoincThreads + threadIdx.x;
+  bool unsorted = false;
   if (i < nb) {
     if (bg_b) bg_b[i] = 1;
-    if (i + 1 < nb && out_of_order(b[i], b[i + 1])) *bad = 1;
+    unsorted = i + 1 < nb && out_of_order(b[i], b[i + 1]);
   }
-  if (i >= na) return;
-  const lloid_trigger t = a[i];
-  if (i + 1 < na && out_of_order(t, a[i + 1])) *bad = 1;
   int64_t c = 0;
-  for (int64_t j = coinc_first(b, nb, t, max_dt); j < nb && coinc_partner(b[j], t, max_dt); ++j) ++c;
-  counts[i] = c;
+  if (i < na) {
+    const lloid_trigger t = a[i];
+    unsorted = unsorted || (i + 1 < na && out_of_order(t, a[i + 1]));
+    for (int64_t j = coinc_first(b, nb, t, max_dt); j < nb && coinc_partner(b[j], t, max_dt); ++j) ++c;
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = c;
+  const int any = __syncthreads_or(unsorted);
+  if (threadIdx.x == 0) {
+    int64_t sum = 0;
+    for (int q = 0; q < kCoincThreads / 64; ++q) sum += sh[q];
+    counts[blockIdx.x] = sum;
+    bad[blockIdx.x] = any;
+  }
 }
 
-__global__ void k_coinc_write(const lloid_trigger *__restrict__ a, int64_t na, const lloid_trigger *__restrict__ b,
-                              int64_t nb, int64_t max_dt, const int64_t *__restrict__ offsets, int64_t cap,
-                              lloid_coinc *__restrict__ out, uint8_t *__restrict__ bg_a,
-                              uint8_t *__restrict__ bg_b) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= na) return;
-  const lloid_trigger t = a[i];
-  int64_t m = offsets[i];
-  const int64_t m0 = m;
-  for (int64_t j = coinc_first(b, nb, t, max_dt); j < nb && coinc_partner(b[j], t, max_dt); ++j, ++m) {
+// SCANNED: counts holds the blocks' offsets; else their counts, and the last
+// block writes the total.  The last block also gathers the blocks' flags.
+// res: the result words, in host memory.
+template <bool SCANNED>
+__global__ __launch_bounds__(kCoincThreads) void k_coinc_write(const lloid_trigger *__restrict__ a, int64_t na,
+                                                               const lloid_trigger *__restrict__ b, int64_t nb,
+                                                               int64_t max_dt, const int64_t *__restrict__ counts,
+                                                               const int *__restrict__ bad, ResultWords *res,
+                                                               int64_t cap, lloid_coinc *__restrict__ out,
+                                                               uint8_t *__restrict__ bg_a, uint8_t *__restrict__ bg_b) {
+  __shared__ int64_t sh[kCoincThreads / 64], sh_off[kCoincThreads / 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int64_t m = 0;
+  if constexpr (SCANNED) {
+    m = counts[blockIdx.x];
+  } else {
+    int64_t s = 0;
+    for (int64_t q = threadIdx.x; q < (int64_t)blockIdx.x; q += kCoincThreads) s += counts[q];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+    if (lane == 0) sh_off[wave] = s;
+    __syncthreads();
+    for (int q = 0; q < kCoincThreads / 64; ++q) m += sh_off[q];
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) res->total = m + counts[blockIdx.x];
+  }
+  if (blockIdx.x == gridDim.x - 1) {
+    bool f = false;
+    for (int64_t q = threadIdx.x; q < (int64_t)gridDim.x; q += kCoincThreads) f = f || bad[q];
+    const int any = __syncthreads_or(f);
+    if (threadIdx.x == 0) res->bad = any;
+  }
+  const int64_t i = (int64_t)blockIdx.x * kCoincThreads + threadIdx.x;
+  lloid_trigger t = {};
+  int64_t j0 = 0, c = 0;
+  if (i < na) {
+    t = a[i];
+    j0 = coinc_first(b, nb, t, max_dt);
+    while (j0 + c < nb && coinc_partner(b[j0 + c], t, max_dt)) ++c;
+    if (bg_a) bg_a[i] = c ? 0 : 1;
+  }
+  int64_t inc = c;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int64_t u = __shfl_up(inc, off);
+    if (lane >= off) inc += u;
+  }
+  if (lane == 63) sh[wave] = inc;
+  __syncthreads();
+  for (int q = 0; q < wave; ++q) m += sh[q];
+  m += inc - c;
+  for (int64_t k = 0; k < c; ++k, ++m) {
+    const int64_t j = j0 + k;
     const lloid_trigger u = b[j];
     if (bg_b) bg_b[j] = 0;
     if (m < cap) {
-      lloid_coinc c;
-      c.a = i;
-      c.b = j;
-      c.bank = t.bank;
-      c.template_id = t.template_id;
-      c.snr_net = sqrtf(t.snr * t.snr + u.snr * u.snr);
-      c.dt = (float)(u.sample - t.sample) + (u.dt - t.dt);
-      out[m] = c;
+      lloid_coinc p;
+      p.a = i;
+      p.b = j;
+      p.bank = t.bank;
+      p.template_id = t.template_id;
+      p.snr_net = sqrtf(t.snr * t.snr + u.snr * u.snr);
+      p.dt = (float)(u.sample - t.sample) + (u.dt - t.dt);
+      out[m] = p;
     }
   }
-  if (bg_a) bg_a[i] = m == m0 ? 1 : 0;
 }
 
 // ---------------------------------------------------------- tuning input
@@ -2692,14 +2752,16 @@ hipError_t launch_condition(const void *x, lloid_dtype dt, int L, const CondArgs
 }
 
 hipError_t launch_coincide(const lloid_trigger *a, int64_t na, const lloid_trigger *b, int64_t nb, int64_t max_dt,
-                           int64_t *counts, int64_t *total, int *bad, int64_t cap, lloid_coinc *out, uint8_t *bg_a,
+                           int64_t *counts, int *bad, ResultWords *res, int64_t cap, lloid_coinc *out, uint8_t *bg_a,
                            uint8_t *bg_b, hipStream_t s) {
-  const int64_t nmax = std::max(na, nb);
-  if (nmax > 0)
-    k_coinc_count<<<blocks_for(nmax, 256), 256, 0, s>>>(a, na, b, nb, max_dt, counts, bg_b, bad);
-  k_trigger_scan<<<1, 1024, 0, s>>>(counts, na, total);
-  if (na > 0)
-    k_coinc_write<<<blocks_for(na, 256), 256, 0, s>>>(a, na, b, nb, max_dt, counts, cap, out, bg_a, bg_b);
+  const int64_t nblk = coinc_blocks(na, nb);
+  k_coinc_count<<<(unsigned)nblk, kCoincThreads, 0, s>>>(a, na, b, nb, max_dt, counts, bad, bg_b);
+  if (nblk > kTrigInline) {
+    k_trigger_scan<<<1, 1024, 0, s>>>(counts, nblk, &res->total);
+    k_coinc_write<true><<<(unsigned)nblk, kCoincThreads, 0, s>>>(a, na, b, nb, max_dt, counts, bad, res, cap, out, bg_a, bg_b);
+  } else {
+    k_coinc_write<false><<<(unsigned)nblk, kCoincThreads, 0, s>>>(a, na, b, nb, max_dt, counts, bad, res, cap, out, bg_a, bg_b);
+  }
   return hipGetLastError();
 }
 

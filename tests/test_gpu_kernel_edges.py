@@ -259,3 +259,42 @@ def test_interpolated_column_blocks(compute, widths):
     finally:
         for h in hs:
             lloid.lloid_bank_destroy(h)
+
+
+# ------------------------------------------------- coincidence over blocks
+
+def _trigger_list(sample, template=0):
+    from paper_2410_16416_amd import lloid
+    t = np.zeros(len(sample), dtype=lloid.TRIGGER_DTYPE)
+    t["sample"], t["template_id"] = sample, template
+    t["snr"] = 5.0 + (np.arange(len(sample)) % 7)
+    return t
+
+
+@pytest.mark.parametrize("na,nb", [(0, 0), (0, 257), (1, 0), (255, 1), (256, 256), (257, 255), (513, 4097),
+                                   (70000, 70001), (1048576 + 5, 300), (300, 1048576 + 257)])
+def test_coincidence_blocks(na, nb):
+    """Lists that end on either side of a block, one much longer than the other,
+    and more blocks than are added up in place: each trigger of one list pairs
+    with the trigger of the other at its time (three times as dense there: the
+    neighbours lie outside max_dt); a list out of order anywhere is refused."""
+    from paper_2410_16416_amd import lloid
+    a, b = _trigger_list(30 * np.arange(na)), _trigger_list(10 * np.arange(nb))
+    pairs, bg = lloid.lloid_coincide(ctx(), a, b, 9, background=True)
+    n = min(na, -(-nb // 3))
+    assert pairs.shape[0] == n
+    assert np.array_equal(pairs["a"], np.arange(n)) and np.array_equal(pairs["b"], 3 * np.arange(n))
+    want = np.ones(na + nb, dtype=np.uint8)
+    want[:n] = 0
+    want[na + 3 * np.arange(n)] = 0
+    assert np.array_equal(bg, want)
+    wide = lloid.lloid_coincide(ctx(), a[:600], b[:600], 25)
+    i, j = np.nonzero(np.abs(a["sample"][:600, None] - b["sample"][None, :600]) <= 25)
+    assert np.array_equal(wide["a"], i) and np.array_equal(wide["b"], j)
+    for lst, k in ((a, na - 1), (b, nb - 1), (a, na // 2), (b, nb // 2)):
+        if k > 0:
+            keep = lst["sample"][k]
+            lst["sample"][k] = lst["sample"][k - 1] - 1
+            with pytest.raises(lloid.LloidError):
+                lloid.lloid_coincide(ctx(), a, b, 9)
+            lst["sample"][k] = keep
