@@ -15,9 +15,13 @@
 // What bounds it: the MFMAs at the clock that their power leaves (K = 480:
 // 1.28 PFLOP/s, what the library's 8192^3 FP16 product reaches on the same
 // card), and below K of some 150 the 80 vector instructions per tile.
-// Measured, 1024 templates x 256 s, against k_mix_dl: K = 480 970 -> 804 us,
-// 352 753 -> 636, 256 559 -> 489, 160 422 -> 378, 96 311 -> 304; 1024 s at K =
-// 480 3.86 -> 3.13 ms (BF16, 200 s: 827 -> 624 us).  On the way: with the
+// Measured, 1024 templates x 256 s, against k_mix_dl: K = 480 970 -> 798 us,
+// 352 753 -> 620, 256 559 -> 477, 160 422 -> 366, 96 311 -> 282; 1024 s at K =
+// 480 3.86 -> 3.04 ms (BF16, 200 s: 827 -> 603 us).  A k-step's comparisons all
+// come before its selects (a select waits two slots for its comparison) and a
+// window's length is worked out once per window, not per tile: 312 -> 282 us at
+// K = 96, 3.11 -> 3.04 ms for the 1024 s.  A deeper ring is slower at a small K (16
+// tiles, K = 96: 380 us).  On the way: with the
 // arithmetic of a tile left after its MFMAs 3.36 ms, with the mixing fragments
 // in the vector registers' spare places and copied for each use 3.66 ms.  The
 // SNR series stays with k_mix_dl: stores of 256 bytes per template and tile
@@ -137,6 +141,9 @@ __device__ __forceinline__ void mix_reg_tiles(const MixJob &jb, int rt, int64_t 
   const int64_t wl0 = uniform64(g0 / tpw);
   WinCursor wi(jb.w0 + wl0, jb.win_p, jb.win_q), wc = wi;   // windows of the loads and of the products
   int ti = (int)(g0 - wl0 * tpw), tc = ti;
+  auto window_len = [&](const WinCursor &w) __attribute__((always_inline)) {
+    return __builtin_amdgcn_readfirstlane((int)(min(w.next_start(), jb.n_end) - w.start));
+  };
   auto window_rsrc = [&](const WinCursor &w) __attribute__((always_inline)) {
     const int64_t we = min(w.next_start(), jb.n_end);
     return make_rsrc((const T *)jb.ocat + (w.start - jb.ocat_abs0) * (int64_t)kld, (we - w.start) * (int64_t)pitch);
@@ -186,8 +193,10 @@ __device__ __forceinline__ void mix_reg_tiles(const MixJob &jb, int rt, int64_t 
   auto pair_best = [&](int e, float v, int rel) __attribute__((always_inline)) {
     const int mt = e >> 3, p = e & 7;
     if (v > best[mt][p].v) best[mt][p] = VN{v, rel};
-    // (stays here, between the MFMAs: the compiler would move it past them)
-    asm volatile("" : "+v"(best[mt][p].v), "+v"(best[mt][p].n));
+  };
+  // (a pair's peak stays here, between the MFMAs: the compiler would move it past them)
+  auto pin = [&](int e) __attribute__((always_inline)) {
+    asm volatile("" : "+v"(best[e >> 3][e & 7].v), "+v"(best[e >> 3][e & 7].n));
   };
   // window peaks: each half-wave's 32 columns of every pair, larger |z|^2
   // first, then lower sample; lane fr of a half then writes pair fr
@@ -212,7 +221,7 @@ __device__ __forceinline__ void mix_reg_tiles(const MixJob &jb, int rt, int64_t 
   };
   bool last = false;   // the previous tile was its window's (or the run's) last
   int64_t w_cur = jb.w0 + wl0;
-  int done = 0;
+  int len_cur = window_len(wc), done = 0;
   // one tile: MFMAs into acc, the previous tile's peaks from prev between them.
   // Its first D k-steps' fragments have been read before the last tile's end,
   // and it reads the next one's (which the barrier at its own start has shown
@@ -254,16 +263,18 @@ __device__ __forceinline__ void mix_reg_tiles(const MixJob &jb, int rt, int64_t 
 #pragma unroll
       for (int q = 0; q < EPK; ++q)
         if (ks * EPK + q < 16) pair_best(ks * EPK + q, v[q], rel);
+#pragma unroll
+      for (int q = 0; q < EPK; ++q)
+        if (ks * EPK + q < 16) pin(ks * EPK + q);
     }
     static_assert(LPW < NKS, "a load per k-step");
     issue_next();
     __builtin_amdgcn_sched_barrier(0);
     if (last) flush();
     // this tile is the next one's previous
-    const int64_t we = min(wc.next_start(), jb.n_end);
     w_prev = w_cur;
     rel_prev = 32 * tc;
-    len_prev = (int)(we - wc.start);
+    len_prev = len_cur;
     ++done;
     ++tc;
     last = tc == tpw || done == n;
@@ -271,6 +282,7 @@ __device__ __forceinline__ void mix_reg_tiles(const MixJob &jb, int rt, int64_t 
       tc = 0;
       ++w_cur;
       wc.advance();
+      len_cur = window_len(wc);
     }
   };
   // tile 0 is in (the first tile's own barrier then shows tile 1)
