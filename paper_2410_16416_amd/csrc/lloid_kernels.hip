@@ -2621,7 +2621,7 @@ static hipError_t mix_t(int variant, const MixJob *jobs, int n_jobs, int64_t n_i
     default:
       // 16-bit operands: direct-to-LDS K chunks of 64, eight 64 x 128 waves.  Takes
       // the SNR series (485 us with it against 535 for the register-held form, 48 s
-      // of 1024 templates) and a concatenated K above 512, whose mixing fragments
+      // of 1024 templates) and a concatenated K above 640, whose mixing fragments
       // no longer fit the registers; the rest is launch_mix_reg's.
       if constexpr (sizeof(T) == 2) {
         if (with_snr) k_mix_dl<T, 4, 2, 2, 4, 64, 1, true><<<(unsigned)n_items, 512, 0, s>>>(jobs, n_jobs);

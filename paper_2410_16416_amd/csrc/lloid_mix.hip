@@ -1,5 +1,5 @@
 // Mixing and window peaks with the mixing rows held in registers (16-bit
-// operands, concatenated K up to 512, no SNR series).
+// operands, concatenated K up to 640, no SNR series).
 //
 // Y[c, n] = sum_k M[c, k] O[n, k]; rows 2i and 2i + 1 (cos, sin) of template i
 // land in the same lane, so |z|^2 and the running per-template peak stay in
@@ -26,6 +26,12 @@
 // in the vector registers' spare places and copied for each use 3.66 ms.  The
 // SNR series stays with k_mix_dl: stores of 256 bytes per template and tile
 // here against 2 KB there, 48 s of 1024 templates 535 against 472 us.
+//
+// A K up to 512 fills the accumulation registers.  Up to 640 the last k-steps'
+// fragments take 64 of the vector registers and the ring has three tiles
+// (two forms, of 576 and 640; a longer K would spill).  Ten uneven banks of 64 s, two of
+// them with K = 544 and 640: 1335 us and 386 us in k_mix_dl -> 1636 us; a serving
+// tick of 12 banks, 81 + 62 us -> 122 us in one launch.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -72,7 +78,9 @@ template <typename F> __device__ __forceinline__ int half_wave_reduce(int v, F o
   return op(v, __builtin_amdgcn_ds_swizzle(v, 0x401f));                   // lane ^ 16
 }
 
-constexpr int kRing = 4;   // operand tiles in LDS, three ahead of the one multiplied
+// Operand tiles in LDS, all but one ahead of the one multiplied.
+constexpr int ring_tiles(int nks) { return nks <= 32 ? 4 : 3; }
+constexpr int kRegSteps = 32;   // k-steps whose mixing fragments fill the accumulation registers
 
 // A divisor of the k-steps that covers an LDS read's latency (a k-step is 64
 // cycles of MFMAs), where there is one.
@@ -86,7 +94,8 @@ template <int NKS> struct MixRegShape {
   static constexpr int P = 2 * NKS + 1;                    // 16-byte chunks per LDS row: odd, so 16 rows start on distinct banks
   static constexpr int LPW = (32 * P + 255) / 256;         // load instructions per wave and tile
   static constexpr int TILE = LPW * 4096;
-  static constexpr int LDS = kRing * TILE;
+  static constexpr int R = ring_tiles(NKS);
+  static constexpr int LDS = R * TILE;
   static constexpr int D = read_ahead(NKS);   // k-steps read ahead
   static_assert(NKS % D == 0, "k-steps in whole turns of the read-ahead");
 };
@@ -98,11 +107,11 @@ template <typename T, int NKS>
 __device__ __forceinline__ void mix_reg_tiles(const MixJob &jb, int rt, int64_t g0, int64_t g1, char *lds) {
   typedef typename Op<T>::vec vec;
   typedef MixRegShape<NKS> S;
-  constexpr int P = S::P, LPW = S::LPW, TILE = S::TILE;
+  constexpr int P = S::P, LPW = S::LPW, TILE = S::TILE, kRing = S::R;
   const int lane = threadIdx.x & 63, fr = lane & 31, fh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int kld = jb.kld, tpw = jb.tpw;
-  constexpr int CPR = 2 * NKS;   // 16-byte chunks of an operand row
+  const int cpr = jb.kcat / 8;   // 16-byte chunks of an operand row (the rest of 2 NKS: zeros)
   const int pitch = kld * 2;
   const int64_t r0 = (int64_t)rt * 256 + 64 * wave;
 
@@ -124,7 +133,11 @@ __device__ __forceinline__ void mix_reg_tiles(const MixJob &jb, int rt, int64_t 
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
-      for (int ks = 0; ks < NKS; ++ks) asm volatile("" : "+a"(af[mt][ks]));
+      for (int ks = 0; ks < (NKS < kRegSteps ? NKS : kRegSteps); ++ks) asm volatile("" : "+a"(af[mt][ks]));
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+      for (int ks = kRegSteps; ks < NKS; ++ks) asm volatile("" : "+v"(af[mt][ks]));
   }
 
   // operand loads: load i of a wave fills LDS chunks 64 (4 i + wave) + lane of
@@ -135,7 +148,7 @@ __device__ __forceinline__ void mix_reg_tiles(const MixJob &jb, int rt, int64_t 
   for (int i = 0; i < LPW; ++i) {
     const int c = 64 * (4 * i + wave) + lane;
     const int row = c / P, q = c - row * P;
-    vo[i] = (row < 32 && q < CPR) ? row * pitch + q * 16 : 0x7ff00000;
+    vo[i] = (row < 32 && q < cpr) ? row * pitch + q * 16 : 0x7ff00000;
   }
   const int n = (int)(g1 - g0);
   const int64_t wl0 = uniform64(g0 / tpw);
@@ -318,6 +331,7 @@ __device__ __forceinline__ void mix_reg_tiles(const MixJob &jb, int rt, int64_t 
 template <typename T>
 __global__ __launch_bounds__(256, 1) void k_mix_reg(const MixJob *__restrict__ jobs, int n_jobs) {
   __shared__ __attribute__((aligned(1024))) char lds[MixRegShape<32>::LDS];
+  static_assert(MixRegShape<36>::LDS <= MixRegShape<32>::LDS && MixRegShape<40>::LDS <= MixRegShape<32>::LDS, "the largest ring");
   const MixJob &jb = jobs[find_job(jobs, n_jobs, blockIdx.x)];
   const int64_t b = (int64_t)blockIdx.x - jb.item0;
   // XCD-aware order as in mix_unit: all row tiles of one run on one XCD
@@ -334,6 +348,8 @@ __global__ __launch_bounds__(256, 1) void k_mix_reg(const MixJob *__restrict__ j
     MIX_REG(1) MIX_REG(2) MIX_REG(3) MIX_REG(4) MIX_REG(5) MIX_REG(6) MIX_REG(7) MIX_REG(8)
     MIX_REG(9) MIX_REG(10) MIX_REG(11) MIX_REG(12) MIX_REG(13) MIX_REG(14) MIX_REG(15) MIX_REG(16)
 #undef MIX_REG
+    case 17: case 18: mix_reg_tiles<T, 36>(jb, rt, g0, g1, lds); break;
+    case 19: case 20: mix_reg_tiles<T, 40>(jb, rt, g0, g1, lds); break;
   }
 }
 

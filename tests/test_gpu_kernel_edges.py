@@ -184,7 +184,7 @@ def test_narrow_fir_tiles(compute, taps):
 @pytest.mark.parametrize("compute", ["f16", "bf16"])
 @pytest.mark.parametrize("k32", list(range(1, 18)))
 def test_register_held_mixing(compute, k32):
-    """Every compiled K (32 to 512; 544 takes the other kernel), one row tile and
+    """Every compiled K (32 to 512 and 544), one row tile and
     several, windows of one operand tile, of many and shared between runs, a
     ragged end: peaks against the oracle, and bit for bit those of the
     register-staged tile shapes."""
@@ -213,7 +213,7 @@ def test_register_held_mixing(compute, k32):
 
 @pytest.mark.parametrize("compute", ["f16", "bf16"])
 def test_mixing_forms_in_one_call(compute):
-    """Banks on both sides of the register-held form's K in one batched call."""
+    """Banks of several forms of the register-held kernel in one batched call."""
     from paper_2410_16416_amd import lloid
     f0 = 1024
     banks = [configs.random_basis_bank(f, [SliceSpec(f0, 0, 700, l)], f0, np.random.default_rng(90 + l))
@@ -298,3 +298,29 @@ def test_coincidence_blocks(na, nb):
             with pytest.raises(lloid.LloidError):
                 lloid.lloid_coincide(ctx(), a, b, 9)
             lst["sample"][k] = keep
+
+
+@pytest.mark.parametrize("compute", ["f16", "bf16"])
+@pytest.mark.parametrize("k", [544, 545, 576, 600, 640, 641, 672])
+def test_register_held_mixing_long_k(compute, k):
+    """The forms whose last mixing fragments live in the vector registers, with
+    k-steps past K (544 and 608), and the first K beyond them: peaks
+    against the oracle and bit for bit those of a register-staged tile shape."""
+    from paper_2410_16416_amd import lloid
+    f0 = 1024
+    bank = configs.random_basis_bank(150, [SliceSpec(f0, 0, 700, k)], f0, np.random.default_rng(1200 + k))
+    x = np.random.default_rng(1201).standard_normal(4 * f0 + 77)
+    z = oracle.lloid_snr(bank, x)
+    b = lloid.bank_from_svd(ctx(), bank, compute)
+    try:
+        for win in ((1, 1), (1, 32), (5, 1)):
+            _, want, _, _ = oracle.peak_table(z, 0, f0, *win)
+            lloid.lloid_ctx_set_tiles(ctx(), 0, 0)
+            res = lloid.lloid_filter(b, 0, x, window=win, peaks=True)
+            assert np.max(np.abs(res.peak_snr - want)) < EPS_ABS[compute]
+            lloid.lloid_ctx_set_tiles(ctx(), 0, 4)
+            r = lloid.lloid_filter(b, 0, x, window=win, peaks=True)
+            assert np.array_equal(r.peak_snr, res.peak_snr) and np.array_equal(r.peak_sample, res.peak_sample)
+    finally:
+        lloid.lloid_ctx_set_tiles(ctx(), 0, 0)
+        lloid.lloid_bank_destroy(b)
