@@ -142,7 +142,7 @@ int mix_parts(int64_t windows, int64_t row_tiles, int64_t steps, int64_t slots);
 // kMixRegOverhead tiles' time (the mixing rows' load, the first tiles'
 // latency), of at most kMixRegRun tiles.  341 templates, 40 s in 0.5 s windows,
 // 255 runs of 31 tiles: 33 on one XCD's 32 CUs, 102 us; 240 runs of 32, one
-// round: 57 us.
+// round: 46 us.
 constexpr int64_t kMixRegRun = 256;
 constexpr double kMixRegOverhead = 4.0;
 int64_t mix_reg_run(int64_t total, int64_t row_tiles, int64_t slots);
