@@ -35,36 +35,13 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "lloid_cursor.h"
 #include "lloid_device.h"
 #include "lloid_internal.h"
 
 namespace lloid {
 
 namespace {
-
-// A wave-uniform 64-bit value in scalar registers (64-bit divisions run on the
-// vector unit, whose results the compiler takes for divergent).
-__device__ __forceinline__ int64_t uniform64(int64_t v) {
-  return ((int64_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) | (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
-}
-
-// Trigger window starts floor(w p / q), w = w0, w0 + 1, ..: a division for the
-// first, additions after it.
-struct WinCursor {
-  int64_t start, rem, step, step_rem, q;
-  __device__ __forceinline__ WinCursor(int64_t w, int64_t p, int64_t q_) : q(q_) {
-    start = uniform64((w * p) / q);
-    rem = w * p - start * q;
-    step = uniform64(p / q);
-    step_rem = p - step * q;
-  }
-  __device__ __forceinline__ int64_t next_start() const { return start + step + (rem + step_rem >= q ? 1 : 0); }
-  __device__ __forceinline__ void advance() {
-    start = next_start();
-    rem += step_rem;
-    if (rem >= q) rem -= q;
-  }
-};
 
 typedef __attribute__((address_space(3))) void lds_void;
 
@@ -152,8 +129,9 @@ __device__ __forceinline__ void mix_reg_tiles(const MixJob &jb, int rt, int64_t 
   }
   const int n = (int)(g1 - g0);
   const int64_t wl0 = uniform64(g0 / tpw);
-  WinCursor wi(jb.w0 + wl0, jb.win_p, jb.win_q), wc = wi;   // windows of the loads and of the products
-  int ti = (int)(g0 - wl0 * tpw), tc = ti;
+  WinCursor wc(jb.w0 + wl0, jb.win_p, jb.win_q);   // window and tile of the products
+  int tc = (int)(g0 - wl0 * tpw);
+  TileLoads ld{wc, tc, 0};                         // those of the loads
   auto window_len = [&](const WinCursor &w) __attribute__((always_inline)) {
     return __builtin_amdgcn_readfirstlane((int)(min(w.next_start(), jb.n_end) - w.start));
   };
@@ -161,23 +139,16 @@ __device__ __forceinline__ void mix_reg_tiles(const MixJob &jb, int rt, int64_t 
     const int64_t we = min(w.next_start(), jb.n_end);
     return make_rsrc((const T *)jb.ocat + (w.start - jb.ocat_abs0) * (int64_t)kld, (we - w.start) * (int64_t)pitch);
   };
-  __amdgpu_buffer_rsrc_t rb = window_rsrc(wi);
-  int issued = 0;
+  __amdgpu_buffer_rsrc_t rb = window_rsrc(ld.win);
   auto issue_one = [&](int i) __attribute__((always_inline)) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void *)(lds + (issued % kRing) * TILE + wave * 1024 + i * 4096), 16,
-                                             vo[i], ti * 32 * pitch, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void *)(lds + (ld.issued % kRing) * TILE + wave * 1024 + i * 4096),
+                                             16, vo[i], ld.ti * 32 * pitch, 0, 0);
   };
   auto issue_next = [&]() __attribute__((always_inline)) {
-    ++ti;
-    if (++issued == n) {
-      // past the run: an empty resource, so that every tile adds LPW loads (of zeros)
-      rb = make_rsrc(jb.ocat, 0);
-      ti = 0;
-    } else if (ti == tpw) {
-      ti = 0;
-      wi.advance();
-      rb = window_rsrc(wi);
-    }
+    const TileSource from = ld.next(n, tpw);
+    // past the run: an empty resource, so that every tile adds LPW loads (of zeros)
+    if (from == TileSource::kNone) rb = make_rsrc(jb.ocat, 0);
+    else if (from == TileSource::kNextWindow) rb = window_rsrc(ld.win);
   };
 #pragma unroll
   for (int t = 0; t < kRing - 1; ++t) {

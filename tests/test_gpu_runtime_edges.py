@@ -1,0 +1,55 @@
+"""Edges of the runtime around the kernels: short trigger windows in streaming
+ticks and in chunks, forms of a kernel side by side in one call, the order of
+a call's reads on the caller's stream, what a captured tick depends on."""
+
+import numpy as np
+import pytest
+
+from workloads import configs
+from workloads.bank import SliceSpec
+
+from gpu_util import ctx
+from test_gpu_stream import canon, offline, run_stream
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("compute", ["f16", "bf16"])
+@pytest.mark.parametrize("k", [64, 512, 576])
+@pytest.mark.parametrize("samples", [32, 64])
+def test_short_windows_end_with_the_operand(compute, k, samples):
+    """Windows of one or two operand tiles (rings of four and of three tiles),
+    where the register-held mixing kernel's loads run ahead over several
+    windows: ticks of few windows, and chunks of a few windows each, whose
+    operands end with the last one, give the triggers of the whole block bit
+    for bit, and those of a tile shape without that kernel."""
+    from paper_2410_16416_amd import lloid
+    f0, win = 1024, (samples, 1024)
+    bank = configs.random_basis_bank(16, [SliceSpec(f0, 0, 600, k)], f0, np.random.default_rng(2000 + k))
+    x = np.random.default_rng(2001 + samples).standard_normal(4 * f0 + 5)
+    h = lloid.bank_from_svd(ctx(), bank, compute)
+    try:
+        whole = lloid.lloid_filter(h, 0, x, window=win, threshold=2.0, peaks=True)
+        assert whole.n_triggers > 0
+        lloid.lloid_ctx_set_chunk_bytes(ctx(), 3 * samples * k * 2)
+        parts = lloid.lloid_filter(h, 0, x, window=win, threshold=2.0, peaks=True)
+        lloid.lloid_ctx_set_chunk_bytes(ctx(), 6 << 30)
+        lloid.lloid_ctx_set_tiles(ctx(), 0, 4)
+        other = lloid.lloid_filter(h, 0, x, window=win, threshold=2.0, peaks=True)
+        lloid.lloid_ctx_set_tiles(ctx(), 0, 0)
+        for r in (parts, other):
+            assert np.array_equal(r.triggers, whole.triggers)
+            assert np.array_equal(r.peak_snr, whole.peak_snr) and np.array_equal(r.peak_sample, whole.peak_sample)
+        s = lloid.lloid_stream_create(ctx(), f0, compute, n_detectors=1, min_rate_hz=f0, window=win, threshold=2.0,
+                                      max_filter_s=1.0, max_windows_per_tick=8)
+        try:
+            slot, active = lloid.lloid_stream_admit(s, h)
+            assert active
+            got = canon(run_stream(lloid, s, [x], [8 * samples, samples, 5 * samples]))
+        finally:
+            lloid.lloid_stream_destroy(s)
+        assert np.array_equal(got, offline(lloid, h, [x], win, slot, threshold=2.0))
+    finally:
+        lloid.lloid_ctx_set_chunk_bytes(ctx(), 6 << 30)
+        lloid.lloid_ctx_set_tiles(ctx(), 0, 0)
+        lloid.lloid_bank_destroy(h)
