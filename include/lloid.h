@@ -207,7 +207,9 @@ lloid_status lloid_bank_destroy(lloid_bank *bank);
 
 /* Filter one block of strain (offline mode: zero strain before sample 0 and
  * after sample n-1) and reduce it to triggers.
- *   strain: host or device, n samples of `strain_dtype` (F64 or F32).
+ *   strain: host or device, n samples of `strain_dtype` (F64 or F32).  Read in
+ *           the order of the context's stream: work queued there before the
+ *           call may still be filling it.
  *   opts:   window and threshold; NULL means 1 s windows and threshold 4.
  *   trig:   host or device, capacity trig_cap; *n_trig receives the number
  *           of triggers.  If it exceeds trig_cap the first trig_cap (in

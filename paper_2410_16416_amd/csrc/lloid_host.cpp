@@ -743,6 +743,13 @@ lloid_status lloid::launch_stages(lloid_ctx *ctx, lloid_dtype ct, const char *dt
   HIP_TRY(mark(LLOID_STAGE_PHASE, 1));
   return LLOID_OK;
 }
+
+static bool stream_idle(hipStream_t s) {
+  const hipError_t e = hipStreamQuery(s);
+  if (e != hipSuccess) (void)hipGetLastError();
+  return e == hipSuccess;
+}
+
 // Filter one block of strain of one detector with every bank of `banks`
 // (same context, full rate and operand type) and compact the triggers.
 // no_alloc: every device buffer comes from the context's static scratch
@@ -903,12 +910,18 @@ static lloid_status filter_banks(lloid_bank *const *banks, int nb, int32_t detec
   const int64_t chunk_n = std::min<int64_t>(n, win.start(wpc) + 1);   // samples of the longest chunk
   const size_t tab_bytes = table_bytes(n_chunks);
   const size_t bytes = layout_bytes(wpc);
-  // small inputs go through the context's stage, read by the first kernel
-  // where they lie: the tables, then a host block of strain
+  // small inputs are read by the first kernel where they lie: the tables in
+  // the context's stage, a host block of strain in the caller's pinned memory
+  // or behind the tables.  Work queued on the caller's stream before the call
+  // may still be filling the block, so it is copied to the stage, now, only from
+  // pageable memory and with nothing pending; the kernel and an upload wait.
   const size_t strain_bytes = (size_t)n * dtype_size(sdt);
   const size_t strain_at = (size_t)round_up((int64_t)(kStageHead + tab_bytes), 256);
   const bool stage_tab = kStageHead + tab_bytes <= kStageBytes;
-  const bool stage_strain = host_strain && stage_tab && strain_at + strain_bytes <= kStageBytes;
+  const bool small_strain = host_strain && stage_tab && strain_at + strain_bytes <= kStageBytes;
+  const void *pinned_strain = small_strain ? device_address(const_cast<void *>(strain)) : nullptr;
+  const bool in_place = pinned_strain && (uintptr_t)pinned_strain % dtype_size(sdt) == 0;
+  const bool stage_strain = small_strain && !pinned_strain && (ctx->own_stream || stream_idle(st));
   char *stage = (char *)ctx->stage;
   std::vector<char> host_tab;   // pageable staging of the tables (no_alloc)
   void *ws_base = nullptr;
@@ -1034,6 +1047,8 @@ static lloid_status filter_banks(lloid_bank *const *banks, int nb, int32_t detec
   if (stage_strain) {
     std::memcpy(stage + strain_at, strain, strain_bytes);
     d_strain = stage + strain_at;
+  } else if (in_place) {
+    d_strain = pinned_strain;
   } else if (host_strain) {
     HIP_TRY(hipMemcpyAsync(strain_tmp, strain, strain_bytes, hipMemcpyHostToDevice, st));
     d_strain = strain_tmp;

@@ -1,0 +1,106 @@
+// CPU tests of the host runtime (lloid_host.cpp) over the test doubles of
+// fake_hip.cpp; built and run by tests/test_host_runtime.py.
+#include <cmath>
+#include <cstdio>
+#include <cstring>
+
+#include "fake_state.h"
+#include "lloid_internal.h"
+
+static int g_fail = 0;
+#define CHECK(cond)                                              \
+  do {                                                           \
+    if (!(cond)) {                                               \
+      std::printf("FAIL %s:%d: %s\n", __FILE__, __LINE__, #cond); \
+      ++g_fail;                                                  \
+    }                                                            \
+  } while (0)
+
+namespace {
+
+hipStream_t caller_stream() {
+  hipStream_t s;
+  (void)hipStreamCreateWithFlags(&s, 0);
+  return s;
+}
+
+lloid_ctx *make_ctx(hipStream_t s) {
+  lloid_ctx *c = nullptr;
+  CHECK(lloid_ctx_create(0, s, &c) == LLOID_OK);
+  return c;
+}
+
+lloid_bank *make_bank(lloid_ctx *c, int templates, int basis, int levels, int f0 = 1024,
+                      lloid_dtype ct = LLOID_F16) {
+  std::vector<double> u((size_t)basis * 64, 0.1), m((size_t)2 * templates * basis, 0.1);
+  std::vector<lloid_slice> sl;
+  for (int k = 0; k < levels; ++k) {
+    lloid_slice s{};
+    s.rate_hz = f0 >> k;
+    s.start_tap = 64 * k;
+    s.n_taps = 64;
+    s.n_basis = basis;
+    s.basis = u.data();
+    s.mixing = m.data();
+    sl.push_back(s);
+  }
+  lloid_bank_desc d{};
+  d.full_rate_hz = f0;
+  d.n_templates = templates;
+  d.n_slices = levels;
+  d.slices = sl.data();
+  d.compute = ct;
+  lloid_bank *b = nullptr;
+  CHECK(lloid_bank_create(c, &d, &b) == LLOID_OK);
+  return b;
+}
+
+bool holds(const std::vector<float> &got, int64_t n, float v) {
+  if ((int64_t)got.size() != n) return false;
+  for (float x : got)
+    if (x != v) return false;
+  return true;
+}
+
+// The strain is read when the context's stream comes to the call, whatever the
+// kind of memory, the block's length and the entry point: work queued there
+// before may still be filling the buffer.
+void strain_in_stream_order() {
+  hipStream_t s = caller_stream();
+  lloid_ctx *c = make_ctx(s);
+  lloid_bank *b = make_bank(c, 4, 16, 1);
+  for (int64_t n : {100, 8192, 100000})
+    for (int kind = 0; kind < 3; ++kind)
+      for (int noalloc = 0; noalloc < 2; ++noalloc)
+        for (int off = 0; off < 2; ++off) {     // a buffer that is not aligned to its samples
+          const size_t bytes = (size_t)n * 4 + 8;
+          void *p = nullptr;
+          if (kind == 0) p = std::malloc(bytes);
+          else CHECK((kind == 1 ? hipHostMalloc(&p, bytes, 0) : hipMalloc(&p, bytes)) == hipSuccess);
+          char *x = (char *)p + 2 * off;
+          for (int64_t i = 0; i < n; ++i) std::memset(x + 4 * i, 0, 4);
+          fake::enqueue(s, [=] {
+            const float v = 3.f;
+            for (int64_t i = 0; i < n; ++i) std::memcpy(x + 4 * i, &v, 4);
+          });
+          lloid_trigger t[4];
+          int64_t nt = 0;
+          const lloid_status r =
+              noalloc ? lloid_filter_noalloc(b, 0, x, LLOID_F32, n, nullptr, t, 4, &nt, nullptr)
+                      : lloid_filter(b, 0, x, LLOID_F32, n, nullptr, t, 4, &nt, nullptr, nullptr);
+          CHECK(r == LLOID_OK);
+          CHECK(holds(fake::state.strain, n, 3.f));
+          if (kind == 0) std::free(p);
+          else (void)(kind == 1 ? hipHostFree(p) : hipFree(p));
+        }
+  lloid_bank_destroy(b);
+  lloid_ctx_destroy(c);
+}
+
+}  // namespace
+
+int main() {
+  strain_in_stream_order();
+  std::printf(g_fail ? "%d checks failed\n" : "ok\n", g_fail);
+  return g_fail != 0;
+}

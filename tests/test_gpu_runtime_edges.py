@@ -53,3 +53,38 @@ def test_short_windows_end_with_the_operand(compute, k, samples):
         lloid.lloid_ctx_set_chunk_bytes(ctx(), 6 << 30)
         lloid.lloid_ctx_set_tiles(ctx(), 0, 0)
         lloid.lloid_bank_destroy(h)
+
+
+@pytest.mark.parametrize("seconds", [4, 60])
+@pytest.mark.parametrize("strain", ["f64", "f32"])
+def test_strain_is_read_in_stream_order(seconds, strain):
+    """A context on the caller's stream: a pinned block that an asynchronous copy
+    on that stream is still to fill, after some ten milliseconds of other work,
+    is filtered as the copy leaves it, small (read where it lies) or large
+    (uploaded); the allocation-free call does the same."""
+    import torch
+    from paper_2410_16416_amd import lloid
+    bank = configs.mini_multirate_bank()
+    n = seconds * bank.f0 + 3
+    dt = torch.float64 if strain == "f64" else torch.float32
+    x = torch.randn(n, dtype=dt, generator=torch.Generator().manual_seed(seconds))
+    st = torch.cuda.Stream()
+    c = lloid.lloid_ctx_create(0, st.cuda_stream)
+    try:
+        h = lloid.bank_from_svd(c, bank, "f16")
+        want = lloid.lloid_filter(h, 0, x.numpy(), window=(1, 4), threshold=2.5, peaks=True)
+        assert want.n_triggers > 0
+        dev, pinned = x.to("cuda"), torch.empty(n, dtype=dt, pin_memory=True)
+        a = torch.randn(4096, 4096, device="cuda")
+        torch.cuda.synchronize()
+        for call in (lloid.lloid_filter, lloid.lloid_filter_noalloc):
+            pinned.zero_()
+            with torch.cuda.stream(st):
+                for _ in range(20):
+                    a = a @ a * 1e-2
+                pinned.copy_(dev, non_blocking=True)
+            got = call(h, 0, pinned.numpy(), window=(1, 4), threshold=2.5, peaks=True)
+            assert np.array_equal(got.triggers, want.triggers) and np.array_equal(got.peak_snr, want.peak_snr)
+        lloid.lloid_bank_destroy(h)
+    finally:
+        lloid.lloid_ctx_destroy(c)
