@@ -418,11 +418,24 @@ struct StageItems {
   bool split = false;              // peaks of some windows are combined from several workgroups
   int64_t up[kMaxHops] = {};       // items of each interpolation launch
   int up_r[kMaxHops] = {};         // smallest factor of its hops
+
+  // Every value that decides a launch: its size, its form or what it clears.
+  void append_to(std::vector<int64_t> &key) const {
+    for (int64_t v : {fir, mix, entries, windows, (int64_t)xi2, (int64_t)xi_kmax, xi_acorr, xi_units, mix_reg,
+                      (int64_t)n_mix_reg, (int64_t)mix_parts, (int64_t)mix_run, (int64_t)split})
+      key.push_back(v);
+    for (int h = 0; h < kMaxHops; ++h) key.push_back(up[h]), key.push_back(up_r[h]);
+  }
 };
 
 struct TabOffsets {
   size_t fir = 0, mix = 0, up[kMaxHops] = {};
   int n_fir = 0, n_mix = 0, n_up[kMaxHops] = {};
+
+  void append_to(std::vector<int64_t> &key) const {
+    for (int64_t v : {(int64_t)fir, (int64_t)mix, (int64_t)n_fir, (int64_t)n_mix}) key.push_back(v);
+    for (int h = 0; h < kMaxHops; ++h) key.push_back((int64_t)up[h]), key.push_back(n_up[h]);
+  }
 };
 
 lloid_status ensure_ws(lloid_ctx *ctx, Workspace &ws, size_t bytes);

@@ -491,25 +491,13 @@ lloid_status enqueue_tick(lloid_stream *s, int64_t wa, int64_t wb, Clock::time_p
   HIP_TRY(hipEventRecord(s->ingest_done, s->ingest));
   HIP_TRY(hipStreamWaitEvent(st, s->ingest_done, 0));
   if (s->use_graph) {
+    // all that the captured launches take from the host
     std::vector<int64_t> key = {(int64_t)(uintptr_t)dtab, (int64_t)(uintptr_t)htab, (int64_t)off, (int64_t)trig_off,
                                 (int64_t)tj.size(), rows, cap, (int64_t)(uintptr_t)counts,
-                                (int64_t)(uintptr_t)tk.htrig, items.fir, items.mix, items.entries, (int64_t)to.fir,
-                                (int64_t)to.mix, to.n_fir, to.n_mix};
-    key.push_back(items.xi2 ? 1 : 0);
-    key.push_back((int64_t)(uintptr_t)xw.units);
-    key.push_back(xw.cap);
-    key.push_back(ctx->fir_variant * 16 + ctx->mix_variant);
-    key.push_back(items.windows);
-    key.push_back(items.mix_parts);
-    key.push_back(items.mix_reg);
-    key.push_back(items.n_mix_reg);
-    key.push_back(items.split ? 1 : 0);
-    for (int h = 0; h < kMaxHops; ++h) {
-      key.push_back(items.up[h]);
-      key.push_back(items.up_r[h]);
-      key.push_back((int64_t)to.up[h]);
-      key.push_back(to.n_up[h]);
-    }
+                                (int64_t)(uintptr_t)tk.htrig, (int64_t)(uintptr_t)xw.units, xw.cap,
+                                ctx->fir_variant * 16 + ctx->mix_variant};
+    items.append_to(key);
+    to.append_to(key);
     if (!tk.exec || key != tk.graph_key) {
       if (tk.exec) (void)hipGraphExecDestroy(tk.exec), tk.exec = nullptr;
       if (tk.graph) (void)hipGraphDestroy(tk.graph), tk.graph = nullptr;

@@ -88,3 +88,53 @@ def test_strain_is_read_in_stream_order(seconds, strain):
         lloid.lloid_bank_destroy(h)
     finally:
         lloid.lloid_ctx_destroy(c)
+
+
+def test_captured_ticks_follow_the_banks_with_lags():
+    """Two banks leave a stream with captured ticks and two of the same sizes
+    enter, but now it is the one of K = 512 and not the one of K = 256 that
+    computes the signal-consistency value: the ticks' buffers and launch sizes
+    are the same, the kernel form is not.  Every trigger equals the offline
+    one, xi2 included."""
+    from paper_2410_16416_amd import lloid
+    from workloads import bank_autocorrelation
+    f0, win, n = 1024, (1, 4), 12 * 1024
+    hs = []
+    try:
+        for lags in (256, 512):
+            for k in (256, 512):
+                bank = configs.random_basis_bank(16, [SliceSpec(f0, 0, 600, k)], f0, np.random.default_rng(2100 + k))
+                if k == lags:
+                    bank.autocorr = bank_autocorrelation(bank, 1)   # one lag: the operands' margins stay as without
+                hs.append(lloid.bank_from_svd(ctx(), bank, "f16"))
+        x = np.random.default_rng(2101).standard_normal(n)
+        s = lloid.lloid_stream_create(ctx(), f0, "f16", n_detectors=1, min_rate_hz=f0, window=win, threshold=2.5,
+                                      max_filter_s=1.0, use_graph=True)
+        try:
+            slots, ends, got = [], [], []
+            for pair, (a, b) in enumerate(((0, n // 2), (n // 2, n))):
+                for h in hs[2 * pair:2 * pair + 2]:
+                    slot, active = lloid.lloid_stream_admit(s, h)
+                    assert active
+                    slots.append(slot)
+                for pos in range(a, b, 256):
+                    lloid.lloid_stream_push(s, 0, pos, x[pos:pos + 256])
+                    got.append(lloid.lloid_stream_poll(s, wait_ms=-1))
+                if pair == 0:
+                    ends.append(lloid.lloid_stream_stats_get(s).next_window)
+                    for slot in slots:
+                        lloid.lloid_stream_remove(s, slot)
+            lloid.lloid_stream_flush(s)
+            got.append(lloid.lloid_stream_poll(s))
+            assert lloid.lloid_stream_stats_get(s).graph_replays > 0
+        finally:
+            lloid.lloid_stream_destroy(s)
+        got = np.concatenate(got)
+        for i, (slot, h) in enumerate(zip(slots, hs)):
+            w_from, w_to = (0, ends[0]) if i < 2 else (ends[0], None)
+            want = offline(lloid, h, [x], win, slot, w_from, w_to, threshold=2.5)
+            assert len(want) > 0
+            assert np.array_equal(canon(got[got["bank"] == slot]), want), slot
+    finally:
+        for h in hs:
+            lloid.lloid_bank_destroy(h)
