@@ -236,9 +236,10 @@ lloid_status lloid_filter(lloid_bank *bank, int32_t detector,
  * buffer of the call comes from one static array per GPU of
  * LLOID_NOALLOC_SCRATCH_BYTES, part of the library's code object (held until
  * the process ends); windows are processed in chunks sized to fit it, and the
- * descriptor tables are staged in the context's 256 KiB of pinned memory or,
- * when they do not fit there, in pageable host memory.  The call makes no
- * hipMalloc, hipHostMalloc or hipFree and records no profiling events.
+ * descriptor tables are staged in 256 KiB of pinned memory that the context
+ * keeps for this call or, when they do not fit there, in pageable host memory.
+ * The call makes no hipMalloc, hipHostMalloc or hipFree, records no profiling
+ * events and shares no buffer with the context's other calls.
  * ENOMEM, before any device work, when one window per chunk (the strain
  * levels, the peak tables, trig_cap trigger records and, for host strain, a
  * copy of it) does not fit the array.  Every call on one GPU, from any

@@ -132,10 +132,10 @@ extern "C" lloid_status lloid_ctx_create(int device, void *hip_stream, lloid_ctx
   c->device = device;
   c->n_cu = prop.multiProcessorCount;
   c->static_scratch = scr;
-  if (hipHostMalloc(&c->stage, kStageBytes, hipHostMallocDefault) != hipSuccess) {
+  if (hipHostMalloc(&c->stage, 2 * kStageBytes, hipHostMallocDefault) != hipSuccess) {
     (void)hipGetLastError();
     delete c;
-    return fail(LLOID_ENOMEM, "pinned staging of %zu bytes failed", kStageBytes);
+    return fail(LLOID_ENOMEM, "pinned staging of %zu bytes failed", 2 * kStageBytes);
   }
   // tile shapes: the defaults, or those named by LLOID_FIR_VARIANT / LLOID_MIX_VARIANT
   if (const char *v = getenv("LLOID_FIR_VARIANT")) c->fir_variant = std::min(std::max(atoi(v), 0), kFirVariants - 1);
@@ -754,7 +754,7 @@ static bool stream_idle(hipStream_t s) {
 // (same context, full rate and operand type) and compact the triggers.
 // no_alloc: every device buffer comes from the context's static scratch
 // (chunks of windows sized to fit it) and descriptor tables that do not fit
-// the context's stage go through pageable host memory: no device or pinned
+// its part of the context's stage go through pageable host memory: no device or pinned
 // allocation, no profiling events.
 static lloid_status filter_banks(lloid_bank *const *banks, int nb, int32_t detector, const void *strain,
                                  lloid_dtype sdt, int64_t n, const lloid_trigger_opts *opts, lloid_trigger *trig,
@@ -922,7 +922,7 @@ static lloid_status filter_banks(lloid_bank *const *banks, int nb, int32_t detec
   const void *pinned_strain = small_strain ? device_address(const_cast<void *>(strain)) : nullptr;
   const bool in_place = pinned_strain && (uintptr_t)pinned_strain % dtype_size(sdt) == 0;
   const bool stage_strain = small_strain && !pinned_strain && (ctx->own_stream || stream_idle(st));
-  char *stage = (char *)ctx->stage;
+  char *stage = stage_part(ctx, no_alloc);
   std::vector<char> host_tab;   // pageable staging of the tables (no_alloc)
   void *ws_base = nullptr;
   if (no_alloc) {
@@ -1308,7 +1308,7 @@ extern "C" lloid_status lloid_coincide(lloid_ctx *ctx, const lloid_trigger *a, i
   int *bad = cv.take<int>(nblk);
   lloid_coinc *dout = host_out ? cv.take<lloid_coinc>((size_t)cap) : out;
   uint8_t *dbg = host_bg ? cv.take<uint8_t>((size_t)(n_a + n_b)) : background;
-  ResultWords *res = (ResultWords *)ctx->stage;
+  ResultWords *res = (ResultWords *)stage_part(ctx, false);
   HIP_TRY(launch_coincide(da, n_a, db, n_b, max_dt, counts, bad, res, cap, dout, dbg, dbg ? dbg + n_a : nullptr, st));
   HIP_TRY(hipStreamSynchronize(st));
   const int64_t h_total = res->total;

@@ -154,9 +154,11 @@ struct lloid_ctx {
   int n_cu = 0;
   lloid::Workspace ws;          // grow-only device scratch of filter calls on this context
   void *static_scratch = nullptr;  // this device's static scratch array (lloid_filter_noalloc)
-  void *stage = nullptr;        // pinned host memory the kernels read and write: kStageBytes, kept
-                                // with the context: a call's result words, then tables and strain
-                                // that fit
+  // Pinned host memory the kernels read and write, kept with the context: a
+  // call's result words, then tables and strain that fit.  Two parts of
+  // kStageBytes: the second is lloid_filter_noalloc's, which shares no buffer
+  // with the context's other calls and may overlap them.
+  void *stage = nullptr;
   void *pinned = nullptr;       // pinned host staging for descriptor tables that do not
   size_t pinned_bytes = 0;
   int64_t chunk_budget = int64_t(6) << 30;  // device bytes of per-chunk operands
@@ -169,12 +171,15 @@ struct lloid_ctx {
 };
 
 namespace lloid {
-// The context's pinned stage: result words (ResultWords), then staged inputs.
+// A part of the context's pinned stage: result words (ResultWords), then staged inputs.
 constexpr size_t kStageBytes = size_t(256) << 10, kStageHead = 256;
 struct ResultWords {
   int64_t total;   // triggers or pairs
   int bad;         // strain sample not finite / lists out of order
 };
+inline char *stage_part(const lloid_ctx *ctx, bool no_alloc) {
+  return (char *)ctx->stage + (no_alloc ? kStageBytes : 0);
+}
 }  // namespace lloid
 
 struct lloid_bank {

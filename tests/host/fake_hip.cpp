@@ -111,6 +111,11 @@ hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned int) {
 }
 hipError_t hipStreamDestroy(hipStream_t s) { return fake::drain(s), hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t s) {
+  if (fake::state.before_sync) {
+    auto f = std::move(fake::state.before_sync);
+    fake::state.before_sync = nullptr;
+    f();
+  }
   fake::drain(s);
   return fails("hipStreamSynchronize") ? hipErrorUnknown : hipSuccess;
 }
@@ -162,6 +167,7 @@ hipError_t launch_ingest(const IngestArgs &a, lloid_dtype dt, hipStream_t s) {
       if (v != v) *a.bad = 1;
       fake::state.strain.push_back(a.dst[k]);
     }
+    if (fake::state.on_strain) fake::state.on_strain(fake::state.strain);
   });
   return hipSuccess;
 }

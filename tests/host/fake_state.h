@@ -14,6 +14,8 @@ constexpr float kTable = 0.25f;   // every entry of a filled transform window
 
 struct State {
   std::vector<float> strain;             // what the last ingest launch converted, when it ran
+  std::function<void(const std::vector<float> &)> on_strain;   // the same, each time
+  std::function<void()> before_sync;     // runs once, when a stream is next waited for: another thread's call
   float table = 0.f;                     // a transform window entry as the last conditioning launch saw it
   int64_t triggers = 0, pairs = 0;       // counts that the next calls report
   std::string fail_at;                   // call or launch that fails, once

@@ -97,10 +97,47 @@ void strain_in_stream_order() {
   lloid_ctx_destroy(c);
 }
 
+// A call of the allocation-free form shares nothing with the other calls of the
+// context: one that comes between another's launches and its wait leaves that
+// one's strain, tables and result words alone, and the other way round.
+void noalloc_calls_overlap_others() {
+  lloid_ctx *c = make_ctx(nullptr);
+  lloid_bank *b = make_bank(c, 4, 16, 1);
+  const int64_t n = 3000;
+  const std::vector<float> one((size_t)n, 1.f), two((size_t)n, 2.f);
+  lloid_trigger t[8], t2[8];
+  int64_t nt = 0, nt2 = 0;
+  lloid_coinc pairs[8];
+  auto filter = [&](const std::vector<float> &x, lloid_trigger *t, int64_t *nt, int triggers, bool noalloc) {
+    fake::state.triggers = triggers;
+    CHECK((noalloc ? lloid_filter_noalloc(b, 0, x.data(), LLOID_F32, n, nullptr, t, 8, nt, nullptr)
+                   : lloid_filter(b, 0, x.data(), LLOID_F32, n, nullptr, t, 8, nt, nullptr, nullptr)) == LLOID_OK);
+  };
+  filter(one, t, &nt, 0, false);   // the context's workspace has its size
+  for (int inner = 0; inner < 2; ++inner) {
+    std::vector<std::vector<float>> seen;
+    fake::state.on_strain = [&](const std::vector<float> &x) { seen.push_back(x); };
+    fake::state.before_sync = [&] { filter(two, t2, &nt2, 5, inner == 1); };
+    filter(one, t, &nt, 3, inner == 0);
+    CHECK(nt == 3 && nt2 == 5);
+    CHECK(seen.size() == 2 && holds(seen[0], n, 1.f) && holds(seen[1], n, 2.f));
+    fake::state.on_strain = nullptr;
+  }
+  int64_t np = 0;
+  fake::state.pairs = 7;
+  fake::state.before_sync = [&] { filter(two, t2, &nt2, 5, true); };
+  std::memset(t, 0, sizeof t);
+  CHECK(lloid_coincide(c, t, 8, t, 8, 3, pairs, 8, &np, nullptr) == LLOID_OK);
+  CHECK(np == 7 && nt2 == 5);
+  lloid_bank_destroy(b);
+  lloid_ctx_destroy(c);
+}
+
 }  // namespace
 
 int main() {
   strain_in_stream_order();
+  noalloc_calls_overlap_others();
   std::printf(g_fail ? "%d checks failed\n" : "ok\n", g_fail);
   return g_fail != 0;
 }
