@@ -744,6 +744,22 @@ lloid_status lloid::launch_stages(lloid_ctx *ctx, lloid_dtype ct, const char *dt
   return LLOID_OK;
 }
 
+// Waits for the stream when a call is left before its own last wait: work it
+// has queued reads and writes the context's pinned memory and the caller's
+// buffers, which the next call, or the caller, may touch at once.
+class WaitOnError {
+ public:
+  explicit WaitOnError(hipStream_t s) : s_(s) {}
+  ~WaitOnError() {
+    if (!done_) (void)hipStreamSynchronize(s_);
+  }
+  void done() { done_ = true; }
+
+ private:
+  hipStream_t s_;
+  bool done_ = false;
+};
+
 static bool stream_idle(hipStream_t s) {
   const hipError_t e = hipStreamQuery(s);
   if (e != hipSuccess) (void)hipGetLastError();
@@ -1035,6 +1051,7 @@ static lloid_status filter_banks(lloid_bank *const *banks, int nb, int32_t detec
   auto mark = [&](int stage, int end) -> hipError_t {
     return prof ? hipEventRecord(ctx->ev[2 * stage + end], st) : hipSuccess;
   };
+  WaitOnError queued(st);
   HIP_TRY(mark(LLOID_STAGE_INGEST, 0));
   IngestArgs in;
   if (htab == (char *)host_tab.data()) {
@@ -1121,6 +1138,7 @@ static lloid_status filter_banks(lloid_bank *const *banks, int nb, int32_t detec
   if (ncopy > 0) HIP_TRY(hipMemcpyAsync(trig, dtrig, (size_t)ncopy * sizeof(lloid_trigger), hipMemcpyDefault, st));
   HIP_TRY(mark(LLOID_STAGE_D2H, 1));
   if (ncopy > 0 || prof) HIP_TRY(hipStreamSynchronize(st));
+  queued.done();
   if (prof) {
     for (int i = 0; i < LLOID_N_STAGES; ++i) {
       float ms = 0.f;
@@ -1212,6 +1230,7 @@ extern "C" lloid_status lloid_condition(lloid_ctx *ctx, int32_t full_rate_hz, co
   if (rs != LLOID_OK) return rs;
   rs = ensure_pinned(ctx, ctx->pinned, ctx->pinned_bytes, res_bytes);
   if (rs != LLOID_OK) return rs;
+  WaitOnError queued(st);
   Carve cv{(char *)ctx->ws.base};
   const void *d_strain = strain;
   if (host_strain) {
@@ -1258,6 +1277,7 @@ extern "C" lloid_status lloid_condition(lloid_ctx *ctx, int32_t full_rate_hz, co
   HIP_TRY(hipMemcpyAsync(hres, res, psd_out ? res_bytes : 16, hipMemcpyDeviceToHost, st));
   if (host_out) HIP_TRY(hipMemcpyAsync(out, c.out, (size_t)n * 4, hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
+  queued.done();
   const int h_bad = *(const int *)(hres + 8);
   const unsigned long long h_count = *(const unsigned long long *)hres;
   if (psd_out)
@@ -1292,6 +1312,7 @@ extern "C" lloid_status lloid_coincide(lloid_ctx *ctx, const lloid_trigger *a, i
   if (host_bg) add((size_t)(n_a + n_b), 1);
   lloid_status rs = ensure_ws(ctx, ctx->ws, bytes);
   if (rs != LLOID_OK) return rs;
+  WaitOnError queued(st);
   Carve cv{(char *)ctx->ws.base};
   const lloid_trigger *da = a, *db = b;
   if (host_a) {
@@ -1320,6 +1341,7 @@ extern "C" lloid_status lloid_coincide(lloid_ctx *ctx, const lloid_trigger *a, i
   if (host_bg && n_a + n_b > 0)
     HIP_TRY(hipMemcpyAsync(background, dbg, (size_t)(n_a + n_b), hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
+  queued.done();
   *n_out = h_total;
   if (h_total > cap) return fail(LLOID_ETRUNC, "%lld coincidences, capacity %lld", (long long)h_total, (long long)cap);
   return LLOID_OK;

@@ -133,11 +133,59 @@ void noalloc_calls_overlap_others() {
   lloid_ctx_destroy(c);
 }
 
+// A call that fails between its first launch and its wait leaves nothing queued.
+void failed_calls_leave_nothing_queued() {
+  hipStream_t s = caller_stream();
+  lloid_ctx *c = make_ctx(s);
+  lloid_bank *b = make_bank(c, 4, 16, 3);
+  const int64_t n = 60000;   // an upload of its own
+  std::vector<float> x((size_t)n, 1.f), out((size_t)n);
+  std::vector<double> psd(129, 1.0);
+  lloid_trigger t[8] = {};
+  lloid_coinc pairs[8];
+  uint8_t bg[16];
+  lloid_condition_opts co{};
+  co.seg_len = 256;
+  auto call = [&](int which) -> lloid_status {
+    int64_t k = 0;
+    switch (which) {
+      case 0: return lloid_filter(b, 0, x.data(), LLOID_F32, n, nullptr, t, 8, &k, nullptr, nullptr);
+      case 1: return lloid_filter_noalloc(b, 0, x.data(), LLOID_F32, 900, nullptr, t, 8, &k, nullptr);
+      case 2: co.psd = nullptr; return lloid_condition(c, 1024, x.data(), LLOID_F32, n, &co, out.data(), psd.data(), &k);
+      case 3: co.psd = psd.data(); return lloid_condition(c, 1024, x.data(), LLOID_F32, n, &co, out.data(), nullptr, &k);
+      default: return lloid_coincide(c, t, 8, t, 8, 3, pairs, 8, &k, bg);
+    }
+  };
+  fake::state.triggers = 3;
+  fake::state.pairs = 3;
+  for (int which = 0; which < 5; ++which) CHECK(call(which) == LLOID_OK);   // workspaces have their sizes
+  int failed = 0;
+  for (const char *name : {"launch_ingest", "launch_decimate", "launch_fir_jobs", "launch_up_jobs", "launch_mix_jobs",
+                           "launch_mix_reg", "launch_peak_phase", "launch_trigger_jobs", "launch_condition",
+                           "launch_coincide", "hipMemcpyAsync"})
+    for (int which = 0; which < 5; ++which)
+      for (int skip = 0; skip < 6; ++skip) {
+        fake::state.fail_at = name;
+        fake::state.fail_skip = skip;
+        const lloid_status r = call(which);
+        const bool hit = fake::state.fail_at.empty();
+        fake::state.fail_at.clear();
+        CHECK(hit ? r != LLOID_OK : r == LLOID_OK);
+        CHECK(fake::pending(s) == 0);
+        failed += hit;
+        CHECK(call(which) == LLOID_OK);
+      }
+  CHECK(failed >= 30);
+  lloid_bank_destroy(b);
+  lloid_ctx_destroy(c);
+}
+
 }  // namespace
 
 int main() {
   strain_in_stream_order();
   noalloc_calls_overlap_others();
+  failed_calls_leave_nothing_queued();
   std::printf(g_fail ? "%d checks failed\n" : "ok\n", g_fail);
   return g_fail != 0;
 }
