@@ -1239,13 +1239,19 @@ extern "C" lloid_status lloid_condition(lloid_ctx *ctx, int32_t full_rate_hz, co
     d_strain = p;
   }
   if (!ctx->d_fft_tw) {   // the first conditioning call of the context makes its transform tables
-    if (hipMalloc(&ctx->d_fft_tw, kCondMaxLen * (sizeof(float2) + sizeof(float))) != hipSuccess) {
+    float2 *tw = nullptr;
+    if (hipMalloc(&tw, kCondMaxLen * (sizeof(float2) + sizeof(float))) != hipSuccess) {
       (void)hipGetLastError();
-      ctx->d_fft_tw = nullptr;
       return fail(LLOID_ENOMEM, "cannot allocate the transform tables");
     }
-    ctx->d_fft_win = (float *)(ctx->d_fft_tw + kCondMaxLen);
-    HIP_TRY(launch_fft_tables(ctx->d_fft_tw, ctx->d_fft_win, st));
+    float *fft_win = (float *)(tw + kCondMaxLen);
+    const hipError_t e = launch_fft_tables(tw, fft_win, st);
+    if (e != hipSuccess) {
+      (void)hipFree(tw);
+      return fail(LLOID_EDEVICE, "the transform tables failed: %s", hipGetErrorString(e));
+    }
+    ctx->d_fft_tw = tw;   // the context's once they are being filled
+    ctx->d_fft_win = fft_win;
   }
   CondArgs c;
   c.T = n;

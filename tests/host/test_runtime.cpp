@@ -180,12 +180,35 @@ void failed_calls_leave_nothing_queued() {
   lloid_ctx_destroy(c);
 }
 
+// A conditioning call whose transform tables could not be made leaves none
+// behind: the next one makes them.
+void transform_tables_are_whole() {
+  lloid_ctx *c = make_ctx(nullptr);
+  const int64_t n = 600;
+  std::vector<float> x((size_t)n, 1.f), out((size_t)n);
+  lloid_condition_opts co{};
+  co.seg_len = 256;
+  for (const char *name : {"launch_fft_tables", "hipMalloc"}) {
+    const bool alloc = std::strcmp(name, "hipMalloc") == 0;
+    if (alloc) lloid_ctx_destroy(c), c = make_ctx(nullptr);
+    fake::state.table = 0.f;
+    fake::state.fail_skip = alloc ? 1 : 0;   // the workspace, then the tables
+    fake::state.fail_at = name;
+    CHECK(lloid_condition(c, 1024, x.data(), LLOID_F32, n, &co, out.data(), nullptr, nullptr) != LLOID_OK);
+    CHECK(fake::state.fail_at.empty());
+    CHECK(lloid_condition(c, 1024, x.data(), LLOID_F32, n, &co, out.data(), nullptr, nullptr) == LLOID_OK);
+    CHECK(fake::state.table == fake::kTable);
+  }
+  lloid_ctx_destroy(c);
+}
+
 }  // namespace
 
 int main() {
   strain_in_stream_order();
   noalloc_calls_overlap_others();
   failed_calls_leave_nothing_queued();
+  transform_tables_are_whole();
   std::printf(g_fail ? "%d checks failed\n" : "ok\n", g_fail);
   return g_fail != 0;
 }
