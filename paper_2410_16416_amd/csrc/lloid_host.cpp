@@ -511,6 +511,9 @@ void lloid::interp_fragments(const double *g, int R, int ks_elems, int vec, std:
       }
 }
 
+// 32-column blocks that a job's channels touch (a channel-major job's start at column 0).
+static int up_rtiles(const UpJob &q) { return (int)ceil_div(q.col0 % 32 + q.channels, 32); }
+
 void lloid::add_bank_jobs(const lloid_bank *b, const LevelView *lv, int64_t t0, int64_t t1, int64_t n_end, int64_t wa,
                           int64_t wb, const Windows &win, const BankBufs &bb, float inv_scale, float *snr,
                           int64_t snr_ld, const TileShapes &ts, std::vector<FirJob> &fj, std::vector<UpJob> *uj,
@@ -568,9 +571,7 @@ void lloid::add_bank_jobs(const lloid_bank *b, const LevelView *lv, int64_t t0, 
         q.n_hi = p.out[h].hi;
         q.n_first = floor_div(p.out[h].lo, 32) * 32;
         q.n_ctiles = (int)ceil_div(p.out[h].hi - q.n_first, kUpCols);
-        q.n_rtiles = (int)ceil_div(sl.lp, 32);
         if (h + 1 == H) {
-          q.n_rtiles = (int)ceil_div(sl.koff % 32 + sl.lp, 32);
           q.dst = bb.ocat;
           q.dst_abs0 = e0;
           q.ld_dst = b->kld;
@@ -582,7 +583,7 @@ void lloid::add_bank_jobs(const lloid_bank *b, const LevelView *lv, int64_t t0, 
           q.ld_dst = (int)ld[h + 1];
           q.dst_tm = 0;
         }
-        q.grp_rtiles = q.n_rtiles;
+        q.grp_rtiles = up_rtiles(q);
         uj[kMaxHops - H + h].push_back(q);   // the last hops of all slices in one launch
       }
     }
@@ -591,10 +592,10 @@ void lloid::add_bank_jobs(const lloid_bank *b, const LevelView *lv, int64_t t0, 
   }
   std::vector<UpJob> &tm = uj[kMaxHops - 1];
   for (size_t k = tm0 + 1; k < tm.size(); ++k) {
-    tm[k].grp = (int)(k - tm0);
-    tm[k].rt0 = tm[k - 1].rt0 + tm[k - 1].n_rtiles;
+    tm[k].grp = 1;
+    tm[k].rt0 = tm[k - 1].rt0 + up_rtiles(tm[k - 1]);
   }
-  for (size_t k = tm0; k < tm.size(); ++k) tm[k].grp_rtiles = tm.back().rt0 + tm.back().n_rtiles;
+  for (size_t k = tm0; k < tm.size(); ++k) tm[k].grp_rtiles = tm.back().rt0 + up_rtiles(tm.back());
   MixJob m{};
   m.mix = b->mix;
   m.ocat = bb.ocat;
@@ -611,7 +612,6 @@ void lloid::add_bank_jobs(const lloid_bank *b, const LevelView *lv, int64_t t0, 
   m.acorr_half = b->acorr_half;
   m.snr = snr;
   m.ocat_abs0 = e0;
-  m.ocat_end = e1;
   m.snr_abs0 = t0;
   m.n_end = n_end;
   m.w0 = wa;
@@ -654,7 +654,7 @@ void lloid::number_jobs(lloid_dtype ct, std::vector<FirJob> &fj, std::vector<UpJ
     // 8 runs (one per XCD) of ceil(tasks / 32) items of 4 tasks
     for (size_t k = 0; k < uj[h].size(); ++k) {
       UpJob &q = uj[h][k];
-      n.up_r[h] = k ? std::min(n.up_r[h], q.r) : q.r;
+      n.up_r[h] = k ? std::min<int>(n.up_r[h], q.r) : q.r;
       if (q.grp) q.item0 = uj[h][k - 1].item0;
       else q.item0 = it, it += 8 * ceil_div((int64_t)q.grp_rtiles * q.n_ctiles, 32);
     }
@@ -865,8 +865,9 @@ static lloid_status filter_banks(lloid_bank *const *banks, int nb, int32_t detec
       if (sl.level > 0) n_up += up_plan(0, 1, sl.level).r.size();
     }
   auto table_bytes = [&](int64_t chunks) -> size_t {
+    // (a chunk's 2 + kMaxHops tables start at multiples of 64)
     return (size_t)chunks * (n_fir * sizeof(FirJob) + n_up * sizeof(UpJob) + nb * sizeof(MixJob) +
-                             64 * (3 + kMaxHops)) +
+                             64 * (2 + kMaxHops)) +
            nb * sizeof(TrigJob) + 256;
   };
   // signal-consistency units of the banks with lags over a chunk of wpc_ windows

@@ -73,11 +73,12 @@ struct UpJob {
   void *dst;             // dst_tm: dst[(n - dst_abs0) * ld_dst + col0 + c]; else dst[c * ld_dst + n - dst_abs0]
   int64_t src_lo, dst_abs0, n_lo, n_hi, n_first, item0;   // n_first: first tile start (multiple of 32)
   int64_t src_bytes;     // extent of src for the buffer resource
-  int ld_src, ld_dst, col0, channels, r, dst_tm, n_ctiles, n_rtiles;
+  int ld_src, ld_dst, col0, channels, n_ctiles;
   // The last hops of a bank's slices form a group (neighbours in the table, the
   // same column tiles and item0): its tasks run over all their row tiles, so that
   // a row of the operand is written at one time.  Other jobs are alone in theirs.
-  int grp, rt0, grp_rtiles;   // place in the group, row tiles before this job, row tiles of the group
+  int rt0, grp_rtiles;         // row tiles before this job in its group, and of the group
+  int r : 16, dst_tm : 8, grp : 8;   // grp: 0 for the first job of a group
 };
 
 // Mixing + peaks of one bank over trigger windows [w0, w0 + nw).
@@ -96,7 +97,6 @@ struct MixJob {
   int64_t ocat_abs0, n_end, w0, nw, win_p, win_q, ld_peak, w_base, snr_ld, snr_abs0, item0, e0;
   int64_t x0;                 // first (job, window) item of this job in the signal-consistency launches
   int64_t t0;                 // first entry of this job's peak table in the order of the trigger compaction
-  int64_t ocat_end;           // absolute sample past the operand's last row
   int64_t *xi_key;            // listing slab [ld_peak][n_templates] of trigger keys (banks with lags)
   float inv_scale;
   int rows, kcat, n_templates, n_rtiles, acorr_half;
@@ -134,7 +134,8 @@ struct TrigJob {
 };
 
 // Entries per trigger-compaction block, and the per-block count slots that
-// n_elems entries need (the scan also keeps the total after them).
+// n_elems entries need.  The ingest kernel clears them, the phase kernel counts
+// in them; the callers lay the peak tables' samples right behind them.
 constexpr int kTrigPerBlock = 1024;
 inline int64_t trig_blocks(int64_t n_elems) { return (n_elems + kTrigPerBlock - 1) / kTrigPerBlock; }
 

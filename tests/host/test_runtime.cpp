@@ -7,6 +7,8 @@
 #include "fake_state.h"
 #include "lloid_internal.h"
 
+using namespace lloid;
+
 static int g_fail = 0;
 #define CHECK(cond)                                              \
   do {                                                           \
@@ -37,7 +39,7 @@ lloid_bank *make_bank(lloid_ctx *c, int templates, int basis, int levels, int f0
   for (int k = 0; k < levels; ++k) {
     lloid_slice s{};
     s.rate_hz = f0 >> k;
-    s.start_tap = 64 * k;
+    s.start_tap = 128 * k;
     s.n_taps = 64;
     s.n_basis = basis;
     s.basis = u.data();
@@ -202,9 +204,65 @@ void transform_tables_are_whole() {
   lloid_ctx_destroy(c);
 }
 
+// What the allocation-free call takes of its scratch with one window per chunk
+// has not grown past what callers have sized their blocks for: the longest block
+// whose strain levels, peak tables, operands, low-rate buffers and tables (of
+// 120, 112, 240 and 88 bytes an entry) come to the scratch's size is accepted.
+void noalloc_accepts_what_fits() {
+  lloid_ctx *c = make_ctx(nullptr);
+  const int f0 = 1024, win_len = 4, F = 600;
+  for (int levels : {1, 3, 8}) {
+    lloid_bank *b = make_bank(c, F, 16, levels, f0);
+    auto need = [&](int64_t W) {
+      const int64_t n = W * win_len;
+      size_t bytes = 0, n_fir = 0, n_up = 0;
+      auto add = [&](size_t cnt, size_t sz) { bytes = (size_t)round_up((int64_t)bytes, 256) + cnt * sz; };
+      Range sup{0, n};
+      for (int k = 0; k < levels; ++k, sup = halo_up(sup)) add((size_t)sup.size(), 4);
+      const size_t tab = (size_t)F * W;
+      for (size_t sz : {4, 8, 4, 4, 4, 4, 8}) add(tab, sz);
+      const int64_t ops = std::min<int64_t>(n, win_len + 1) + 2;
+      add((size_t)ops * b->kld, 2);
+      for (const auto &sl : b->slices) {
+        ++n_fir;
+        if (sl.level > 0)
+          for (int64_t ld : low_ld(ops, sl.level)) add((size_t)sl.lp * ld, 2), ++n_up;
+      }
+      add((size_t)trig_blocks((int64_t)tab) + 2, 8);
+      add(1, 4);
+      add(0, sizeof(XiUnit));
+      add(2, 4);
+      add(8, sizeof(lloid_trigger));
+      add((size_t)W * (n_fir * 120 + n_up * 112 + 240 + 64 * (3 + kMaxHops)) + 88 + 256, 1);
+      return bytes;
+    };
+    int64_t lo = 1, hi = int64_t(1) << 24;
+    while (hi - lo > 1) {
+      const int64_t mid = (lo + hi) / 2;
+      (need(mid) <= (size_t)LLOID_NOALLOC_SCRATCH_BYTES ? lo : hi) = mid;
+    }
+    void *x = nullptr;
+    CHECK(hipMalloc(&x, (size_t)lo * win_len * 4) == hipSuccess);
+    std::memset(x, 0, (size_t)lo * win_len * 4);
+    lloid_trigger_opts o{};
+    o.window_num = win_len;
+    o.window_den = f0;
+    o.threshold = 4.f;
+    lloid_trigger t[8];
+    int64_t nt = 0;
+    const lloid_status r = lloid_filter_noalloc(b, 0, x, LLOID_F32, lo * win_len, &o, t, 8, &nt, nullptr);
+    CHECK(r == LLOID_OK);
+    if (r != LLOID_OK) std::printf("%lld windows: %s\n", (long long)lo, lloid_last_error());
+    (void)hipFree(x);
+    lloid_bank_destroy(b);
+  }
+  lloid_ctx_destroy(c);
+}
+
 }  // namespace
 
 int main() {
+  noalloc_accepts_what_fits();
   strain_in_stream_order();
   noalloc_calls_overlap_others();
   failed_calls_leave_nothing_queued();
