@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "lloid_internal.h"
+#include "lloid_loud.h"
 
 using namespace lloid;
 
@@ -1222,7 +1223,8 @@ extern "C" lloid_status lloid_condition(lloid_ctx *ctx, int32_t full_rate_hz, co
   add((size_t)(nseg_p * nf), 4);           // periodograms
   add((size_t)nf, 4);                      // gain
   add((size_t)(nseg_w * L), 4);            // whitened segments
-  if (gating) add((size_t)ceil_div(n, 64), 8);
+  const size_t loud_n = gating ? (size_t)(loud_words(n) + loud_summary_words(n)) : 0;
+  if (gating) add(loud_n, 8);
   if (host_out) add((size_t)n, 4);
   // results in one block: the gated count, the data flag, the PSD (FP32 on the device)
   const size_t res_bytes = 16 + (size_t)nf * 4;
@@ -1265,7 +1267,7 @@ extern "C" lloid_status lloid_condition(lloid_ctx *ctx, int32_t full_rate_hz, co
   c.parts = cv.take<float>((size_t)(nseg_p * nf));
   c.gain = cv.take<float>((size_t)nf);
   c.y = cv.take<float>((size_t)(nseg_w * L));
-  if (gating) c.loud = cv.take<uint64_t>((size_t)ceil_div(n, 64));
+  if (gating) c.loud = cv.take<uint64_t>(loud_n);
   c.out = host_out ? cv.take<float>((size_t)n) : out;
   char *res = cv.take<char>(res_bytes);
   c.count = (unsigned long long *)res;

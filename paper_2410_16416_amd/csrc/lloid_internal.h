@@ -306,7 +306,7 @@ struct CondArgs {
   float *parts = nullptr;          // [segments inside the block][L/2 + 1]
   float *psd = nullptr, *gain = nullptr;   // [L/2 + 1]
   float *y = nullptr;              // [segments touching the block][L]
-  uint64_t *loud = nullptr;        // ceil(T / 64) words, gating only
+  uint64_t *loud = nullptr;        // loud_words(T) + loud_summary_words(T) words, gating only
   float *out = nullptr;
   unsigned long long *count = nullptr;
   int *bad = nullptr;

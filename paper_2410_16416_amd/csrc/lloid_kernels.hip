@@ -18,6 +18,7 @@
 
 #include "lloid_device.h"
 #include "lloid_internal.h"
+#include "lloid_loud.h"
 
 namespace lloid {
 
@@ -2145,7 +2146,7 @@ template <int LG, bool WHITEN, typename TI>
 __global__ __launch_bounds__(CondShape<LG>::THREADS) void k_cond_segment(
     const TI *__restrict__ x, int64_t T, int64_t seg0, int64_t nseg, const float2 *__restrict__ tw,
     const float *__restrict__ win, const float *__restrict__ gain, float *__restrict__ parts, float *__restrict__ y,
-    int *__restrict__ bad) {
+    int *__restrict__ bad, uint64_t *__restrict__ summary, int64_t n_summary) {
   typedef CondShape<LG> S;
   constexpr int L = S::L, NT = S::NT;
   __shared__ float2 buf[S::SEGS * (L + L / 8)];
@@ -2168,6 +2169,12 @@ __global__ __launch_bounds__(CondShape<LG>::THREADS) void k_cond_segment(
     v[c] = make_float2(u * h * h, 0.f);
   }
   if (WHITEN && !finite) atomicOr(bad, 1);
+  // the loud samples' summary bits, which the next launch sets (its T / 4032
+  // words at most: L/8 threads for every L/2 samples are here)
+  if constexpr (WHITEN) {
+    const int64_t t = (int64_t)blockIdx.x * S::THREADS + threadIdx.x;
+    if (t < n_summary) summary[t] = 0;
+  }
   float2 *seg = buf + sg * (L + L / 8);
   fft_regs<LG, -1>(v, seg, tw, j);
   if constexpr (!WHITEN) {
@@ -2259,7 +2266,7 @@ __global__ void k_psd_gain(const float *__restrict__ psd, int nf, float f0, floa
 
 // out[n] = the two segments' outputs over sample n (segment m starts at m h,
 // h = L/2 = 2^lgh; y holds segments seg0, seg0 + 1, ...).  loud: NULL, or one
-// bit per sample, set where |out[n]| > thr.
+// bit per sample, set where |out[n]| > thr, and their cleared summary bits.
 constexpr int kOverlapPer = 4;   // samples per thread, 256 apart
 
 __global__ __launch_bounds__(256) void k_overlap_add(const float *__restrict__ y, int64_t T, int lgh, int64_t seg0,
@@ -2279,45 +2286,49 @@ __global__ __launch_bounds__(256) void k_overlap_add(const float *__restrict__ y
     }
     if (loud) {
       const uint64_t m = __ballot(l);
-      if ((threadIdx.x & 63) == 0 && n < T) loud[n >> 6] = m;
+      if ((threadIdx.x & 63) == 0 && n < T) {
+        loud[n >> 6] = m;
+        if (m)
+          loud_mark(loud, T, n >> 6, [](uint64_t *p, uint64_t bit) {
+            return (uint64_t)atomicOr((unsigned long long *)p, (unsigned long long)bit);
+          });
+      }
     }
   }
 }
 
 // Zeroes every sample within half_width of a loud one and counts them.  A
-// workgroup first looks for any loud sample in its reach (its own samples and
+// workgroup first asks for any loud sample in its reach (its own samples and
 // half_width on each side): transients are rare, so nearly all leave there.
+// Latency decides: a reach of up to kGateWords words is read in one round, a word
+// per thread; a longer one, and a sample's own question, take at most two words
+// of each level, whatever the half width.  2^21 samples, half width 512: 4.8 us
+// (8 with the second question alone); a call of 2^24 samples with a half width
+// of 10^6: 436 us, with one loud sample 791, where reading every word in reach
+// took 835 us and 16.2 ms.
 constexpr int kGateSpan = 512;    // samples per workgroup
-constexpr int kGateWords = 1024;  // words of its reach kept in LDS (half widths up to 32 thousand samples)
+constexpr int kGateWords = 256;   // half widths up to 7900 samples
 
 __global__ __launch_bounds__(256) void k_gate(const uint64_t *__restrict__ loud, int64_t T, int64_t half_width,
                                               float *__restrict__ out, unsigned long long *__restrict__ count) {
-  __shared__ uint64_t lw[kGateWords];
   const int64_t n0 = (int64_t)blockIdx.x * kGateSpan;
-  const int64_t w0 = max<int64_t>(0, n0 - half_width) >> 6;
-  const int64_t w1 = min<int64_t>(T - 1, n0 + kGateSpan - 1 + half_width) >> 6;
-  int any = 0;
-  for (int64_t w = w0 + threadIdx.x; w <= w1; w += 256) {
-    const uint64_t m = loud[w];
-    any |= m != 0;
-    if (w - w0 < kGateWords) lw[w - w0] = m;
+  const int64_t a0 = max<int64_t>(0, n0 - half_width), e0 = min<int64_t>(T - 1, n0 + kGateSpan - 1 + half_width);
+  const int64_t w = (a0 >> 6) + threadIdx.x;
+  if ((e0 >> 6) - (a0 >> 6) < kGateWords) {
+    if (!__syncthreads_or(w <= (e0 >> 6) && loud[w])) return;
+  } else if (!loud_any(loud, T, a0, e0)) {
+    return;
   }
-  if (!__syncthreads_or(any)) return;
-  const uint64_t *words = w1 - w0 < kGateWords ? lw : loud + w0;
+  bool g[kGateSpan / 256];
+#pragma unroll
   for (int q = 0; q < kGateSpan / 256; ++q) {
     const int64_t n = n0 + q * 256 + threadIdx.x;
-    bool g = false;
-    if (n < T) {
-      const int64_t a = max<int64_t>(0, n - half_width), e = min<int64_t>(T - 1, n + half_width);
-      for (int64_t w = a >> 6; w <= (e >> 6) && !g; ++w) {
-        uint64_t m = words[w - w0];
-        if (w == (a >> 6)) m &= ~0ull << (a & 63);
-        if (w == (e >> 6)) m &= ~0ull >> (63 - (e & 63));
-        g = m != 0;
-      }
-      if (g) out[n] = 0.f;
-    }
-    const uint64_t m = __ballot(g);
+    g[q] = n < T && loud_any(loud, T, max<int64_t>(0, n - half_width), min<int64_t>(T - 1, n + half_width));
+  }
+#pragma unroll
+  for (int q = 0; q < kGateSpan / 256; ++q) {
+    if (g[q]) out[n0 + q * 256 + threadIdx.x] = 0.f;
+    const uint64_t m = __ballot(g[q]);
     if ((threadIdx.x & 63) == 0 && m) atomicAdd(count, (unsigned long long)__popcll(m));
   }
 }
@@ -2718,15 +2729,16 @@ static void cond_passes(const TI *x, const CondArgs &c, hipStream_t s) {
   if (c.estimate) {
     const int64_t nseg = (c.T - L) / (L / 2) + 1;
     k_cond_segment<LG, false, TI><<<blocks_for(nseg, S::SEGS), S::THREADS, 0, s>>>(x, c.T, 0, nseg, c.tw, c.win, nullptr,
-                                                                                    c.parts, nullptr, nullptr);
+                                                                                    c.parts, nullptr, nullptr, nullptr, 0);
     k_psd_mean<<<blocks_for(nf, 64), 256, 0, s>>>(c.parts, nseg, L, c.f0, c.psd, c.gain);
   } else {
     k_psd_gain<<<blocks_for(nf, 256), 256, 0, s>>>(c.psd, nf, c.f0, c.gain);
   }
   const int64_t nseg_w = (2 * (c.T - 1)) / L + 2;   // segments -1 .. floor(2 (T - 1) / L)
-  k_cond_segment<LG, true, TI><<<blocks_for(nseg_w, S::SEGS), S::THREADS, 0, s>>>(x, c.T, -1, nseg_w, c.tw, c.win, c.gain,
-                                                                                   nullptr, c.y, c.bad);
   const bool gating = c.gate_thr > 0.f;
+  k_cond_segment<LG, true, TI><<<blocks_for(nseg_w, S::SEGS), S::THREADS, 0, s>>>(
+      x, c.T, -1, nseg_w, c.tw, c.win, c.gain, nullptr, c.y, c.bad, gating ? c.loud + loud_words(c.T) : nullptr,
+      gating ? loud_summary_words(c.T) : 0);
   k_overlap_add<<<blocks_for(c.T, 256 * kOverlapPer), 256, 0, s>>>(c.y, c.T, LG - 1, -1, c.gate_thr, c.out,
                                                                     gating ? c.loud : nullptr);
   if (gating) k_gate<<<blocks_for(c.T, kGateSpan), 256, 0, s>>>(c.loud, c.T, c.gate_half, c.out, c.count);

@@ -138,3 +138,27 @@ def test_captured_ticks_follow_the_banks_with_lags():
     finally:
         for h in hs:
             lloid.lloid_bank_destroy(h)
+
+
+@pytest.mark.parametrize("half", [0, 63, 4095, 4096, 262143, 262145, 2 ** 31 - 1])
+@pytest.mark.parametrize("loud", [(), (300000,), (0, 599999), tuple(range(5, 600000, 90001))])
+def test_gate_reach_over_the_summary_levels(half, loud):
+    """Half widths around a word of the loud samples' bits and of each level of
+    summary bits (64, 4096 and 262144 samples) and past the block: the gated
+    samples and their number are the oracle's; a call without gating is the
+    same where nothing is gated."""
+    import oracle
+    from paper_2410_16416_amd import lloid
+    L, thr, n = 256, 20.0, 600000
+    x = np.random.default_rng(2200).standard_normal(n)
+    x[list(loud)] += 4000.0
+    flat = np.full(L // 2 + 1, 2.0 / 1024)     # the identity: white noise of unit variance
+    plain, _, _ = lloid.lloid_condition(ctx(), 1024, x, L, psd=flat)
+    out, _, gated = lloid.lloid_condition(ctx(), 1024, x, L, thr, half, psd=flat)
+    near = np.zeros(n, dtype=bool)
+    for k in np.nonzero(np.abs(plain) > thr)[0]:
+        near[max(0, k - half):k + half + 1] = True
+    assert gated == near.sum() and np.array_equal(out, np.where(near, 0, plain))
+    if half < 10 ** 6:
+        want, count = oracle.gate(oracle.whiten(x, 1024, L, flat), thr, half)
+        assert gated == count and np.array_equal(out == 0, want == 0)
