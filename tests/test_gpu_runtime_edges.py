@@ -5,10 +5,12 @@ a call's reads on the caller's stream, what a captured tick depends on."""
 import numpy as np
 import pytest
 
+import oracle
+
 from workloads import configs
 from workloads.bank import SliceSpec
 
-from gpu_util import ctx
+from gpu_util import EPS_ABS, ctx
 from test_gpu_stream import canon, offline, run_stream
 
 pytestmark = pytest.mark.gpu
@@ -147,7 +149,6 @@ def test_gate_reach_over_the_summary_levels(half, loud):
     summary bits (64, 4096 and 262144 samples) and past the block: the gated
     samples and their number are the oracle's; a call without gating is the
     same where nothing is gated."""
-    import oracle
     from paper_2410_16416_amd import lloid
     L, thr, n = 256, 20.0, 600000
     x = np.random.default_rng(2200).standard_normal(n)
@@ -162,3 +163,52 @@ def test_gate_reach_over_the_summary_levels(half, loud):
     if half < 10 ** 6:
         want, count = oracle.gate(oracle.whiten(x, 1024, L, flat), thr, half)
         assert gated == count and np.array_equal(out == 0, want == 0)
+
+
+@pytest.mark.parametrize("compute", ["f16", "bf16"])
+@pytest.mark.parametrize("samples", [512, 128, 2048])
+def test_both_mixing_forms_in_one_call(compute, samples):
+    """Banks on both sides of K = 640 in one batched call and in one streaming
+    tick: the direct-to-LDS form and the register-held one are two launches over
+    one table, with row tiles, splits and item numbers of their own.  The block
+    is 32 windows of 512 samples (the split rules then share windows in the
+    first form only), 128 of 128 (in neither; in the ticks in the second only) or
+    8 of 2048 (in both).  Peaks
+    against the oracle, and bit for bit those of the banks alone, of a tile
+    shape that takes every bank, and of the ticks."""
+    from paper_2410_16416_amd import lloid
+    f0, n, win = 1024, 16384, (samples, 1024)
+    banks = [configs.random_basis_bank(f, [SliceSpec(f0, 0, 720, k)], f0, np.random.default_rng(2300 + k))
+             for f, k in ((129, 500), (100, 672), (200, 40), (90, 700), (300, 640))]
+    x = np.random.default_rng(2301).standard_normal(n)
+    hs = [lloid.bank_from_svd(ctx(), b, compute) for b in banks]
+    try:
+        wide = [lloid.lloid_bank_query(h).concat_k > 640 for h in hs]
+        assert wide == [False, True, False, True, False]
+        both = lloid.lloid_filter_batch(hs, 0, x, window=win, threshold=3.0, peaks=True)
+        lloid.lloid_ctx_set_tiles(ctx(), 0, 4)
+        other = lloid.lloid_filter_batch(hs, 0, x, window=win, threshold=3.0, peaks=True)
+        lloid.lloid_ctx_set_tiles(ctx(), 0, 0)
+        assert np.array_equal(both.triggers, other.triggers) and both.n_triggers > 0
+        for k, (h, b) in enumerate(zip(hs, banks)):
+            one = lloid.lloid_filter(h, 0, x, window=win, threshold=3.0, peaks=True)
+            _, want, _, _ = oracle.peak_table(oracle.lloid_snr(b, x[:4096]), 0, f0, *win)
+            # (the oracle's block ends at 4096 samples: windows that end before it)
+            m = 4096 // samples
+            assert np.max(np.abs(one.peak_snr[:, :m] - want[:, :m])) < EPS_ABS[compute]
+            for r in (both, other):
+                assert np.array_equal(r.peak_snr[k], one.peak_snr)
+                assert np.array_equal(r.peak_sample[k], one.peak_sample)
+        s = lloid.lloid_stream_create(ctx(), f0, compute, n_detectors=1, min_rate_hz=f0, window=win, threshold=3.0,
+                                      max_filter_s=1.0, max_windows_per_tick=4)
+        try:
+            for h in hs:
+                assert lloid.lloid_stream_admit(s, h)[1]
+            got = run_stream(lloid, s, [x], [2 * samples])
+        finally:
+            lloid.lloid_stream_destroy(s)
+        assert np.array_equal(canon(got), canon(both.triggers))
+    finally:
+        lloid.lloid_ctx_set_tiles(ctx(), 0, 0)
+        for h in hs:
+            lloid.lloid_bank_destroy(h)
