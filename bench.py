@@ -39,7 +39,7 @@ METRIC = "template-samples of SNR/sec (1 GPU) at stated SNR error; p99 stride la
 PEAK_TFLOPS = {"f16": 2516.6, "bf16": 2516.6, "f32": 157.3}   # dense MFMA, MI355X
 PEAK_HBM_GBS = 8000.0
 PROFILES = os.path.join(ROOT, "profiles")
-KERNEL_SRC = os.path.join(ROOT, "paper_2410_16416_amd", "csrc", "lloid_kernels.hip")
+CSRC = os.path.join(ROOT, "paper_2410_16416_amd", "csrc")
 TILE_CACHE = os.path.join(ROOT, "paper_2410_16416_amd", "tiles_gfx950.json")
 
 
@@ -48,8 +48,14 @@ def log(msg):
 
 
 def kernel_hash() -> str:
-    with open(KERNEL_SRC, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+    """Of every source that device code is compiled from (kernel files and headers)."""
+    h = hashlib.sha256()
+    for name in sorted(os.listdir(CSRC)):
+        if name.endswith((".hip", ".h")):
+            h.update(name.encode() + b"\0")
+            with open(os.path.join(CSRC, name), "rb") as f:
+                h.update(f.read() + b"\0")
+    return h.hexdigest()[:16]
 
 
 def stage_work(bank, seconds: float, compute: str):
