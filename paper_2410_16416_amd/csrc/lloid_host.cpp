@@ -646,7 +646,10 @@ void lloid::number_jobs(lloid_dtype ct, std::vector<FirJob> &fj, std::vector<UpJ
   // longest items first (a narrow tile takes about 3/8 of a wide one's time)
   auto cost = [](const FirJob &j) { return j.narrow ? 3 * (int64_t)j.np : 8 * (int64_t)j.np; };
   std::stable_sort(fj.begin(), fj.end(), [&](const FirJob &a, const FirJob &b) { return cost(a) > cost(b); });
-  std::stable_sort(mj.begin(), mj.end(), [](const MixJob &a, const MixJob &b) { return a.kcat > b.kcat; });
+  auto reg = [&](const MixJob &m) { return mix_reg_job(ct, ts.mix_variant, m); };
+  std::stable_sort(mj.begin(), mj.end(), [&](const MixJob &a, const MixJob &b) {
+    return reg(a) != reg(b) ? reg(b) : a.kcat > b.kcat;   // the register-held launch's jobs last
+  });
   int64_t it = 0;
   for (auto &j : fj) j.item0 = it, it += (int64_t)j.n_rtiles * j.n_ctiles;
   n.fir = it;
@@ -664,10 +667,8 @@ void lloid::number_jobs(lloid_dtype ct, std::vector<FirJob> &fj, std::vector<UpJ
   it = 0;
   int64_t e = 0, rows = 0, windows = 0, reg_rows = 0, reg_total = 0;   // (windows: the same for every job)
   const int64_t tpw = ceil_div(win_len, kMixRegTile);
-  auto reg = [&](const MixJob &m) { return mix_reg_job(ct, ts.mix_variant, m); };
   for (auto &m : mj)
     if (reg(m)) {
-      // (jobs are sorted by kcat: these are the last ones)
       m.n_rtiles = (int)ceil_div(m.rows, kMixRegRows);
       reg_rows += m.n_rtiles;
       reg_total = std::max(reg_total, m.nw * tpw);

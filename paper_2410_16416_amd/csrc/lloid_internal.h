@@ -265,7 +265,7 @@ hipError_t launch_up_jobs(lloid_dtype t, const UpJob *jobs, int n_jobs, int64_t 
 // The jobs for which mix_reg_job holds come last in the table and are launched
 // by launch_mix_reg, their items numbered from 0.
 inline bool mix_reg_job(lloid_dtype t, int variant, const MixJob &m) {
-  return t != LLOID_F32 && variant == 0 && m.kcat <= 640 && !m.snr;
+  return t != LLOID_F32 && variant == 0 && !m.snr && mix_reg_fits(m.kcat, ceil_div(m.win_p, m.win_q));
 }
 constexpr int kMixRegRows = 256, kMixRegTile = 32;   // mixing rows of a workgroup, samples of an operand tile
 hipError_t launch_mix_reg(lloid_dtype t, const MixJob *jobs, int n_jobs, int64_t n_items, hipStream_t s);

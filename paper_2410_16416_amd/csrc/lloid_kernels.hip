@@ -2631,9 +2631,9 @@ static hipError_t mix_t(int variant, const MixJob *jobs, int n_jobs, int64_t n_i
       else return mix_v<T, kMixMT, kMixNT, kMixWM, kMixWN, 32>(jobs, n_jobs, n_items, with_snr, s);
     default:
       // 16-bit operands: direct-to-LDS K chunks of 64, eight 64 x 128 waves.  Takes
-      // the SNR series (485 us with it against 535 for the register-held form, 48 s
-      // of 1024 templates) and a concatenated K above 640, whose mixing fragments
-      // no longer fit the registers; the rest is launch_mix_reg's.
+      // the SNR series (a 48 s call of 1024 templates 485 us, 535 with the
+      // register-held form) and what mix_reg_fits leaves it: a concatenated K above
+      // 640, and small ones on long windows; the rest is launch_mix_reg's.
       if constexpr (sizeof(T) == 2) {
         if (with_snr) k_mix_dl<T, 4, 2, 2, 4, 64, 1, true><<<(unsigned)n_items, 512, 0, s>>>(jobs, n_jobs);
         else k_mix_dl<T, 4, 2, 2, 4, 64, 1, false><<<(unsigned)n_items, 512, 0, s>>>(jobs, n_jobs);

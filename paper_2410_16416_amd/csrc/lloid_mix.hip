@@ -1,5 +1,6 @@
 // Mixing and window peaks with the mixing rows held in registers (16-bit
-// operands, concatenated K up to 640, no SNR series).
+// operands, concatenated K up to 640, below 128 only with short windows, no SNR
+// series: mix_reg_job).
 //
 // Y[c, n] = sum_k M[c, k] O[n, k]; rows 2i and 2i + 1 (cos, sin) of template i
 // land in the same lane, so |z|^2 and the running per-template peak stay in
@@ -25,7 +26,7 @@
 // arithmetic of a tile left after its MFMAs 3.36 ms, with the mixing fragments
 // in the vector registers' spare places and copied for each use 3.66 ms.  The
 // SNR series stays with k_mix_dl: stores of 256 bytes per template and tile
-// here against 2 KB there, 48 s of 1024 templates 535 against 472 us.
+// here against 2 KB there, a call of 48 s and 1024 templates 535 against 485 us.
 //
 // A K up to 512 fills the accumulation registers.  Up to 640 the last k-steps'
 // fragments take 64 of the vector registers and the ring has three tiles

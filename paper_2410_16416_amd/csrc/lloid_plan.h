@@ -147,6 +147,20 @@ constexpr int64_t kMixRegRun = 256;
 constexpr double kMixRegOverhead = 4.0;
 int64_t mix_reg_run(int64_t total, int64_t row_tiles, int64_t slots);
 
+// Whether the register-held mixing form takes a concatenated K and windows of
+// win_len samples (16-bit operands, no SNR series).  Beyond K = 640 its mixing
+// fragments do not fit the registers.  Below K = 128 its arithmetic per tile, the
+// same for every K, outlasts the products, and the direct-to-LDS form, which
+// pays more per window, is faster on long windows.  Register-held against
+// direct-to-LDS, 1024 templates on 2^20 samples, windows of 512, 1024, 2048, 4096
+// and 16384 samples: K = 32 0.82, 1.09, 1.36, 1.58, 1.83 of its time; K = 64 0.73,
+// 0.92, 1.08, 1.22, 1.37; K = 96 0.63, 0.75, 0.85, 0.95, 1.02; K = 128 0.63, 0.77,
+// 0.89, 0.96, 1.01 (BF16 within 0.06 of these).
+inline bool mix_reg_fits(int kcat, int64_t win_len) {
+  if (kcat > 640) return false;
+  return kcat >= 128 || win_len <= (kcat < 96 ? 16 * (int64_t)kcat : 4096);
+}
+
 // Whether a FIR job of `taps` takes narrow tiles (a quarter of the columns)
 // in a launch whose jobs need `work` = sum over jobs of wide tiles x taps, on
 // `n_cu` CUs: where a wide tile, on a CU shared by two, lasts longer than the

@@ -259,9 +259,56 @@ void noalloc_accepts_what_fits() {
   lloid_ctx_destroy(c);
 }
 
+// The two mixing launches split one table: the register-held form's jobs come
+// last, each part longest K first, and the items of each launch are numbered
+// from 0 in the order of its jobs.
+void mixing_forms_split_the_table() {
+  // beyond K = 640 and, on long windows, below K = 128 the direct-to-LDS form is used
+  CHECK(mix_reg_fits(640, 1 << 20) && !mix_reg_fits(672, 1));
+  CHECK(mix_reg_fits(32, 512) && !mix_reg_fits(32, 1024) && mix_reg_fits(64, 1024) && !mix_reg_fits(64, 2048));
+  CHECK(mix_reg_fits(96, 4096) && !mix_reg_fits(96, 16384) && mix_reg_fits(128, 1 << 20));
+  const int ks[] = {96, 672, 32, 640, 64, 128, 1024, 160};
+  for (int64_t win_len : {33, 1024, 2048, 100000})
+    for (lloid_dtype ct : {LLOID_F16, LLOID_F32})
+      for (int variant : {0, 3}) {
+        const TileShapes ts(ct, 0, variant);
+        std::vector<FirJob> fj;
+        std::vector<UpJob> uj[kMaxHops];
+        std::vector<MixJob> mj;
+        for (int k : ks) {
+          MixJob m{};
+          m.kcat = k;
+          m.kld = (int)round_up(k, 64);
+          m.rows = 512;
+          m.n_templates = 200;
+          m.nw = 11;
+          m.win_p = win_len;
+          m.win_q = 1;
+          m.n_rtiles = (int)ceil_div(m.rows, ts.mbm);
+          mj.push_back(m);
+        }
+        StageItems n;
+        number_jobs(ct, fj, uj, mj, win_len, ts, 256, n);
+        const int dl = (int)mj.size() - n.n_mix_reg;
+        int64_t next[2] = {0, 0}, e = 0;
+        for (int i = 0; i < (int)mj.size(); ++i) {
+          const bool r = mix_reg_job(ct, variant, mj[i]);
+          CHECK(r == (i >= dl));
+          CHECK(i == 0 || i == dl || mj[i - 1].kcat >= mj[i].kcat);
+          CHECK(mj[i].item0 == next[r]);
+          const int64_t units = r ? ceil_div(mj[i].nw * mj[i].tpw, mj[i].run) : mj[i].nw * mj[i].parts;
+          next[r] += units >= 8 ? ceil_div(units, 8) * 8 * mj[i].n_rtiles : round_up(units * mj[i].n_rtiles, 8);
+          CHECK(mj[i].e0 == e);
+          e += mj[i].nw * mj[i].n_templates;
+        }
+        CHECK(n.mix == next[0] && n.mix_reg == next[1] && n.entries == e);
+      }
+}
+
 }  // namespace
 
 int main() {
+  mixing_forms_split_the_table();
   noalloc_accepts_what_fits();
   strain_in_stream_order();
   noalloc_calls_overlap_others();
