@@ -64,8 +64,8 @@ __global__ __launch_bounds__(256) void k_ingest(IngestArgs a, int tab_blocks, in
 // kDecimGroup levels in one launch: a workgroup owns a run of samples of the
 // deepest level and the samples over them at the levels between, loads the
 // finer level's samples those need into LDS (32 more on each side per level)
-// and cascades there, recomputing the halos (23 % more sums at four levels of
-// 4096-sample runs).  A launch per level cost four launches and their gaps:
+// and cascades there, recomputing the halos (at four levels of 4096-sample runs
+// 18 % more sums, 23 % more samples read).  A launch per level cost four launches and their gaps:
 // 38.5 us of kernels for 1024 s at 2048 Hz against 21, 12 against 8.5 us for 8 s.
 constexpr int kDecimSpan = 4096;                            // finer-level samples a workgroup owns at most
 constexpr int kDecimBuf = kDecimSpan + 64 * ((1 << kDecimGroup) - 1) + 64;
@@ -565,8 +565,9 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void k_fir(const FirJob *
 // brings its 32 source rows' windows to LDS with coalesced direct loads (read
 // from memory as fragments, every lane's 16 bytes were a line of their own, and each
 // block was read twice: 59 against 82 us for FP32, 48 s), works tile by tile, so
-// that a tile's stores go out while the next is computed (few registers, five
-// waves per SIMD), writes 32-column blocks that start at the operand's own 32-column grid
+// that a tile's stores go out while the next is computed (few registers: with
+// 16-bit sources five or six waves per SIMD; FP32 sources' windows leave LDS for
+// two or three), writes 32-column blocks that start at the operand's own 32-column grid
 // with a dword per lane, without bounds checks inside, and the tasks run over
 // all slices' blocks of a column tile.  Before and after: FP32, 48 s 109 -> 59 us;
 // FP16, 48 s with the series 37 -> 22, 8 s 17 -> 13, 1024 s 630 -> 554; BF16, 200 s
@@ -2515,7 +2516,7 @@ hipError_t launch_decimate(DecimArgs a, hipStream_t s) {
     hi = std::max(hi, ((lv.hi - 1) >> (K - k)) + 1);
   }
   if (hi <= lo) return hipSuccess;
-  // runs of 4096 finer-level samples, or of 1024 (twice the halo work) where
+  // runs of 4096 finer-level samples, or of 1024 (four times as many halos) where
   // the long ones would leave CUs without a workgroup
   a.span = kDecimSpan >> K;
   if (hi - lo <= 256 * (int64_t)a.span) a.span = (kDecimSpan / 4) >> K;
